@@ -52,7 +52,8 @@ def ops_per_pair(n_se, n_lin):
     return 25 + 2 * n_se + (n_lin + 2 if n_lin else 0)
 
 
-KERNEL_SOURCES = ("paper_2012_03683_amd/csrc/cvo_pairs.hip", "paper_2012_03683_amd/csrc/cvo_internal.hpp")
+KERNEL_SOURCES = ("paper_2012_03683_amd/csrc/cvo_pairs.hip", "paper_2012_03683_amd/csrc/cvo_device.hpp",
+                  "paper_2012_03683_amd/csrc/cvo_internal.hpp")
 TRAFFIC_FILE = os.path.join(ROOT, "profiles", "pair_pass_traffic.json")
 
 

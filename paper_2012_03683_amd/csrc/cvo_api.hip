@@ -8,6 +8,7 @@
 
 #include <algorithm>
 #include <cmath>
+#include <cstddef>
 #include <cstdio>
 #include <cstring>
 #include <map>
@@ -160,6 +161,12 @@ struct cvo_context {
         fixed.top += need;
         fixed.regions[name] = {off, need};
         return fixed.base + off;
+    }
+    // elements a buffer of the arena has room for without growing
+    template <class T> size_t room(const std::string &name) const
+    {
+        auto it = bufs.find(name);
+        return it == bufs.end() ? 0 : it->second.cap / sizeof(T);
     }
     template <class T> T *get_t(const std::string &name, size_t count)
     {
@@ -448,73 +455,11 @@ FeatLayout make_layout(const cvo_feature_spec *sp, double sigma)
     return L;
 }
 
-// ------------------------------------------------------------------ views
-struct GridView {
-    int B = 0;
-    std::vector<GridDesc> desc;
-    GridDesc *d_desc = nullptr;
-    float4 *pts = nullptr;
-    float *feat = nullptr;
-    int *perm = nullptr;
-    int *cell_start = nullptr;
-    long long ntot = 0;
-    std::vector<double> rc;
-};
-
-struct ClusterView {
-    int B = 0;
-    std::vector<ClusterDesc> desc;
-    ClusterDesc *d_desc = nullptr;
-    float4 *pts = nullptr;
-    float *feat = nullptr;
-    int *perm = nullptr;
-    int2 *clus = nullptr;
-    double4 *cgeo = nullptr;
-    int *cpair = nullptr;
-    int *tclus = nullptr;  // cluster of every sorted point
-    int nclus = 0;
-    long long ntot = 0;
-    std::vector<double> rc;
-};
-
 int bits_for(unsigned long long v)
 {
     int b = 0;
     while ((1ULL << b) <= v && b < 63) ++b;
     return b;
-}
-
-// bounding boxes and the non-finite check
-// Bounding boxes of one call's clouds, kept for the views rebuilt later in
-// the same call (the clouds cannot change while a call runs).
-struct BoxCache {
-    std::vector<float> box;
-    CloudPtrs *dc = nullptr;
-};
-
-std::vector<float> cloud_boxes(cvo_context *ctx, const std::string &pre, const std::vector<CloudPtrs> &cl,
-                               CloudPtrs **d_clouds, BoxCache *cache = nullptr)
-{
-    if (cache && cache->dc) {
-        *d_clouds = cache->dc;
-        return cache->box;
-    }
-    const int B = (int)cl.size();
-    CloudPtrs *dc = ctx->get_t<CloudPtrs>(pre + ".clouds", B);
-    ctx->upload(dc, cl.data(), sizeof(CloudPtrs) * B);
-    float *d_box = ctx->get_t<float>(pre + ".box", 8 * B);
-    launch_bbox(dc, B, d_box, ctx->stream);
-    ctx->check_launch("bbox");
-    std::vector<float> box(8 * B);
-    ctx->download(box.data(), d_box, sizeof(float) * 8 * B);
-    for (int c = 0; c < B; ++c)
-        require(box[8 * c + 6] == 0.0f, "a cloud has non-finite coordinates");
-    *d_clouds = dc;
-    if (cache) {
-        cache->box = box;
-        cache->dc = dc;
-    }
-    return box;
 }
 
 // Shape of the views of one pair: query points per cluster, grid cell edge
@@ -575,293 +520,145 @@ ViewShape density_shape(cvo_context *ctx, int cls, const FeatLayout &lay)
     }
 }
 
-GridView build_grid(cvo_context *ctx, const std::string &pre, const std::vector<CloudPtrs> &cl,
-                    const std::vector<double> &rc, const FeatLayout &lay, const std::vector<ViewShape> &shape,
-                    BoxCache *bc = nullptr)
-{
-    GridView v;
-    const int B = (int)cl.size();
-    v.B = B;
-    v.rc = rc;
-    CloudPtrs *dc = nullptr;
-    std::vector<float> box = cloud_boxes(ctx, pre, cl, &dc, bc);
-    const long long cell_cap = 1LL << 23;
-    v.desc.resize(B);
-    long long cell_base = 0, pt_base = 0, max_cells = 0, nmax = 0;
-    std::vector<long long> bases(B);
-    for (int c = 0; c < B; ++c) {
-        GridDesc &g = v.desc[c];
-        std::memset(&g, 0, sizeof(g));
-        const long long n = cl[c].n;
-        if (n == 0) {
-            g.ox = g.oy = g.oz = 0.0;
-            g.h = 1.0;
-            g.inv_h = 1.0;
-            g.nx = g.ny = g.nz = 1;
-        } else {
-            const double lo[3] = {box[8 * c], box[8 * c + 1], box[8 * c + 2]};
-            const double hi[3] = {box[8 * c + 3], box[8 * c + 4], box[8 * c + 5]};
-            double ext = std::max({hi[0] - lo[0], hi[1] - lo[1], hi[2] - lo[2], 1e-6});
-            double h = std::isfinite(rc[c]) ? shape[c].cell_factor * rc[c] : ext * 1.01;
-            h = std::max(h, ext * 1e-6);
-            int nn[3];
-            double inv = 1.0 / h;
-            for (;;) {
-                inv = 1.0 / h;
-                long long tot = 1;
-                for (int k = 0; k < 3; ++k) {
-                    // same expression as the device binning: floor((p - o) * inv_h)
-                    nn[k] = (int)std::floor((hi[k] - lo[k]) * inv) + 1;
-                    tot *= nn[k];
-                }
-                if (tot <= cell_cap && nn[0] < (1 << 30) / std::max(1, nn[1])) break;
-                h *= 1.25;
-            }
-            g.ox = lo[0];
-            g.oy = lo[1];
-            g.oz = lo[2];
-            g.h = h;
-            g.inv_h = inv;
-            g.nx = nn[0];
-            g.ny = nn[1];
-            g.nz = nn[2];
-        }
-        g.cell_base = (int)cell_base;
-        g.pt_base = pt_base;
-        g.n = n;
-        bases[c] = pt_base;
-        const long long nc = (long long)g.nx * g.ny * g.nz;
-        max_cells = std::max(max_cells, nc);
-        cell_base += nc + 1;
-        pt_base += n;
-        nmax = std::max(nmax, n);
-    }
-    require(cell_base < (1LL << 31), "cell tables too large");
-    v.ntot = pt_base;
-    const int kbits = bits_for((unsigned long long)max_cells);  // max_cells itself must fit
-    const int cbits = bits_for((unsigned long long)(B > 1 ? B - 1 : 0));
-    require(kbits + cbits <= 62, "grid keys exceed 62 bits");
-    v.d_desc = ctx->get_t<GridDesc>(pre + ".desc", B);
-    ctx->upload(v.d_desc, v.desc.data(), sizeof(GridDesc) * B);
-    long long *d_base = ctx->get_t<long long>(pre + ".base", B);
-    ctx->upload(d_base, bases.data(), sizeof(long long) * B);
-
-    const long long ntot = std::max(v.ntot, 1LL);
-    unsigned long long *keys = ctx->get_t<unsigned long long>(pre + ".keys", ntot);
-    unsigned long long *ktmp = ctx->get_t<unsigned long long>(pre + ".ktmp", ntot);
-    int *vals = ctx->get_t<int>(pre + ".vals", ntot);
-    int *vtmp = ctx->get_t<int>(pre + ".vtmp", ntot);
-    const long long ntiles = (ntot + kRadixTile - 1) / kRadixTile;
-    int *hist = ctx->get_t<int>(pre + ".hist", ntiles * 256);
-    int *bsum = ctx->get_t<int>(pre + ".bsum", (ntiles * 256 + 2047) / 2048 + 1);
-    v.pts = ctx->get_t<float4>(pre + ".pts", ntot);
-    v.feat = ctx->get_t<float>(pre + ".feat", ntot * std::max(lay.d4, 1));
-    v.perm = ctx->get_t<int>(pre + ".perm", ntot);
-    v.cell_start = ctx->get_t<int>(pre + ".cells", cell_base);
-    if (v.ntot > 0) {
-        launch_grid_keys(dc, v.d_desc, B, nmax, keys, vals, kbits, ctx->stream);
-        bool in_tmp = false;
-        launch_radix_sort(keys, vals, ktmp, vtmp, hist, bsum, v.ntot, kbits + cbits, ctx->stream, &in_tmp);
-        if (in_tmp) { std::swap(keys, ktmp); std::swap(vals, vtmp); }
-        launch_gather(keys, vals, v.ntot, kbits, dc, d_base, lay, v.pts, v.feat, v.perm, ctx->stream);
-    }
-    launch_cell_table(keys, v.ntot, v.d_desc, B, max_cells, kbits, v.cell_start, ctx->stream);
-    ctx->check_launch("grid build");
-    return v;
-}
-
-ClusterView build_clusters(cvo_context *ctx, const std::string &pre, const std::vector<CloudPtrs> &cl,
-                           const std::vector<double> &rc, const FeatLayout &lay, const std::vector<ViewShape> &shape,
-                           BoxCache *bc = nullptr)
-{
-    ClusterView v;
-    const int B = (int)cl.size();
-    v.B = B;
-    v.rc = rc;
-    CloudPtrs *dc = nullptr;
-    std::vector<float> box = cloud_boxes(ctx, pre, cl, &dc, bc);
-    const int cbits = bits_for((unsigned long long)(B > 1 ? B - 1 : 0));
-    const int maxbits = std::min(19, (62 - cbits) / 3);
-    std::vector<ClusterBuild> cb(B);
-    std::vector<int2> lcap(B);  // (largest octree level, max points per cluster)
-    std::vector<long long> bases(B);
-    v.desc.resize(B);
-    long long pt_base = 0, nmax = 0, nchunks = 0;
-    bool any_chunks = false, any_octree = false;
-    int bits = 1;  // Morton bits per axis: as many as the widest cloud needs
-    for (int c = 0; c < B; ++c) {
-        const long long n = cl[c].n;
-        ClusterBuild &g = cb[c];
-        std::memset(&g, 0, sizeof(g));
-        double lo[3] = {0, 0, 0}, ext = 1.0;
-        if (n > 0) {
-            for (int k = 0; k < 3; ++k) lo[k] = box[8 * c + k];
-            ext = std::max({box[8 * c + 3] - lo[0], box[8 * c + 4] - lo[1], box[8 * c + 5] - lo[2], 1e-6});
-        }
-        const double cap = std::isfinite(rc[c]) ? shape[c].cluster_factor * rc[c] : ext * 2.0;
-        // octree blocks need 16 quanta per cap; chunks only use the Morton
-        // order, which a finer quantum makes more local
-        const bool chunks = shape[c].rule == CVO_CLUSTER_CHUNKS;
-        int L = chunks ? 6 : 4;
-        double q = cap / (double)(1 << L);
-        // quanta needed to cover the box must fit in maxbits per axis
-        if (ext / q + 1.0 > (double)(1 << maxbits)) {
-            q = ext / ((double)(1 << maxbits) - 2.0);
-            L = std::max(0, (int)std::floor(std::log2(std::max(cap / q, 1.0))));
-        }
-        L = std::min(L, maxbits);
-        // quanta along the widest axis (+1 for rounding at the far face)
-        bits = std::max({bits, L, bits_for((unsigned long long)std::floor(ext / q) + 1)});
-        g.ox = lo[0];
-        g.oy = lo[1];
-        g.oz = lo[2];
-        g.q = q;
-        g.pt_base = pt_base;
-        g.n = n;
-        g.cap = cap;
-        g.chunk_base = nchunks;
-        nchunks += (n + shape[c].cluster_max - 1) / shape[c].cluster_max;
-        any_chunks = any_chunks || chunks;
-        // (octree level -1 marks a cloud clustered by the chunk rule)
-        lcap[c] = make_int2(chunks ? -1 : L, shape[c].cluster_max);
-        any_octree = any_octree || !chunks;
-        bases[c] = pt_base;
-        ClusterDesc &d = v.desc[c];
-        d.clus_base = 0;
-        d.nclus = 0;
-        d.pt_base = (int)pt_base;
-        d.n = (int)n;
-        pt_base += n;
-        nmax = std::max(nmax, n);
-    }
-    v.ntot = pt_base;
-    bits = std::min(bits, maxbits);
-    ClusterBuild *d_cb = ctx->get_t<ClusterBuild>(pre + ".cb", B);
-    ctx->upload(d_cb, cb.data(), sizeof(ClusterBuild) * B);
-    long long *d_base = ctx->get_t<long long>(pre + ".base", B);
-    ctx->upload(d_base, bases.data(), sizeof(long long) * B);
-    int2 *d_lcap = ctx->get_t<int2>(pre + ".lcap", B);
-    ctx->upload(d_lcap, lcap.data(), sizeof(int2) * B);
-    v.d_desc = ctx->get_t<ClusterDesc>(pre + ".desc", B);
-
-    const long long ntot = std::max(v.ntot, 1LL);
-    unsigned long long *keys = ctx->get_t<unsigned long long>(pre + ".keys", ntot);
-    unsigned long long *ktmp = ctx->get_t<unsigned long long>(pre + ".ktmp", ntot);
-    int *vals = ctx->get_t<int>(pre + ".vals", ntot);
-    int *vtmp = ctx->get_t<int>(pre + ".vtmp", ntot);
-    const long long ntiles = (ntot + kRadixTile - 1) / kRadixTile;
-    int *hist = ctx->get_t<int>(pre + ".hist", std::max(ntiles * 256, ntot));
-    int *bsum = ctx->get_t<int>(pre + ".bsum", (std::max(ntiles * 256, ntot) + 2047) / 2048 + 1);
-    v.pts = ctx->get_t<float4>(pre + ".pts", ntot);
-    v.feat = ctx->get_t<float>(pre + ".feat", ntot * std::max(lay.d4, 1));
-    v.perm = ctx->get_t<int>(pre + ".perm", ntot);
-    v.clus = ctx->get_t<int2>(pre + ".clus", ntot);
-    v.cgeo = ctx->get_t<double4>(pre + ".cgeo", ntot);
-    v.cpair = ctx->get_t<int>(pre + ".cpair", ntot);
-    v.tclus = ctx->get_t<int>(pre + ".tclus", ntot);
-    int *head = ctx->get_t<int>(pre + ".head", ntot);
-    int *hidx = ctx->get_t<int>(pre + ".hidx", ntot);
-    int2 *span = ctx->get_t<int2>(pre + ".span", ntot);
-    int *d_total = ctx->get_t<int>(pre + ".total", 1);
-    v.nclus = 0;
-    if (v.ntot > 0) {
-        launch_morton_keys(dc, d_cb, B, nmax, keys, vals, bits, ctx->stream);
-        bool in_tmp = false;
-        launch_radix_sort(keys, vals, ktmp, vtmp, hist, bsum, v.ntot, 3 * bits + cbits, ctx->stream, &in_tmp);
-        if (in_tmp) { std::swap(keys, ktmp); std::swap(vals, vtmp); }
-        launch_gather(keys, vals, v.ntot, 3 * bits, dc, d_base, lay, v.pts, v.feat, v.perm, ctx->stream);
-        // each cloud by its own rule: the octree kernel skips chunk-rule
-        // clouds, and chunks exist only for chunk-rule clouds
-        if (any_octree) launch_cluster_heads(keys, v.ntot, d_lcap, 3 * bits, head, span, ctx->stream);
-        if (any_chunks) launch_chunk_heads(v.pts, d_cb, d_lcap, B, nchunks, head, span, ctx->stream);
-        launch_exclusive_scan(head, hidx, bsum, v.ntot, d_total, ctx->stream);
-        launch_cluster_emit(head, hidx, span, v.pts, keys, 3 * bits, v.ntot, v.clus, v.cgeo, v.cpair, v.tclus,
-                            ctx->stream);
-        ctx->check_launch("cluster build");
-        int total = 0;
-        ctx->download(&total, d_total, sizeof(int));
-        v.nclus = total;
-    }
-    ctx->upload(v.d_desc, v.desc.data(), sizeof(ClusterDesc) * B);
-    return v;
-}
-
-// ------------------------------------------------------------------ work plan
-// Pieces: every cluster's candidate list (at the pose in the device state) is
-// shared by pieces of about `piece_work` query x candidate products, each
-// taking every np-th chunk of 64 candidates, and the pieces are processed
-// heaviest first.
-struct Plan {
-    int4 *qmap = nullptr;   // per query: (t, cluster size, pieces, first slot)
-    int4 *pieces = nullptr;
-    int *porder = nullptr;
-    PieceRec *recs = nullptr;
-    int2 *cpieces = nullptr;
+// ------------------------------------------------------------------ views
+// The views of B pairs (grids of the reference clouds, clusters of the query
+// clouds) and the plan of their pair pass.
+struct Views {
+    ViewArgs a{};
+    std::vector<ClusterDesc> desc;  // sorted query points of each pair
+    char *d_head = nullptr;         // the call's input buffer: the head (states first), then the pairs
+    ClusterDesc *d_desc = nullptr;
     int npieces = 0;
     long long nslots = 0;
 };
 
-// With exact_slots false, nslots is only an upper bound (64 queries per
-// piece), which sizes the forward moments without a host read.
-Plan make_plan(cvo_context *ctx, const std::string &pre, const ClusterView &q, const GridView &r,
-               const PairState *d_state, int inverse, double kappa, bool exact_slots = true)
+// One pair of clouds as a view build takes it.
+struct PairSpec {
+    CloudPtrs ref, query;
+    double rc;
+    ViewShape shape;
+    int inverse;
+};
+
+// Builds the views of `pairs` and plans their pair pass at the poses in the
+// device states, which stand at the start of the call's input buffer with
+// whatever else is uploaded once (head_bytes in all).  head: their host copy,
+// uploaded together with the pairs; null on a later build of the same call,
+// which leaves them as they are.  The host waits once, for the piece and slot counts (with the
+// fixed scratch of the allocation-free entry point also for the size of the
+// cell tables).  A later build also finds the clouds' boxes in the arena.
+void build_pairs(cvo_context *ctx, Views &v, const std::vector<PairSpec> &pairs, const FeatLayout &lay, double kappa,
+                 const void *head, size_t head_bytes)
 {
-    Plan pl;
-    if (q.nclus == 0) return pl;
-    PairPassArgs a;
-    std::memset(&a, 0, sizeof(a));
-    a.clus = q.clus;
-    a.cgeo = q.cgeo;
-    a.cpair = q.cpair;
-    a.nclus = q.nclus;
-    a.cell_start = r.cell_start;
-    a.grids = r.d_desc;
-    a.state = d_state;
-    a.pose_is_inverse = inverse;
-    a.kappa = kappa;
-    const int nc = q.nclus;
-    int *npc = ctx->get_t<int>(pre + ".npc", nc);
-    int *cmax = ctx->get_t<int>(pre + ".cmax", nc);
-    long long *ccount = ctx->get_t<long long>(pre + ".ccount", nc);
-    int *pbase = ctx->get_t<int>(pre + ".pbase", nc);
-    int *bsum = ctx->get_t<int>(pre + ".pbsum", (nc + 2047) / 2048 + 1);
-    int *d_total = ctx->get_t<int>(pre + ".ptotal", 2);
-    launch_plan_count(a, ctx->tuning.piece_work, npc, cmax, ccount, ctx->stream);
-    launch_exclusive_scan(npc, pbase, bsum, nc, d_total, ctx->stream);
-    ctx->check_launch("plan count");
-    int P = 0;
-    ctx->download(&P, d_total, sizeof(int));
-    pl.npieces = P;
-    pl.pieces = ctx->get_t<int4>(pre + ".pieces", P);
-    int *pn = ctx->get_t<int>(pre + ".pn", P);
-    int *tbase = ctx->get_t<int>(pre + ".tbase", P);
-    unsigned long long *key = ctx->get_t<unsigned long long>(pre + ".pkey", P);
-    unsigned long long *ktmp = ctx->get_t<unsigned long long>(pre + ".pktmp", P);
-    int *val = ctx->get_t<int>(pre + ".pval", P);
-    int *vtmp = ctx->get_t<int>(pre + ".pvtmp", P);
-    const long long ntiles = (P + kRadixTile - 1) / kRadixTile;
-    int *hist = ctx->get_t<int>(pre + ".phist", ntiles * 256);
-    int *bsum2 = ctx->get_t<int>(pre + ".pbsum2", (std::max<long long>(ntiles * 256, P) + 2047) / 2048 + 1);
-    pl.cpieces = ctx->get_t<int2>(pre + ".cpieces", nc);
-    launch_plan_emit(a, npc, pbase, ccount, pl.pieces, pn, key, val, pl.cpieces, ctx->stream);
-    launch_exclusive_scan(pn, tbase, bsum2, P, d_total + 1, ctx->stream);
-    launch_plan_slots(pl.pieces, tbase, P, ctx->stream);
-    pl.qmap = ctx->get_t<int4>(pre + ".qmap", std::max<long long>(q.ntot, 1));
-    launch_plan_qmap(q.clus, pl.cpieces, pl.pieces, nc, pl.qmap, ctx->stream);
-    bool in_tmp = false;
-    launch_radix_sort(key, val, ktmp, vtmp, hist, bsum2, P, 16, ctx->stream, &in_tmp);
-    pl.porder = in_tmp ? vtmp : val;
-    pl.recs = ctx->get_t<PieceRec>(pre + ".recs", std::max(P, 1));
-    launch_plan_records(pl.porder, pl.pieces, q.cpair, q.clus, q.cgeo, P, pl.recs, ctx->stream);
-    ctx->check_launch("plan emit");
-    if (exact_slots) {
-        int nslots = 0;
-        ctx->download(&nslots, d_total + 1, sizeof(int));
-        pl.nslots = nslots;
-    } else {
-        pl.nslots = (long long)P * kWave;
+    ctx->timing.view_builds += 1;
+    const int B = (int)pairs.size();
+    ViewArgs &a = v.a;
+    a = ViewArgs{};
+    a.B = B;
+    // one upload: the head, the pairs, the query ranges
+    static_assert(sizeof(PairIn) % 16 == 0 && alignof(PairIn) == 16, "the pairs follow the head");
+    head_bytes = (head_bytes + 15) & ~size_t(15);
+    std::vector<char> blob(head_bytes + B * (sizeof(PairIn) + sizeof(ClusterDesc)));
+    if (head) std::memcpy(blob.data(), head, head_bytes);
+    PairIn *in = reinterpret_cast<PairIn *>(blob.data() + head_bytes);
+    v.desc.resize(B);
+    long long nmax = 1;
+    for (int b = 0; b < B; ++b) {
+        const PairSpec &p = pairs[b];
+        PairIn &o = in[b];
+        std::memset(&o, 0, sizeof(o));
+        o.xx = p.ref.xyz;
+        o.xf = p.ref.feat;
+        o.zx = p.query.xyz;
+        o.zf = p.query.feat;
+        o.nx = p.ref.n;
+        o.nz = p.query.n;
+        o.xb = a.n[0];
+        o.zb = a.n[1];
+        o.rc = p.rc;
+        o.cell_factor = p.shape.cell_factor;
+        o.cluster_factor = p.shape.cluster_factor;
+        o.cluster_max = p.shape.cluster_max;
+        o.octree = p.shape.rule == CVO_CLUSTER_OCTREE;
+        o.inverse = p.inverse;
+        v.desc[b] = ClusterDesc{(int)a.n[1], (int)p.query.n};
+        a.n[0] += p.ref.n;
+        a.n[1] += p.query.n;
+        nmax = std::max({nmax, p.ref.n, p.query.n});
     }
-    return pl;
+    require(a.n[0] < (1LL << 31) && a.n[1] < (1LL << 31), "more than 2^31 points in one call");
+    std::memcpy(blob.data() + head_bytes + B * sizeof(PairIn), v.desc.data(), B * sizeof(ClusterDesc));
+    v.d_head = ctx->get_t<char>("v.in", blob.size());
+    const size_t skip = head ? 0 : head_bytes;
+    ctx->upload(v.d_head + skip, blob.data() + skip, blob.size() - skip);
+    a.in = reinterpret_cast<PairIn *>(v.d_head + head_bytes);
+    v.d_desc = reinterpret_cast<ClusterDesc *>(v.d_head + head_bytes + B * sizeof(PairIn));
+
+    const size_t n0 = std::max(a.n[0], 1LL), n1 = std::max(a.n[1], 1LL);
+    a.boxblocks = (int)std::min<long long>(kBoxBlocks, (nmax + 1023) / 1024);
+    a.box = ctx->get_t<float>("v.box", 2 * (size_t)B * kBoxBlocks * 8);
+    a.grid = ctx->get_t<GridDesc>("v.grid", B);
+    a.cp = ctx->get_t<ClusterParam>("v.cp", B);
+    a.info = ctx->get_t<BuildInfo>("v.info", 1);
+    for (int k = 0; k < 2; ++k) {
+        a.key[k] = ctx->get_t<unsigned long long>(k ? "v.key1" : "v.key0", n0 + n1);
+        a.val[k] = ctx->get_t<int>(k ? "v.val1" : "v.val0", n0 + n1);
+        a.pts[k] = ctx->get_t<float4>(k ? "v.zpts" : "v.xpts", k ? n1 : n0);
+        a.feat[k] = ctx->get_t<float>(k ? "v.zfeat" : "v.xfeat", (k ? n1 : n0) * std::max(lay.d4, 1));
+    }
+    a.table = ctx->get_t<int>("v.table", view_table_ints(a.n[0], a.n[1]));
+    a.bsum = ctx->get_t<int>("v.bsum", view_bsum_ints(a.n[0], a.n[1]));
+    a.perm = ctx->get_t<int>("v.perm", n1);
+    a.clus = ctx->get_t<ClusterRec>("v.clus", n1);
+    a.qmap = ctx->get_t<int4>("v.qmap", n1);
+    a.state = reinterpret_cast<PairState *>(v.d_head);
+    a.work = ctx->tuning.piece_work;
+    if (head) launch_boxes(a, ctx->stream);
+
+    // the head of BuildInfo, which is all the host reads of it
+    struct {
+        unsigned long long alloc;
+        long long cells;
+        int bad, overflow;
+    } info;
+    static_assert(offsetof(BuildInfo, cells) == 8 && offsetof(BuildInfo, bad) == 16 &&
+                      offsetof(BuildInfo, overflow) == 20 && sizeof(info) == 24,
+                  "head of BuildInfo");
+    // the cell tables' size is not known here: they go into what the arena
+    // holds (at least one full table), and are built again if that was too little
+    size_t cells = std::max(ctx->room<int>("v.cells"), (size_t)kCellCap + 2);
+    for (;;) {
+        if (ctx->fixed.on) {
+            a.cell_cap = (1LL << 31) - 1;
+            launch_params(a, ctx->stream);
+            ctx->download(&info, a.info, sizeof(info));
+            require(info.bad == 0, "a cloud has non-finite coordinates");
+            require(info.cells < (1LL << 31), "cell tables too large");
+            cells = (size_t)info.cells;
+        }
+        a.cell_start = ctx->get_t<int>("v.cells", cells);
+        a.cell_cap = (long long)cells;
+        a.recs = ctx->fixed.on ? nullptr : static_cast<PieceRec *>(ctx->get("v.recs", 1));
+        a.rec_cap = ctx->fixed.on ? 0 : (long long)ctx->room<PieceRec>("v.recs");
+        if (!ctx->fixed.on) launch_params(a, ctx->stream);
+        launch_views(a, lay, kappa, ctx->stream);
+        if (a.rec_cap) launch_records(a, ctx->stream);
+        ctx->check_launch("view build");
+        ctx->download(&info, a.info, sizeof(info));
+        require(info.bad == 0, "a cloud has non-finite coordinates");
+        require(info.cells < (1LL << 31), "cell tables too large");
+        if (!info.overflow) break;
+        cells = (size_t)info.cells;
+    }
+    v.npieces = (int)(info.alloc & 0xffffffffu);
+    v.nslots = (long long)(info.alloc >> 32);
+    require(v.nslots < (1LL << 31), "too many output slots");
+    if (v.npieces > a.rec_cap) {
+        a.recs = ctx->get_t<PieceRec>("v.recs", v.npieces);
+        a.rec_cap = v.npieces;
+        launch_records(a, ctx->stream);
+        ctx->check_launch("piece records");
+    }
 }
 
 // ------------------------------------------------------------------ pair pass + reduce
@@ -889,23 +686,17 @@ Moments moments(cvo_context *ctx, const std::string &pre, long long n, int d4, b
     return m;
 }
 
-PairPassArgs pass_args(const ClusterView &q, const GridView &r, const PairState *st, int inverse, float sig2,
-                       double kappa, const Moments &m, const Plan &pl)
+PairPassArgs pass_args(const Views &v, const PairState *st, float sig2, double kappa, const Moments &m)
 {
     PairPassArgs a;
     std::memset(&a, 0, sizeof(a));
-    a.qpts = q.pts;
-    a.qfeat = q.feat;
-    a.clus = q.clus;
-    a.cgeo = q.cgeo;
-    a.cpair = q.cpair;
-    a.nclus = q.nclus;
-    a.rpts = r.pts;
-    a.rfeat = r.feat;
-    a.cell_start = r.cell_start;
-    a.grids = r.d_desc;
+    a.qpts = v.a.pts[1];
+    a.qfeat = v.a.feat[1];
+    a.rpts = v.a.pts[0];
+    a.rfeat = v.a.feat[0];
+    a.cell_start = v.a.cell_start;
+    a.grids = v.a.grid;
     a.state = st;
-    a.pose_is_inverse = inverse;
     a.sig2 = sig2;
     a.kappa = kappa;
     a.oW = m.W;
@@ -914,16 +705,9 @@ PairPassArgs pass_args(const ClusterView &q, const GridView &r, const PairState 
     a.oCnt = m.cnt;
     a.oG = m.G;
     a.oL = m.L;
-    a.recs = pl.recs;
-    a.npieces = pl.npieces;
+    a.recs = v.a.recs;
+    a.npieces = v.npieces;
     return a;
-}
-
-SlotMap slot_map(const Plan &pl)
-{
-    SlotMap m;
-    m.qmap = pl.qmap;
-    return m;
 }
 
 void run_pair_pass(cvo_context *ctx, const PairPassArgs &a, const FeatLayout &lay, int mode)
@@ -975,9 +759,7 @@ PairState init_state(const double *T, double ell)
 // Everything a forward evaluation or an ascent needs for B pairs.
 struct Problem {
     FeatLayout lay;
-    GridView grid;       // X clouds, reference role
-    ClusterView clus;    // Z clouds, query role
-    Plan plan;
+    Views views;
     Moments mom;
     std::vector<ViewShape> shape;  // per pair, of the current views
     PairState *d_state = nullptr;
@@ -987,25 +769,20 @@ struct Problem {
     double kappa = 3.0;
     float sig2 = 1.f;
     int ellobj = 0;         // reduce the lengthscale objective's sums too
-    BoxCache box_x, box_z;  // bounding boxes from the first view build
 };
 
 // Grid of X, clusters of Z, and the work plan at the pose held in the device
-// state (which must be current).
+// state: `head` (states and constants) on a call's first build, later the
+// device's own.
 void build_views(cvo_context *ctx, Problem &p, const std::vector<CloudPtrs> &X, const std::vector<CloudPtrs> &Z,
-                 const std::vector<double> &ell, const std::vector<ViewShape> &shape)
+                 const std::vector<double> &ell, const std::vector<ViewShape> &shape, const void *head = nullptr)
 {
     p.shape = shape;
-    ctx->timing.view_builds += 1;
-    std::vector<double> rc(ell.size());
-    for (size_t k = 0; k < ell.size(); ++k) rc[k] = p.kappa * ell[k];
-    p.grid = build_grid(ctx, "fx", X, rc, p.lay, shape, &p.box_x);
-    p.clus = build_clusters(ctx, "fz", Z, rc, p.lay, shape, &p.box_z);
-    // the fixed scratch of the allocation-free entry point is sized by the
-    // exact slot count (one host read) rather than its loose upper bound
-    p.plan = make_plan(ctx, "fp", p.clus, p.grid, p.d_state, 0, p.kappa, ctx->fixed.on);
-    p.mom = moments(ctx, "fm", p.plan.nslots, p.lay.d4, false);
-    p.nblk = reduce_blocks(p.clus.desc);
+    std::vector<PairSpec> pairs(X.size());
+    for (size_t k = 0; k < X.size(); ++k) pairs[k] = PairSpec{X[k], Z[k], p.kappa * ell[k], shape[k], 0};
+    build_pairs(ctx, p.views, pairs, p.lay, p.kappa, head, X.size() * (sizeof(PairState) + sizeof(AlignConst)));
+    p.mom = moments(ctx, "fm", p.views.nslots, p.lay.d4, false);
+    p.nblk = reduce_blocks(p.views.desc);
     p.partials = ctx->get_t<double>("partials", shape.size() * (size_t)p.nblk * kRedVals);
 }
 
@@ -1015,22 +792,24 @@ void setup_problem(cvo_context *ctx, Problem &p, const std::vector<CloudPtrs> &X
     const int B = (int)X.size();
     std::vector<double> ell(B);
     for (int b = 0; b < B; ++b) ell[b] = st[b].ell;
-    p.d_state = ctx->get_t<PairState>("state", B);
-    ctx->upload(p.d_state, st.data(), sizeof(PairState) * B);
-    build_views(ctx, p, X, Z, ell, std::vector<ViewShape>(B, fixed_shape(ctx)));
-    p.d_ac = ctx->get_t<AlignConst>("aconst", B);
-    ctx->upload(p.d_ac, ac.data(), sizeof(AlignConst) * B);
+    static_assert(sizeof(PairState) % 16 == 0 && sizeof(AlignConst) % 16 == 0, "states, then constants");
+    std::vector<char> head(B * (sizeof(PairState) + sizeof(AlignConst)));
+    std::memcpy(head.data(), st.data(), B * sizeof(PairState));
+    std::memcpy(head.data() + B * sizeof(PairState), ac.data(), B * sizeof(AlignConst));
+    build_views(ctx, p, X, Z, ell, std::vector<ViewShape>(B, fixed_shape(ctx)), head.data());
+    p.d_state = reinterpret_cast<PairState *>(p.views.d_head);
+    p.d_ac = reinterpret_cast<AlignConst *>(p.views.d_head + B * sizeof(PairState));
 }
 
 // Kernel arguments of one ascent iteration (pair pass, then reduction).
 void iteration_args(const Problem &p, int mode, double *trace, long long trace_rows, PairPassArgs &a,
                     ReduceArgs &r)
 {
-    a = pass_args(p.clus, p.grid, p.d_state, 0, p.sig2, p.kappa, p.mom, p.plan);
+    a = pass_args(p.views, p.d_state, p.sig2, p.kappa, p.mom);
     std::memset(&r, 0, sizeof(r));
-    r.qpts = p.clus.pts;
-    r.cdesc = p.clus.d_desc;
-    r.map = slot_map(p.plan);
+    r.qpts = p.views.a.pts[1];
+    r.cdesc = p.views.d_desc;
+    r.map = SlotMap{p.views.a.qmap};
     r.W = p.mom.W;
     r.D = p.mom.D;
     r.S = p.mom.S;
@@ -1044,7 +823,7 @@ void iteration_args(const Problem &p, int mode, double *trace, long long trace_r
     r.mode = mode;
     r.ellobj = p.ellobj;
     long long mx = 0;
-    for (const auto &d : p.clus.desc) mx = std::max(mx, (long long)d.n);
+    for (const auto &d : p.views.desc) mx = std::max(mx, (long long)d.n);
     r.one_query = (long long)p.nblk * kRedThreads >= mx;
 }
 
@@ -1059,7 +838,7 @@ void enqueue_iteration(cvo_context *ctx, Problem &p, int mode, double *trace, lo
             throw CvoError(CVO_ERR_UNSUPPORTED, "no compiled pair kernel for the feature layout");
         ctx->timing.evaluations += 1;
     }
-    launch_reduce(r, p.grid.B, ctx->stream);
+    launch_reduce(r, p.views.a.B, ctx->stream);
     ctx->check_launch("reduce");
 }
 
@@ -1736,66 +1515,49 @@ cvo_status cvo_inner_product_backward(cvo_handle h, const cvo_cloud *X, const cv
         }
         const FeatLayout lay = make_layout(spec, kp->sigma);
         const double rc = kp->kappa * kp->ell;
-        PairState s0 = init_state(T, kp->ell);
-        PairState *d_state = h->get_t<PairState>("bstate", 1);
-        h->upload(d_state, &s0, sizeof(PairState));
-        // target side: queries Z (pose T) against the X grid
-        if (dZ || dV || dEll) {
-            GridView gx = build_grid(h, "fx", {to_ptrs(X)}, {rc}, lay, {fixed_shape(h)});
-            ClusterView cz = build_clusters(h, "fz", {to_ptrs(Z)}, {rc}, lay, {fixed_shape(h)});
-            Plan pl = make_plan(h, "bp", cz, gx, d_state, 0, kp->kappa);
-            Moments m = moments(h, "bm", pl.nslots, lay.d4, true);
-            PairPassArgs a = pass_args(cz, gx, d_state, 0, lay.sig2, kp->kappa, m, pl);
-            run_pair_pass(h, a, lay, 1);
-            BackwardArgs ba;
-            std::memset(&ba, 0, sizeof(ba));
-            ba.map = slot_map(pl);
-            ba.qperm = cz.perm;
-            ba.D = m.D;
-            ba.G = m.G;
-            ba.state = d_state;
-            ba.pose_is_inverse = 0;
-            ba.lay = lay;
-            ba.gF = gF;
-            ba.dxyz = dZ;
-            ba.dfeat = dV;
-            ba.src_feat = Z->feat;
-            ba.n = M;
-            launch_backward_finish(ba, h->stream);
-            if (dEll) {
-                double *d_sum = h->get_t<double>("bsum", 1);
-                launch_sum_doubles(m.L, pl.nslots, d_sum, h->stream);
-                double sl = 0.0;
-                h->download(&sl, d_sum, sizeof(double));
-                const double ascale = kLog2e / (2.0 * kp->ell * kp->ell);
-                *dEll = gF * sl / (ascale * kp->ell * kp->ell * kp->ell);
+        // target side: queries Z (pose T) against the X grid; source side:
+        // queries X (pose T^-1) against the Z grid; both in the same launches
+        const bool target = dZ || dV || dEll, source = dX || dU;
+        std::vector<PairSpec> sides;
+        if (target) sides.push_back(PairSpec{to_ptrs(X), to_ptrs(Z), rc, fixed_shape(h), 0});
+        if (source) sides.push_back(PairSpec{to_ptrs(Z), to_ptrs(X), rc, fixed_shape(h), 1});
+        if (!sides.empty()) {
+            const std::vector<PairState> st(sides.size(), init_state(T, kp->ell));
+            Views v;
+            build_pairs(h, v, sides, lay, kp->kappa, st.data(), sizeof(PairState) * st.size());
+            const PairState *d_state = v.a.state;
+            Moments m = moments(h, "bm", v.nslots, lay.d4, true);
+            run_pair_pass(h, pass_args(v, d_state, lay.sig2, kp->kappa, m), lay, 1);
+            for (size_t k = 0; k < sides.size(); ++k) {
+                const bool src = sides[k].inverse;
+                BackwardArgs ba;
+                std::memset(&ba, 0, sizeof(ba));
+                ba.map = SlotMap{v.a.qmap + v.desc[k].pt_base};
+                ba.qperm = v.a.perm + v.desc[k].pt_base;
+                ba.D = m.D;
+                ba.G = m.G;
+                ba.L = m.L;
+                ba.state = d_state;
+                ba.pose_is_inverse = src;
+                ba.lay = lay;
+                ba.gF = gF;
+                ba.dxyz = src ? dX : dZ;
+                ba.dfeat = src ? dU : dV;
+                ba.src_feat = src ? X->feat : Z->feat;
+                ba.n = src ? N : M;
+                const int nb = backward_blocks(ba.n);
+                double *part = !src && dEll ? h->get_t<double>("bsum", nb + 1) : nullptr;
+                ba.lsum = part;
+                launch_backward_finish(ba, h->stream);
+                h->check_launch("backward");
+                if (part) {
+                    launch_sum_doubles(part, nb, part + nb, h->stream);
+                    double sl = 0.0;
+                    h->download(&sl, part + nb, sizeof(double));
+                    const double ascale = kLog2e / (2.0 * kp->ell * kp->ell);
+                    *dEll = gF * sl / (ascale * kp->ell * kp->ell * kp->ell);
+                }
             }
-            h->check_launch("backward (target side)");
-        }
-        // source side: queries X (pose T^-1) against the Z grid
-        if (dX || dU) {
-            GridView gz = build_grid(h, "rz", {to_ptrs(Z)}, {rc}, lay, {fixed_shape(h)});
-            ClusterView cx = build_clusters(h, "rx", {to_ptrs(X)}, {rc}, lay, {fixed_shape(h)});
-            Plan pl = make_plan(h, "bq", cx, gz, d_state, 1, kp->kappa);
-            Moments m = moments(h, "bm2", pl.nslots, lay.d4, true);
-            PairPassArgs a = pass_args(cx, gz, d_state, 1, lay.sig2, kp->kappa, m, pl);
-            run_pair_pass(h, a, lay, 1);
-            BackwardArgs ba;
-            std::memset(&ba, 0, sizeof(ba));
-            ba.map = slot_map(pl);
-            ba.qperm = cx.perm;
-            ba.D = m.D;
-            ba.G = m.G;
-            ba.state = d_state;
-            ba.pose_is_inverse = 1;
-            ba.lay = lay;
-            ba.gF = gF;
-            ba.dxyz = dX;
-            ba.dfeat = dU;
-            ba.src_feat = X->feat;
-            ba.n = N;
-            launch_backward_finish(ba, h->stream);
-            h->check_launch("backward (source side)");
         }
         HIP_OK(hipStreamSynchronize(h->stream));
         if (h->profiling) h->harvest_events();
@@ -1894,7 +1656,7 @@ cvo_status cvo_autotune(cvo_handle h, const cvo_cloud *X, const cvo_cloud *Z, co
                             PairState s0 = init_state(T, kp->ell);
                             AlignConst ac = const_for(nullptr, X->n, Z->n);
                             setup_problem(h, p, {to_ptrs(X)}, {to_ptrs(Z)}, {s0}, {ac});
-                            PairPassArgs a = pass_args(p.clus, p.grid, p.d_state, 0, p.sig2, p.kappa, p.mom, p.plan);
+                            PairPassArgs a = pass_args(p.views, p.d_state, p.sig2, p.kappa, p.mom);
                             if (npairs < 0.0) {
                                 // the evaluation's pair count sets its density class
                                 enqueue_iteration(h, p, 0, nullptr, 0, false);

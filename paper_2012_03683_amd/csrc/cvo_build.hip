@@ -2,57 +2,197 @@
 //
 // The paper's double sum (eq. (7)) is sparse (Sec. III-B): a point only
 // interacts with points within the cutoff.  These kernels bin clouds so the
-// pair pass scans neighbourhoods instead of all N*M pairs:
-//   bbox_kernel       per-cloud bounding box and a non-finite-coordinate count
-//   grid_keys         row-major cell index of every point (reference view)
-//   morton_keys       Morton code of every point (query view)
-//   radix_hist / radix_scatter   stable LSD radix sort of (key, index)
-//   scan_*            exclusive prefix sums
-//   gather_points     sorted float4 copies and padded, pre-scaled feature rows
-//   cell_table        dense first-index-per-cell table (lower bounds)
-//   cluster_heads / cluster_emit  octree clusters of at most cluster_max points
-//   chunk_heads       or clusters as halved chunks of Morton-ordered points
-// Every kernel is deterministic: counts use integer atomics only, and all
-// orderings come from the stable sort.
+// pair pass scans neighbourhoods instead of all N*M pairs, and plan its work.
+// Both sides of all pairs go through the same launches:
+//   box_kernel        partial bounding boxes and the non-finite check
+//   params_kernel     grids, cluster parameters and key widths from the boxes
+//   key_kernel        cell index (reference side) / Morton code (query side)
+//                     of every point, and the first pass's digit counts
+//   sort_pass         one 8-bit pass of a stable LSD radix sort per launch
+//   (radix_hist, scan_*, radix_scatter: the passes of large sorts)
+//   view_kernel       sorted float4 copies, padded and pre-scaled feature
+//                     rows, and the dense first-index-per-cell table
+//   cluster_kernel    query clusters, their candidate counts at the current
+//                     pose, their pieces and output slots, the query map
+//   record_kernel     the pieces in dispatch order, heaviest bucket first
+// What bounds them is latency, not bytes (30,000 + 30,000 points with 24
+// feature columns move under 20 MB in all), so the chain is made short: both
+// sides share each launch, nothing is launched only to scan or to clear, and
+// the host reads nothing before the piece and slot counts.  One evaluation of
+// 14,873 x 15,000 points: 81 launches and 4 host waits (467-487 us) became 18
+// launches and 2 waits (167 us).
+// Every result is deterministic: orderings come from the stable sort; the
+// atomics only place slots and records, whose position changes no sum.
+#include "cvo_device.hpp"
 #include "cvo_launch.hpp"
+
+#include <algorithm>
 
 namespace cvo {
 
-// ---------------------------------------------------------------- bbox
-__global__ __launch_bounds__(1024) void bbox_kernel(const CloudPtrs *clouds, float *out)
+// ---------------------------------------------------------------- boxes
+// Partial box of one cloud (blockIdx.y = 2 pair + side), 8 floats per block:
+// minimum, maximum, non-finite count.  A block takes the points of its grid
+// stride; the partial boxes are joined in params_kernel.
+__global__ __launch_bounds__(256) void box_kernel(const ViewArgs a)
 {
-    const int c = blockIdx.x;
-    const float *xyz = clouds[c].xyz;
-    const long long n = clouds[c].n;
+    const PairIn &p = a.in[blockIdx.y >> 1];
+    const bool q = blockIdx.y & 1;
+    const float *xyz = q ? p.zx : p.xx;
+    const long long n = q ? p.nz : p.nx;
     float mn[3] = {INFINITY, INFINITY, INFINITY}, mx[3] = {-INFINITY, -INFINITY, -INFINITY};
     int bad = 0;
-    for (long long i = threadIdx.x; i < n; i += blockDim.x) {
+    for (long long i = (long long)blockIdx.x * 256 + threadIdx.x; i < n; i += (long long)gridDim.x * 256) {
+#pragma unroll
         for (int k = 0; k < 3; ++k) {
-            float v = xyz[3 * i + k];
+            const float v = xyz[3 * i + k];
             if (!isfinite(v)) { bad = 1; continue; }
             mn[k] = fminf(mn[k], v);
             mx[k] = fmaxf(mx[k], v);
         }
     }
-    __shared__ float smn[3][1024], smx[3][1024];
-    __shared__ int sbad[1024];
-    for (int k = 0; k < 3; ++k) { smn[k][threadIdx.x] = mn[k]; smx[k][threadIdx.x] = mx[k]; }
-    sbad[threadIdx.x] = bad;
+    __shared__ float s_box[4][7];
+    for (int off = 32; off > 0; off >>= 1) {
+#pragma unroll
+        for (int k = 0; k < 3; ++k) {
+            mn[k] = fminf(mn[k], __shfl_xor(mn[k], off));
+            mx[k] = fmaxf(mx[k], __shfl_xor(mx[k], off));
+        }
+        bad |= __shfl_xor(bad, off);
+    }
+    if ((threadIdx.x & 63) == 0) {
+        float *o = s_box[threadIdx.x >> 6];
+        for (int k = 0; k < 3; ++k) { o[k] = mn[k]; o[3 + k] = mx[k]; }
+        o[6] = (float)bad;
+    }
     __syncthreads();
-    for (int s = blockDim.x / 2; s > 0; s >>= 1) {
-        if (threadIdx.x < s) {
-            for (int k = 0; k < 3; ++k) {
-                smn[k][threadIdx.x] = fminf(smn[k][threadIdx.x], smn[k][threadIdx.x + s]);
-                smx[k][threadIdx.x] = fmaxf(smx[k][threadIdx.x], smx[k][threadIdx.x + s]);
+    if (threadIdx.x < 7) {
+        float v = s_box[0][threadIdx.x];
+        for (int w = 1; w < 4; ++w) {
+            const float o = s_box[w][threadIdx.x];
+            v = threadIdx.x < 3 ? fminf(v, o) : fmaxf(v, o);
+        }
+        a.box[((long long)blockIdx.y * kBoxBlocks + blockIdx.x) * 8 + threadIdx.x] = v;
+    }
+}
+
+__device__ inline int bits_for(unsigned long long v)  // bits that hold v
+{
+    return v ? 64 - __clzll(v) : 0;
+}
+
+// One workgroup: a wave joins a cloud's partial boxes and its first lane
+// derives the cloud's grid (reference side) or cluster parameters (query
+// side); then the cell tables' bases and the key widths of all pairs.
+constexpr int kParamPairs = 512;  // pairs per round
+__global__ __launch_bounds__(1024) void params_kernel(const ViewArgs a)
+{
+    __shared__ long long s_nc[kParamPairs];
+    __shared__ int s_bad, s_mbits, s_max;
+    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+    const int cbits = bits_for((unsigned long long)(a.B - 1));
+    const int maxbits = min(kMortonBits, (62 - cbits) / 3);
+    if (threadIdx.x == 0) { s_bad = 0; s_mbits = 1; s_max = 1; }
+    for (int i = threadIdx.x; i < kCostBuckets; i += 1024) a.info->hist[i] = 0;
+    long long base = 0;  // (thread 0)
+    for (int p0 = 0; p0 < a.B; p0 += kParamPairs) {
+        const int np = min(kParamPairs, a.B - p0);
+        __syncthreads();
+        for (int c = wv; c < 2 * np; c += 16) {
+            const int b = p0 + (c >> 1), side = c & 1;
+            float v[7];
+#pragma unroll
+            for (int k = 0; k < 7; ++k)
+                v[k] = lane < a.boxblocks ? a.box[((2LL * b + side) * kBoxBlocks + lane) * 8 + k]
+                                          : (k < 3 ? INFINITY : k < 6 ? -INFINITY : 0.0f);
+            for (int off = 32; off > 0; off >>= 1)
+#pragma unroll
+                for (int k = 0; k < 7; ++k) {
+                    const float o = __shfl_xor(v[k], off);
+                    v[k] = k < 3 ? fminf(v[k], o) : fmaxf(v[k], o);
+                }
+            if (lane != 0) continue;
+            const PairIn &in = a.in[b];
+            const long long n = side ? in.nz : in.nx;
+            // (a cloud without any finite point on an axis gets an empty box;
+            // the call ends with an error before its views are used)
+            const bool none = n == 0 || !(v[0] <= v[3]) || !(v[1] <= v[4]) || !(v[2] <= v[5]);
+            double lo[3], hi[3];
+#pragma unroll
+            for (int k = 0; k < 3; ++k) { lo[k] = none ? 0.0 : (double)v[k]; hi[k] = none ? 0.0 : (double)v[3 + k]; }
+            if (v[6] != 0.0f) s_bad = 1;
+            const double ext = fmax(fmax(hi[0] - lo[0], hi[1] - lo[1]), fmax(hi[2] - lo[2], 1e-6));
+            if (side == 0) {
+                GridDesc g;
+                double h = isfinite(in.rc) ? in.cell_factor * in.rc : ext * 1.01;
+                h = fmax(h, ext * 1e-6);
+                double nn[3], inv;
+                for (;;) {
+                    inv = 1.0 / h;
+                    // same expression as the binning: floor((p - o) * inv_h)
+#pragma unroll
+                    for (int k = 0; k < 3; ++k) nn[k] = floor((hi[k] - lo[k]) * inv) + 1.0;
+                    if (nn[0] * nn[1] * nn[2] <= (double)kCellCap) break;
+                    h *= 1.25;
+                }
+                if (none) { h = inv = 1.0; nn[0] = nn[1] = nn[2] = 1.0; }
+                g.ox = lo[0]; g.oy = lo[1]; g.oz = lo[2];
+                g.h = h;
+                g.inv_h = inv;
+                g.nx = (int)nn[0]; g.ny = (int)nn[1]; g.nz = (int)nn[2];
+                g.cell_base = 0;
+                g.pt_base = in.xb;
+                g.n = n;
+                a.grid[b] = g;
+                const long long nc = (long long)g.nx * g.ny * g.nz;
+                s_nc[b - p0] = nc;
+                atomicMax(&s_max, (int)nc);
+            } else {
+                // octree blocks need 16 quanta per cap; chunks only use the
+                // Morton order, which a finer quantum makes more local
+                const double cap = isfinite(in.rc) ? in.cluster_factor * in.rc : ext * 2.0;
+                int L = in.octree ? 4 : 6;
+                double q = cap / (double)(1 << L);
+                // quanta needed to cover the box must fit in maxbits per axis
+                if (!(ext / q + 1.0 <= (double)(1 << maxbits))) {
+                    q = ext / ((double)(1 << maxbits) - 2.0);
+                    const double r = cap / q;
+                    L = r < 2.0 ? 0 : (r >= 1048576.0 ? 20 : 31 - __clz((int)r));
+                }
+                L = min(L, maxbits);
+                ClusterParam cp;
+                cp.ox = lo[0]; cp.oy = lo[1]; cp.oz = lo[2];
+                cp.iq = 1.0 / q;
+                cp.cap = cap;
+                cp.level = L;
+                cp.pad = 0;
+                a.cp[b] = cp;
+                // quanta along the widest axis (+1 for rounding at the far face)
+                atomicMax(&s_mbits, max(L, bits_for((unsigned long long)floor(ext / q) + 1)));
             }
-            sbad[threadIdx.x] += sbad[threadIdx.x + s];
         }
         __syncthreads();
+        if (threadIdx.x == 0)
+            for (int i = 0; i < np; ++i) {
+                const long long nc = s_nc[i];
+                s_nc[i] = base;
+                base += nc + 1;
+            }
+        __syncthreads();
+        for (int i = threadIdx.x; i < np; i += 1024) a.grid[p0 + i].cell_base = (int)min(s_nc[i], 0x7fffffffLL);
     }
+    __syncthreads();
     if (threadIdx.x == 0) {
-        for (int k = 0; k < 3; ++k) { out[8 * c + k] = smn[k][0]; out[8 * c + 3 + k] = smx[k][0]; }
-        out[8 * c + 6] = (float)sbad[0];
-        out[8 * c + 7] = 0.0f;
+        BuildInfo &f = *a.info;
+        f.alloc = 0;
+        f.cells = base;
+        f.bad = s_bad;
+        f.overflow = base > a.cell_cap;
+        f.nclus = 0;
+        f.kbits = bits_for((unsigned long long)s_max);  // the cell count itself must fit
+        f.mbits = min(s_mbits, maxbits);
+        f.sbits[0] = f.kbits + cbits;
+        f.sbits[1] = 3 * f.mbits + cbits;
     }
 }
 
@@ -68,25 +208,6 @@ __device__ inline int cell_of(float p, double o, double s, int n)
     return (int)f;
 }
 
-__global__ void grid_keys(const CloudPtrs *clouds, const GridBuild *gb, unsigned long long *keys,
-                          int *vals, int kbits)
-{
-    const int c = blockIdx.y;
-    const GridBuild g = gb[c];
-    const long long n = clouds[c].n;
-    const float *xyz = clouds[c].xyz;
-    for (long long i = (long long)blockIdx.x * blockDim.x + threadIdx.x; i < n;
-         i += (long long)gridDim.x * blockDim.x) {
-        int ix = cell_of(xyz[3 * i + 0], g.ox, g.inv_h, g.nx);
-        int iy = cell_of(xyz[3 * i + 1], g.oy, g.inv_h, g.ny);
-        int iz = cell_of(xyz[3 * i + 2], g.oz, g.inv_h, g.nz);
-        unsigned long long cell = (unsigned long long)ix +
-                                  (unsigned long long)g.nx * ((unsigned long long)iy + (unsigned long long)g.ny * iz);
-        keys[g.pt_base + i] = ((unsigned long long)c << kbits) | cell;
-        vals[g.pt_base + i] = (int)(g.pt_base + i);
-    }
-}
-
 __device__ inline unsigned long long spread3(unsigned long long v)
 {
     // spread the low 21 bits of v so bit k lands at bit 3k
@@ -99,23 +220,73 @@ __device__ inline unsigned long long spread3(unsigned long long v)
     return v;
 }
 
-__global__ void morton_keys(const CloudPtrs *clouds, const ClusterBuild *cb, unsigned long long *keys,
-                            int *vals, int bits)
+// The pair of global point i of a side (xb / zb ascend; empty clouds skipped).
+__device__ inline int pair_of(const ViewArgs &a, int side, long long i)
 {
-    const int c = blockIdx.y;
-    const ClusterBuild g = cb[c];
-    const long long n = clouds[c].n;
-    const float *xyz = clouds[c].xyz;
-    const int lim = (1 << bits);
-    const double iq = 1.0 / g.q;
-    for (long long i = (long long)blockIdx.x * blockDim.x + threadIdx.x; i < n;
-         i += (long long)gridDim.x * blockDim.x) {
-        unsigned long long qx = (unsigned long long)cell_of(xyz[3 * i + 0], g.ox, iq, lim);
-        unsigned long long qy = (unsigned long long)cell_of(xyz[3 * i + 1], g.oy, iq, lim);
-        unsigned long long qz = (unsigned long long)cell_of(xyz[3 * i + 2], g.oz, iq, lim);
-        unsigned long long m = spread3(qx) | (spread3(qy) << 1) | (spread3(qz) << 2);
-        keys[g.pt_base + i] = ((unsigned long long)c << (3 * bits)) | m;
-        vals[g.pt_base + i] = (int)(g.pt_base + i);
+    int lo = 0, hi = a.B - 1;
+    while (lo < hi) {
+        const int mid = (lo + hi + 1) >> 1;
+        if ((side ? a.in[mid].zb : a.in[mid].xb) <= i) lo = mid; else hi = mid - 1;
+    }
+    return lo;
+}
+
+__host__ __device__ inline int tiles_of(long long n) { return (int)((n + kRadixTile - 1) / kRadixTile); }
+
+// Digit table of pass `pass` of a side: 256 counts per tile of the keys as
+// they stand before that pass.
+__device__ inline int *digit_table(const ViewArgs &a, int side, int pass)
+{
+    const long long t0 = tiles_of(a.n[0]), t1 = tiles_of(a.n[1]);
+    return a.table + 256 * (side ? kMaxPasses * t0 + pass * t1 : pass * t0);
+}
+
+// Keys of one tile.  TABLE: also the tile's digit counts of the first pass,
+// and the zeros that the passes count the later digits into.
+template <bool TABLE>
+__global__ __launch_bounds__(1024) void key_kernel(const ViewArgs a)
+{
+    const int side = blockIdx.y;
+    const long long n = a.n[side];
+    const long long i = (long long)blockIdx.x * kRadixTile + threadIdx.x;
+    if ((long long)blockIdx.x * kRadixTile >= n || a.info->overflow) return;
+    __shared__ int h[256];
+    if (TABLE) {
+        if (threadIdx.x < 256) h[threadIdx.x] = 0;
+        for (int p = 1 + (threadIdx.x >> 8); p < kMaxPasses; p += 4)
+            digit_table(a, side, p)[256 * blockIdx.x + (threadIdx.x & 255)] = 0;
+        __syncthreads();
+    }
+    if (i < n) {
+        const int b = pair_of(a, side, i);
+        const PairIn &in = a.in[b];
+        const float *xyz = (side ? in.zx : in.xx) + 3 * (i - (side ? in.zb : in.xb));
+        unsigned long long key;
+        if (side == 0) {
+            const GridDesc &g = a.grid[b];
+            const int ix = cell_of(xyz[0], g.ox, g.inv_h, g.nx);
+            const int iy = cell_of(xyz[1], g.oy, g.inv_h, g.ny);
+            const int iz = cell_of(xyz[2], g.oz, g.inv_h, g.nz);
+            key = (unsigned long long)ix +
+                  (unsigned long long)g.nx * ((unsigned long long)iy + (unsigned long long)g.ny * iz);
+            key |= (unsigned long long)b << a.info->kbits;
+        } else {
+            const ClusterParam &g = a.cp[b];
+            const int lim = 1 << a.info->mbits;
+            const unsigned long long qx = (unsigned long long)cell_of(xyz[0], g.ox, g.iq, lim);
+            const unsigned long long qy = (unsigned long long)cell_of(xyz[1], g.oy, g.iq, lim);
+            const unsigned long long qz = (unsigned long long)cell_of(xyz[2], g.oz, g.iq, lim);
+            key = spread3(qx) | (spread3(qy) << 1) | (spread3(qz) << 2);
+            key |= (unsigned long long)b << (3 * a.info->mbits);
+        }
+        const long long o = (side ? a.n[0] : 0) + i;
+        a.key[0][o] = key;
+        a.val[0][o] = (int)i;
+        if (TABLE) atomicAdd(&h[key & 255], 1);
+    }
+    if (TABLE) {
+        __syncthreads();
+        if (threadIdx.x < 256) digit_table(a, side, 0)[256 * blockIdx.x + threadIdx.x] = h[threadIdx.x];
     }
 }
 
@@ -205,133 +376,168 @@ void launch_exclusive_scan(const int *in, int *out, int *bsum, long long n, int 
 }
 
 // ---------------------------------------------------------------- radix sort
-constexpr int kRadixThreads = 256;
-constexpr int kRadixItems = kRadixTile / kRadixThreads;
-static_assert(kRadixTile % kRadixThreads == 0, "radix tile");
+// Passes alternate between the two buffers; after the last one the sorted
+// keys are in buffer (passes & 1).
+__device__ inline int passes_of(const ViewArgs &a, int side) { return a.n[side] > 1 ? (a.info->sbits[side] + 7) / 8 : 0; }
 
-__global__ __launch_bounds__(kRadixThreads) void radix_hist(const unsigned long long *keys, long long n,
-                                                            int shift, int *hist, int ntiles)
+// The lanes of the wave with the same value of `bits` bits as this one.
+template <int BITS> __device__ __forceinline__ unsigned long long wave_match(int v)
 {
+    unsigned long long peers = ~0ULL;
+#pragma unroll
+    for (int b = 0; b < BITS; ++b) {
+        const unsigned long long bal = __ballot((v >> b) & 1);
+        peers &= ((v >> b) & 1) ? bal : ~bal;
+    }
+    return peers;
+}
+
+// Rank of this lane's digit among the earlier lanes of its wave with the same
+// digit, and the number of lanes that hold it (invalid lanes: digit 256).
+__device__ __forceinline__ void wave_rank(int d, int lane, int &rank, int &count)
+{
+    const unsigned long long peers = wave_match<9>(d);
+    rank = __popcll(peers & ((1ULL << lane) - 1ULL));
+    count = __popcll(peers);
+}
+
+// One pass in one launch, both sides (blockIdx.y).  A tile finds where its
+// digits go from the pass's digit table: the counts of all tiles (each
+// thread adds a quarter of them for one digit), an exclusive scan over the
+// digits, and the counts of the tiles before it.  Its 1,024 keys are ranked
+// stably (earlier lanes of the wave, earlier waves) and written, and counted
+// into the next pass's table at the tile they land in (one atomic per wave for
+// the keys that share tile and digit: the high digits of neighbours agree,
+// and one atomic per key on the same counter took 12.7 us at 15 tiles).
+// Latency bound: 4.1 us per launch at 2 tiles a side, 6.1 us at 15, 7.4 us at
+// 40, for both sides, against about 19 us for one side's histogram, three scan
+// launches and scatter.  Every tile reads the whole table, so beyond
+// kTableTiles tiles (128 KB read per tile) the separate launches win.
+__global__ __launch_bounds__(1024) void sort_pass(const ViewArgs a, int pass)
+{
+    const int side = blockIdx.y;
+    const long long n = a.n[side];
+    const int ntiles = tiles_of(n);
+    const int tile = blockIdx.x;
+    if (tile >= ntiles || pass >= passes_of(a, side) || a.info->overflow) return;
+    __shared__ int s_tot[4][256], s_bef[4][256], s_base[256], s_w[4];
+    __shared__ int s_cnt[16][256];
+    const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
+    const int part = tid >> 8, d0 = tid & 255;
+    const long long o = side ? a.n[0] : 0;
+    const int e = tile * kRadixTile + tid;
+    const bool valid = e < n;
+    const unsigned long long key = valid ? a.key[pass & 1][o + e] : 0ULL;
+    const int val = valid ? a.val[pass & 1][o + e] : 0;
+    {
+        const int *tb = digit_table(a, side, pass);
+        int tot = 0, bef = 0;
+        for (int t = part; t < ntiles; t += 4) {
+            const int c = tb[256 * t + d0];
+            tot += c;
+            bef += t < tile ? c : 0;
+        }
+        s_tot[part][d0] = tot;
+        s_bef[part][d0] = bef;
+    }
+#pragma unroll
+    for (int k = 0; k < 4; ++k) s_cnt[4 * part + k][d0] = 0;
+    const int d = valid ? (int)((key >> (8 * pass)) & 255) : 256;
+    int rank, count;
+    wave_rank(d, lane, rank, count);
+    __syncthreads();
+    if (valid && rank == 0) s_cnt[wv][d] = count;
+    int tot = 0, incl = 0;
+    if (tid < 256) {
+        tot = s_tot[0][tid] + s_tot[1][tid] + s_tot[2][tid] + s_tot[3][tid];
+        incl = wave_scan_add(tot);
+        if (lane == 63) s_w[wv] = incl;
+    }
+    __syncthreads();
+    if (tid < 256) {
+        int acc = incl - tot + s_bef[0][tid] + s_bef[1][tid] + s_bef[2][tid] + s_bef[3][tid];
+        for (int w = 0; w < wv; ++w) acc += s_w[w];
+#pragma unroll
+        for (int w = 0; w < 16; ++w) {
+            const int c = s_cnt[w][tid];
+            s_cnt[w][tid] = acc;
+            acc += c;
+        }
+    }
+    __syncthreads();
+    int place = -1;  // counter of the next pass: destination tile and next digit
+    if (valid) {
+        const int pos = s_cnt[wv][d] + rank;
+        a.key[(pass + 1) & 1][o + pos] = key;
+        a.val[(pass + 1) & 1][o + pos] = val;
+        place = 256 * (pos / kRadixTile) + (int)((key >> (8 * pass + 8)) & 255);
+    }
+    if (pass + 1 < passes_of(a, side)) {
+        static_assert(kTableTiles <= 256, "a counter's number takes 16 bits");
+        const unsigned long long same = wave_match<17>(place);  // (bit 16: invalid lanes)
+        if (valid && (same & ((1ULL << lane) - 1ULL)) == 0)
+            atomicAdd(&digit_table(a, side, pass + 1)[place], __popcll(same));
+    }
+}
+
+// The passes of a large sort, both sides in the same launches: a histogram
+// per tile (digit-major, the query side's after the reference side's), the
+// scan of all of them, and the scatter.  The scan runs on from one side to
+// the next as their keys do, so its values are places in the joint buffers.
+// (A side that needs no more passes still counts, so that holds for the other.)
+__global__ __launch_bounds__(1024) void radix_hist(const ViewArgs a, int pass, int *hist)
+{
+    const int side = blockIdx.y, ntiles = tiles_of(a.n[side]);
+    if (blockIdx.x >= ntiles || a.info->overflow) return;
     __shared__ int h[256];
-    h[threadIdx.x] = 0;
+    if (threadIdx.x < 256) h[threadIdx.x] = 0;
     __syncthreads();
-    const long long base = (long long)blockIdx.x * kRadixTile;
-    for (int r = 0; r < kRadixItems; ++r) {
-        long long e = base + r * kRadixThreads + threadIdx.x;
-        if (e < n) atomicAdd(&h[(keys[e] >> shift) & 255], 1);
+    const long long e = (long long)blockIdx.x * kRadixTile + threadIdx.x;
+    const int buf = min(pass, passes_of(a, side)) & 1;
+    if (e < a.n[side]) atomicAdd(&h[(a.key[buf][(side ? a.n[0] : 0) + e] >> (8 * pass)) & 255], 1);
+    __syncthreads();
+    const long long t0 = side ? tiles_of(a.n[0]) : 0;
+    if (threadIdx.x < 256) hist[256 * t0 + (long long)threadIdx.x * ntiles + blockIdx.x] = h[threadIdx.x];
+}
+
+__global__ __launch_bounds__(1024) void radix_scatter(const ViewArgs a, int pass, const int *hist)
+{
+    const int side = blockIdx.y, ntiles = tiles_of(a.n[side]);
+    if (blockIdx.x >= ntiles || pass >= passes_of(a, side) || a.info->overflow) return;
+    __shared__ int s_cnt[16][256];
+    const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
+    const long long o = side ? a.n[0] : 0;
+    const long long e = (long long)blockIdx.x * kRadixTile + tid;
+    const bool valid = e < a.n[side];
+    const unsigned long long key = valid ? a.key[pass & 1][o + e] : 0ULL;
+    const int val = valid ? a.val[pass & 1][o + e] : 0;
+#pragma unroll
+    for (int k = 0; k < 4; ++k) s_cnt[4 * (tid >> 8) + k][tid & 255] = 0;
+    const int d = valid ? (int)((key >> (8 * pass)) & 255) : 256;
+    int rank, count;
+    wave_rank(d, lane, rank, count);
+    __syncthreads();
+    if (valid && rank == 0) s_cnt[wv][d] = count;
+    __syncthreads();
+    if (tid < 256) {
+        const long long t0 = side ? tiles_of(a.n[0]) : 0;
+        int acc = hist[256 * t0 + (long long)tid * ntiles + blockIdx.x];
+#pragma unroll
+        for (int w = 0; w < 16; ++w) {
+            const int c = s_cnt[w][tid];
+            s_cnt[w][tid] = acc;
+            acc += c;
+        }
     }
     __syncthreads();
-    hist[threadIdx.x * ntiles + blockIdx.x] = h[threadIdx.x];
-}
-
-// Stable scatter: within a round of 256 consecutive elements, an element's
-// rank among equal digits is (earlier lanes of its wave with the digit) +
-// (counts of the digit in earlier waves); rounds and tiles follow in order.
-__global__ __launch_bounds__(kRadixThreads) void radix_scatter(const unsigned long long *kin, const int *vin,
-                                                               unsigned long long *kout, int *vout, long long n,
-                                                               int shift, const int *hist, int ntiles)
-{
-    __shared__ int run[256];
-    __shared__ int wcnt[kRadixThreads / kWave][256];
-    __shared__ int woff[kRadixThreads / kWave][256];
-    const int lane = threadIdx.x & (kWave - 1);
-    const int wv = threadIdx.x / kWave;
-    run[threadIdx.x] = hist[threadIdx.x * ntiles + blockIdx.x];
-    const unsigned long long lt = (lane == 0) ? 0ULL : (~0ULL >> (64 - lane));
-    const long long base = (long long)blockIdx.x * kRadixTile;
-    for (int r = 0; r < kRadixItems; ++r) {
-        const long long e = base + r * kRadixThreads + threadIdx.x;
-        const bool valid = e < n;
-        unsigned long long key = valid ? kin[e] : 0ULL;
-        int val = valid ? vin[e] : 0;
-        int d = valid ? (int)((key >> shift) & 255) : 256;
-        unsigned long long peers = ~0ULL;
-        for (int b = 0; b < 9; ++b) {
-            unsigned long long bal = __ballot((d >> b) & 1);
-            peers &= ((d >> b) & 1) ? bal : ~bal;
-        }
-        const int rank = __popcll(peers & lt);
-        for (int k = threadIdx.x; k < (kRadixThreads / kWave) * 256; k += kRadixThreads)
-            (&wcnt[0][0])[k] = 0;
-        __syncthreads();
-        if (valid && rank == 0) wcnt[wv][d] = __popcll(peers);
-        __syncthreads();
-        {
-            const int dd = threadIdx.x;  // one thread per digit
-            int acc = run[dd];
-            for (int w = 0; w < kRadixThreads / kWave; ++w) {
-                woff[w][dd] = acc;
-                acc += wcnt[w][dd];
-            }
-            run[dd] = acc;
-        }
-        __syncthreads();
-        if (valid) {
-            const int pos = woff[wv][d] + rank;
-            kout[pos] = key;
-            vout[pos] = val;
-        }
-        __syncthreads();
+    if (valid) {
+        const int pos = s_cnt[wv][d] + rank;
+        a.key[(pass + 1) & 1][pos] = key;
+        a.val[(pass + 1) & 1][pos] = val;
     }
 }
 
-void launch_radix_sort(unsigned long long *keys, int *vals, unsigned long long *ktmp, int *vtmp, int *hist,
-                       int *bsum, long long n, int bits, hipStream_t s, bool *result_in_tmp)
-{
-    const int ntiles = (int)((n + kRadixTile - 1) / kRadixTile);
-    bool in_tmp = false;
-    if (n > 1) {
-        for (int shift = 0; shift < bits; shift += 8) {
-            const unsigned long long *ki = in_tmp ? ktmp : keys;
-            const int *vi = in_tmp ? vtmp : vals;
-            unsigned long long *ko = in_tmp ? keys : ktmp;
-            int *vo = in_tmp ? vals : vtmp;
-            hipLaunchKernelGGL(radix_hist, dim3(ntiles), dim3(kRadixThreads), 0, s, ki, n, shift, hist, ntiles);
-            launch_exclusive_scan(hist, hist, bsum, (long long)ntiles * 256, nullptr, s);
-            hipLaunchKernelGGL(radix_scatter, dim3(ntiles), dim3(kRadixThreads), 0, s, ki, vi, ko, vo, n, shift,
-                               hist, ntiles);
-            in_tmp = !in_tmp;
-        }
-    }
-    *result_in_tmp = in_tmp;
-}
-
-// ---------------------------------------------------------------- gather
-// Sorted float4 copies of the raw coordinates, the permutation, and padded
-// feature rows (destination column k = source column col[k] times scale[k]).
-__global__ void gather_points(const unsigned long long *keys, const int *vals, long long ntot, int cshift,
-                              const CloudPtrs *clouds, const long long *pt_base, FeatLayout lay,
-                              float4 *pts, float *feat, int *perm)
-{
-    for (long long p = (long long)blockIdx.x * blockDim.x + threadIdx.x; p < ntot;
-         p += (long long)gridDim.x * blockDim.x) {
-        const int c = (int)(keys[p] >> cshift);
-        const long long i = vals[p] - pt_base[c];
-        const float *xyz = clouds[c].xyz;
-        pts[p] = make_float4(xyz[3 * i], xyz[3 * i + 1], xyz[3 * i + 2], 0.0f);
-        perm[p] = (int)i;
-        if (lay.d4 > 0) {
-            const float *f = clouds[c].feat + i * lay.src_dim;
-            for (int k = 0; k < lay.d4; ++k) {
-                float v = 0.0f;
-                if (lay.col[k] >= 0) {
-                    v = f[lay.col[k]] * lay.scale[k];
-                } else if (lay.col[k] == -2) {
-                    // tensor-product column of the folded LIN blocks (eq. (6))
-                    int cc = k - lay.sed;
-                    v = 1.0f;
-                    for (int b = lay.nlin - 1; b >= 0; --b) {
-                        v *= f[lay.lin_src[b] + cc % lay.lin_dim[b]];
-                        cc /= lay.lin_dim[b];
-                    }
-                }
-                feat[p * lay.d4 + k] = v;
-            }
-        }
-    }
-}
-
-// ---------------------------------------------------------------- cell table
+// ---------------------------------------------------------------- views
 __device__ inline long long lower_bound_u64(const unsigned long long *a, long long n, unsigned long long x)
 {
     long long lo = 0, hi = n;
@@ -342,198 +548,396 @@ __device__ inline long long lower_bound_u64(const unsigned long long *a, long lo
     return lo;
 }
 
-__global__ void cell_table(const unsigned long long *keys, long long ntot, const GridBuild *gb, int kbits,
-                           int *cell_start)
+// blockIdx.y 0 and 1: sorted copies of a side -- the float4 coordinates and
+// the padded feature row, one float4 per thread, so a row is read and written
+// by consecutive threads (destination column k = source column col[k] times
+// scale[k]).  blockIdx.y 2: the cell tables, one lower bound per cell.
+__global__ __launch_bounds__(256) void view_kernel(const ViewArgs a, const FeatLayout lay)
 {
-    const int c = blockIdx.y;
-    const GridBuild g = gb[c];
-    const long long ncells = (long long)g.nx * g.ny * g.nz;
-    for (long long k = (long long)blockIdx.x * blockDim.x + threadIdx.x; k <= ncells;
-         k += (long long)gridDim.x * blockDim.x) {
-        unsigned long long target = ((unsigned long long)c << kbits) | (unsigned long long)k;
-        cell_start[g.cell_base + k] = (int)lower_bound_u64(keys, ntot, target);
-    }
-}
-
-// ---------------------------------------------------------------- clusters
-// A point's cluster is the largest aligned Morton block (level L <= lcap,
-// edge 2^L quanta) holding at most tpw points, with (lcap, tpw) given per
-// cloud.  Block counts grow with L, so every point of such a block makes the
-// same choice.  A level-0 block with more than tpw points is cut into
-// ceil(count/tpw) near-equal chunks.
-__global__ void cluster_heads(const unsigned long long *keys, long long ntot, const int2 *caps, int cshift,
-                              int *head, int2 *span)
-{
-    for (long long p = (long long)blockIdx.x * blockDim.x + threadIdx.x; p < ntot;
-         p += (long long)gridDim.x * blockDim.x) {
-        const unsigned long long key = keys[p];
-        const int2 cap = caps[key >> cshift];
-        const int lcap = cap.x, tpw = cap.y;
-        if (lcap < 0) continue;  // clustered by the chunk rule
-        long long start = -1, end = -1;
-        long long lo0 = 0, hi0 = 0;
-        for (int L = lcap; L >= 0; --L) {
-            const unsigned long long blk = key >> (3 * L);
-            const long long lo = lower_bound_u64(keys, ntot, blk << (3 * L));
-            const long long hi = lower_bound_u64(keys, ntot, (blk + 1) << (3 * L));
-            if (hi - lo <= tpw) { start = lo; end = hi; break; }
-            lo0 = lo; hi0 = hi;
+    if (a.info->overflow) return;
+    const int side = blockIdx.y;
+    if (side == 2) {
+        const unsigned long long *keys = a.key[passes_of(a, 0) & 1];
+        const int kbits = a.info->kbits;
+        const long long total = a.info->cells;
+        int b = 0;
+        for (long long k = (long long)blockIdx.x * 256 + threadIdx.x; k < total; k += (long long)gridDim.x * 256) {
+            while (b + 1 < a.B && a.grid[b + 1].cell_base <= k) ++b;
+            const unsigned long long target = ((unsigned long long)b << kbits) | (unsigned long long)(k - a.grid[b].cell_base);
+            a.cell_start[k] = (int)lower_bound_u64(keys, a.n[0], target);
         }
-        if (start < 0) {
-            const long long cnt = hi0 - lo0;
-            const long long nch = (cnt + tpw - 1) / tpw;
-            const long long sz = (cnt + nch - 1) / nch;
-            const long long ch = (p - lo0) / sz;
-            start = lo0 + ch * sz;
-            end = start + sz < hi0 ? start + sz : hi0;
-        }
-        head[p] = (p == start) ? 1 : 0;
-        span[p] = make_int2((int)start, (int)(end - start));
+        return;
     }
-}
-
-// Chunk clusters, one wavefront per chunk of cluster_max consecutive
-// Morton-ordered points (lane l holds point l).  Level k splits the chunk
-// into aligned parts of cluster_max >> k points; a part is final when its
-// bounding box edge fits the cap or it holds one point.  Parts are thus
-// runs of cluster_max / 2^k points (the last chunk of a cloud clipped),
-// which fill the pair pass's power-of-two lane groups, and each stays
-// compact in space.  head/span as cluster_heads writes them.
-__global__ __launch_bounds__(kWave) void chunk_heads(const float4 *pts, const ClusterBuild *cb, const int2 *caps,
-                                                      int B, long long nchunks, int *head, int2 *span)
-{
-    const long long w = blockIdx.x;
-    if (w >= nchunks) return;
-    // the cloud of this chunk (chunk_base ascending)
-    int c = 0;
-    while (c + 1 < B && cb[c + 1].chunk_base <= w) ++c;
-    const ClusterBuild g = cb[c];
-    const int tpw = caps[c].y;
-    const long long c0 = g.pt_base + (w - g.chunk_base) * tpw;
-    const int len = (int)min((long long)tpw, g.pt_base + g.n - c0);
-    const int l = threadIdx.x;
-    const bool in = l < len;
-    float4 q = make_float4(0.f, 0.f, 0.f, 0.f);
-    if (in) q = pts[c0 + l];
-    bool done = !in;
-    for (int sz = tpw; sz >= 1; sz >>= 1) {
-        // bounding box of each aligned part of sz lanes (lanes beyond len neutral)
-        double lo[3] = {in ? (double)q.x : INFINITY, in ? (double)q.y : INFINITY, in ? (double)q.z : INFINITY};
-        double hi[3] = {in ? (double)q.x : -INFINITY, in ? (double)q.y : -INFINITY, in ? (double)q.z : -INFINITY};
-        for (int off = 1; off < sz; off <<= 1) {
+    __shared__ int s_col[64];
+    __shared__ float s_scale[64];
+    if (threadIdx.x < 64) {
+        s_col[threadIdx.x] = lay.col[threadIdx.x];
+        s_scale[threadIdx.x] = lay.scale[threadIdx.x];
+    }
+    __syncthreads();
+    const int buf = passes_of(a, side) & 1;
+    const long long o = side ? a.n[0] : 0;
+    const int shift = side ? 3 * a.info->mbits : a.info->kbits;
+    const int f4 = lay.d4 / 4, items = f4 + 1;
+    const long long total = a.n[side] * items;
+    for (long long w = (long long)blockIdx.x * 256 + threadIdx.x; w < total; w += (long long)gridDim.x * 256) {
+        const long long p = total < (1LL << 31) ? (long long)((unsigned)w / (unsigned)items) : w / items;
+        const int f = (int)(w - p * items);
+        const int b = (int)(a.key[buf][o + p] >> shift);
+        const PairIn &in = a.in[b];
+        const long long i = a.val[buf][o + p] - (side ? in.zb : in.xb);
+        if (f == f4) {
+            const float *xyz = (side ? in.zx : in.xx) + 3 * i;
+            a.pts[side][p] = make_float4(xyz[0], xyz[1], xyz[2], 0.0f);
+            if (side) a.perm[p] = (int)i;
+            continue;
+        }
+        const float *row = (side ? in.zf : in.xf) + i * lay.src_dim;
+        float v[4];
 #pragma unroll
-            for (int a = 0; a < 3; ++a) {
-                lo[a] = fmin(lo[a], __shfl_xor(lo[a], off));
-                hi[a] = fmax(hi[a], __shfl_xor(hi[a], off));
+        for (int q = 0; q < 4; ++q) {
+            const int k = 4 * f + q, col = s_col[k];
+            v[q] = 0.0f;
+            if (col >= 0) {
+                v[q] = row[col] * s_scale[k];
+            } else if (col == -2) {
+                // tensor-product column of the folded LIN blocks (eq. (6))
+                int cc = k - lay.sed;
+                v[q] = 1.0f;
+                for (int l = lay.nlin - 1; l >= 0; --l) {
+                    v[q] *= row[lay.lin_src[l] + cc % lay.lin_dim[l]];
+                    cc /= lay.lin_dim[l];
+                }
             }
         }
-        const double edge = fmax(hi[0] - lo[0], fmax(hi[1] - lo[1], hi[2] - lo[2]));
-        const int first = l & ~(sz - 1);
-        const int plen = min(sz, len - first);
-        if (!done && (edge <= g.cap || plen <= 1)) {
-            head[c0 + l] = (l == first) ? 1 : 0;
-            span[c0 + l] = make_int2((int)(c0 + first), plen);
-            done = true;
-        }
-        if (__all(done)) break;
+        reinterpret_cast<float4 *>(a.feat[side])[p * f4 + f] = make_float4(v[0], v[1], v[2], v[3]);
     }
 }
 
-__global__ void cluster_emit(const int *head, const int *hidx, const int2 *span, const float4 *pts,
-                             const unsigned long long *keys, int cshift, long long ntot, int2 *clus,
-                             double4 *cgeo, int *cpair, int *tclus)
+// ---------------------------------------------------------------- clusters and plan
+// A piece's cost bucket, non-decreasing in the cost: steps of 96 below 49152
+// (every piece of the default plan: n <= 64 queries x at most 576), none
+// heavier apart above.
+__device__ __forceinline__ int cost_bucket(unsigned long long cost)
 {
-    for (long long p = (long long)blockIdx.x * blockDim.x + threadIdx.x; p < ntot;
-         p += (long long)gridDim.x * blockDim.x) {
-        if (!head[p]) continue;
-        const int idx = hidx[p];
-        const int2 sp = span[p];
-        double lo[3] = {INFINITY, INFINITY, INFINITY}, hi[3] = {-INFINITY, -INFINITY, -INFINITY};
-        for (int k = 0; k < sp.y; ++k) {
-            float4 q = pts[sp.x + k];
-            double v[3] = {(double)q.x, (double)q.y, (double)q.z};
-            for (int a = 0; a < 3; ++a) { lo[a] = fmin(lo[a], v[a]); hi[a] = fmax(hi[a], v[a]); }
+    return (int)min(cost / 96ULL, (unsigned long long)(kCostBuckets - 1));
+}
+
+constexpr int kHalo = 64;         // points beside a block that a cluster may reach
+constexpr int kClusThreads = 256;
+constexpr int kClusSpan = kClusThreads + 2 * kHalo;
+
+// One thread per sorted query point finds the point's cluster; the first
+// point of a cluster is its head.
+//   octree rule: the largest aligned Morton block (level <= ClusterParam.level)
+//     holding at most cluster_max points.  Block counts grow with the level, so
+//     every point of a block makes the same choice, and a block of at most 64
+//     points lies within the staged neighbours: its ends are found by walking
+//     outward while the keys agree.  A level-0 block with more points is cut
+//     into ceil(count / cluster_max) near-equal runs.
+//   chunk rule: chunks of cluster_max consecutive points of the cloud, halved
+//     until the part's bounding box edge is within ClusterParam.cap or the part
+//     is one point.
+// Then 2 to 16 lanes per head count the candidates of its neighbourhood at
+// the current pose (one grid row per lane and turn), from which its pieces
+// follow: c_max = max(512, work / n) candidates each.  A block reserves its
+// clusters' output slots, records and places in the cost buckets with one
+// atomic each (an atomic per cluster serialises on the few buckets that most
+// clusters of a sparse cloud share: 22 us for 1,900 of them).
+__global__ __launch_bounds__(kClusThreads) void cluster_kernel(const ViewArgs a, double kappa)
+{
+    if (a.info->overflow) return;
+    __shared__ float4 s_pt[kClusSpan];
+    __shared__ unsigned long long s_key[kClusSpan];
+    __shared__ double4 s_geo[kClusThreads];
+    __shared__ int s_first[kClusThreads], s_n[kClusThreads], s_b[kClusThreads], s_np[kClusThreads], s_C[kClusThreads];
+    __shared__ int s_slot[kClusThreads];
+    __shared__ int s_hist[kCostBuckets];
+    __shared__ int s_w[4], s_w2[4], s_heads;
+    __shared__ unsigned long long s_base;
+    __shared__ int s_cbase;
+    const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
+    const long long N = a.n[1];
+    const long long p0 = (long long)blockIdx.x * kClusThreads;
+    const int buf = passes_of(a, 1) & 1;
+    const unsigned long long *keys = a.key[buf] + a.n[0];
+    for (int k = tid; k < kClusSpan; k += kClusThreads) {
+        const long long p = p0 - kHalo + k;
+        const bool in = p >= 0 && p < N;
+        s_pt[k] = in ? a.pts[1][p] : make_float4(0.f, 0.f, 0.f, 0.f);
+        s_key[k] = in ? keys[p] : ~0ULL;
+    }
+    for (int k = tid; k < kCostBuckets; k += kClusThreads) s_hist[k] = 0;
+    __syncthreads();
+    const long long p = p0 + tid;
+    const int shift = 3 * a.info->mbits;
+    bool head = false;
+    int cnt = 0, b = 0;
+    if (p < N) {
+        const int me = tid + kHalo;
+        const unsigned long long key = s_key[me];
+        b = (int)(key >> shift);
+        const PairIn &in = a.in[b];
+        const ClusterParam &cp = a.cp[b];
+        const int tpw = in.cluster_max;
+        long long start = p;
+        if (!in.octree) {
+            const long long rel = p - in.zb;
+            const long long c0 = in.zb + rel / tpw * tpw;
+            const int len = (int)min((long long)tpw, in.zb + in.nz - c0);
+            const int l = (int)(p - c0);
+            for (int sz = tpw;; sz >>= 1) {
+                const int first = l & ~(sz - 1);
+                const int plen = min(sz, len - first);
+                const float4 *q = &s_pt[me - l + first];
+                float lo[3] = {INFINITY, INFINITY, INFINITY}, hi[3] = {-INFINITY, -INFINITY, -INFINITY};
+                for (int k = 0; k < plen; ++k) {
+                    const float4 v = q[k];
+                    lo[0] = fminf(lo[0], v.x); hi[0] = fmaxf(hi[0], v.x);
+                    lo[1] = fminf(lo[1], v.y); hi[1] = fmaxf(hi[1], v.y);
+                    lo[2] = fminf(lo[2], v.z); hi[2] = fmaxf(hi[2], v.z);
+                }
+                const double edge = fmax((double)hi[0] - lo[0], fmax((double)hi[1] - lo[1], (double)hi[2] - lo[2]));
+                if (edge <= cp.cap || plen <= 1) {
+                    start = c0 + first;
+                    cnt = plen;
+                    break;
+                }
+            }
+        } else {
+            int lo = me, hi = me + 1;  // staged indices of the block at level L
+            for (int L = 0; L <= cp.level; ++L) {
+                const unsigned long long blk = key >> (3 * L);
+                while (hi - lo <= tpw && lo > 0 && s_key[lo - 1] >> (3 * L) == blk) --lo;
+                while (hi - lo <= tpw && hi < kClusSpan && s_key[hi] >> (3 * L) == blk) ++hi;
+                if (hi - lo > tpw) {
+                    if (L == 0) {
+                        const long long lo0 = lower_bound_u64(keys, N, key), hi0 = lower_bound_u64(keys, N, key + 1);
+                        const long long all = hi0 - lo0, nch = (all + tpw - 1) / tpw, sz = (all + nch - 1) / nch;
+                        start = lo0 + (p - lo0) / sz * sz;
+                        cnt = (int)(min(start + sz, hi0) - start);
+                    }
+                    break;
+                }
+                start = p0 - kHalo + lo;
+                cnt = hi - lo;
+            }
         }
-        double cc[3], r2 = 0.0, mag = 0.0;
-        for (int a = 0; a < 3; ++a) { cc[a] = 0.5 * (lo[a] + hi[a]); mag = fmax(mag, fabs(cc[a])); }
-        for (int k = 0; k < sp.y; ++k) {
-            float4 q = pts[sp.x + k];
-            double dx = (double)q.x - cc[0], dy = (double)q.y - cc[1], dz = (double)q.z - cc[2];
-            r2 = fmax(r2, dx * dx + dy * dy + dz * dz);
+        head = p == start;
+    }
+    // the block's heads, compacted in order, with their geometry
+    {
+        const unsigned long long m = __ballot(head);
+        if (lane == 0) s_w[wv] = __popcll(m);
+        __syncthreads();
+        int k = __popcll(m & ((1ULL << lane) - 1ULL));
+        for (int w = 0; w < wv; ++w) k += s_w[w];
+        if (tid == 0) s_heads = s_w[0] + s_w[1] + s_w[2] + s_w[3];
+        if (head) {
+            const float4 *q = &s_pt[tid + kHalo];
+            double lo[3] = {INFINITY, INFINITY, INFINITY}, hi[3] = {-INFINITY, -INFINITY, -INFINITY};
+            for (int i = 0; i < cnt; ++i) {
+                const double v[3] = {(double)q[i].x, (double)q[i].y, (double)q[i].z};
+                for (int c = 0; c < 3; ++c) { lo[c] = fmin(lo[c], v[c]); hi[c] = fmax(hi[c], v[c]); }
+            }
+            double cc[3], r2 = 0.0, mag = 0.0;
+            for (int c = 0; c < 3; ++c) { cc[c] = 0.5 * (lo[c] + hi[c]); mag = fmax(mag, fabs(cc[c])); }
+            for (int i = 0; i < cnt; ++i) {
+                const double dx = (double)q[i].x - cc[0], dy = (double)q[i].y - cc[1], dz = (double)q[i].z - cc[2];
+                r2 = fmax(r2, dx * dx + dy * dy + dz * dz);
+            }
+            // inflate so FP64 rounding of the transformed centre and points can
+            // never place a member outside the sphere
+            const double r = sqrt(r2) * (1.0 + 1e-12) + 1e-12 * (mag + 1.0);
+            s_geo[k] = make_double4(cc[0], cc[1], cc[2], r);
+            s_first[k] = (int)p;
+            s_n[k] = cnt;
+            s_b[k] = b;
         }
-        // inflate so FP64 rounding of the transformed centre and points can
-        // never place a member outside the sphere
-        const double r = sqrt(r2) * (1.0 + 1e-12) + 1e-12 * (mag + 1.0);
-        clus[idx] = sp;
-        cgeo[idx] = make_double4(cc[0], cc[1], cc[2], r);
-        cpair[idx] = (int)(keys[p] >> cshift);
-        for (int k = 0; k < sp.y; ++k) tclus[sp.x + k] = idx;
+        __syncthreads();
+    }
+    const int nh = s_heads;
+    const bool cut = isfinite(kappa);
+    // lanes per head: as many as leave at most two turns
+    const int lg = nh > 128 ? 1 : (nh > 64 ? 2 : (nh > 32 ? 3 : 4));
+    const int G = 1 << lg, lg_ = tid & (G - 1);
+    for (int k0 = 0; k0 < nh; k0 += kClusThreads >> lg) {
+        const int k = k0 + (tid >> lg);
+        int C = 0;
+        if (k < nh) {
+            const int kb = s_b[k];
+            const PairState *st = a.state + kb;
+            const double *P = a.in[kb].inverse ? st->Tinv : st->T;
+            double Pm[12];
+#pragma unroll
+            for (int i = 0; i < 12; ++i) Pm[i] = P[i];
+            const GridDesc gd = a.grid[kb];
+            const Neighbourhood nb = neighbourhood(Pm, s_geo[k], kappa * st->ell, cut, gd);
+            if (nb.any) {
+                const int nyr = nb.iy1 - nb.iy0 + 1, nrows = nyr * (nb.iz1 - nb.iz0 + 1);
+                const int run = nb.ix1 - nb.ix0 + 1;
+#pragma unroll 4
+                for (int r = lg_; r < nrows; r += G) {
+                    const int iy = nb.iy0 + r % nyr, iz = nb.iz0 + r / nyr;
+                    const long long c0 =
+                        (long long)gd.cell_base + nb.ix0 + (long long)gd.nx * (iy + (long long)gd.ny * iz);
+                    C += a.cell_start[c0 + run] - a.cell_start[c0];
+                }
+            }
+        }
+        for (int off = G >> 1; off > 0; off >>= 1) C += __shfl_xor(C, off);
+        if (lg_ == 0 && k < nh) {
+            const int cm = max(kMinPieceCand, a.work / s_n[k]);
+            s_np[k] = C > 0 ? min((C + cm - 1) / cm, 4096) : 1;
+            s_C[k] = C;
+        }
+    }
+    __syncthreads();
+    // output slots and records (thread k: head k)
+    const int np = tid < nh ? s_np[tid] : 0;
+    const int ns = tid < nh ? np * s_n[tid] : 0;
+    const int ip = wave_scan_add(np), is = wave_scan_add(ns);
+    if (lane == 63) { s_w[wv] = ip; s_w2[wv] = is; }
+    int code = 0, place = 0;
+    if (tid < nh) {
+        const int cand = (s_C[tid] + np - 1) / np;  // candidates per piece
+        code = kCostBuckets - 1 - cost_bucket((unsigned long long)s_n[tid] * (unsigned long long)(cand + 64));
+        place = atomicAdd(&s_hist[code], np);
+    }
+    __syncthreads();
+    for (int k = tid; k < kCostBuckets; k += kClusThreads)
+        if (s_hist[k] > 0) s_hist[k] = atomicAdd(&a.info->hist[k], s_hist[k]);
+    if (tid == 0) {
+        const unsigned long long tp = s_w[0] + s_w[1] + s_w[2] + s_w[3];
+        const unsigned long long ts = s_w2[0] + s_w2[1] + s_w2[2] + s_w2[3];
+        s_base = nh > 0 ? atomicAdd(&a.info->alloc, tp | ts << 32) : 0ULL;
+        s_cbase = nh > 0 ? atomicAdd(&a.info->nclus, nh) : 0;
+    }
+    __syncthreads();
+    if (tid < nh) {
+        int slot = (int)(s_base >> 32) + is - ns;
+        for (int w = 0; w < wv; ++w) slot += s_w2[w];
+        s_slot[tid] = slot;
+        const int n = s_n[tid];
+        ClusterRec r;
+        r.geo = s_geo[tid];
+        r.first = s_first[tid];
+        r.n = n;
+        r.np = np;
+        r.slot = slot;
+        r.b = s_b[tid];
+        r.inverse = a.in[r.b].inverse;
+        r.code = code;
+        r.place = s_hist[code] + place;
+        a.clus[s_cbase + tid] = r;
+    }
+    __syncthreads();
+    for (int k = tid >> 4; k < nh; k += kClusThreads / 16) {
+        const int n = s_n[k], first = s_first[k];
+        for (int t = tid & 15; t < n; t += 16) a.qmap[first + t] = make_int4(t, n, s_np[k], s_slot[k] + t);
+    }
+}
+
+// The pieces' records, bucket by bucket (heaviest first; a cluster's pieces
+// together): 16 lanes per cluster write them.  Nothing is written when there
+// is no room for all of them.
+__global__ __launch_bounds__(256) void record_kernel(const ViewArgs a)
+{
+    static_assert(kCostBuckets == 512, "two buckets per thread");
+    __shared__ int s_base[kCostBuckets];
+    __shared__ int s_w[4];
+    const BuildInfo *f = a.info;
+    if (f->overflow || (long long)(unsigned)f->alloc > a.rec_cap) return;
+    const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6, l16 = tid & 15;
+    const int h0 = f->hist[2 * tid], h1 = f->hist[2 * tid + 1];
+    const int incl = wave_scan_add(h0 + h1);
+    if (lane == 63) s_w[wv] = incl;
+    __syncthreads();
+    int ex = incl - h0 - h1;
+    for (int w = 0; w < wv; ++w) ex += s_w[w];
+    s_base[2 * tid] = ex;
+    s_base[2 * tid + 1] = ex + h0;
+    __syncthreads();
+    const int nclus = f->nclus;
+    for (int c = blockIdx.x * 16 + (tid >> 4); c < nclus; c += gridDim.x * 16) {
+        const ClusterRec r = a.clus[c];
+        const int pos = s_base[r.code] + r.place;
+        for (int k = l16; k < r.np; k += 16) {
+            PieceRec o;
+            o.pc = make_int4(r.first, k, r.np, r.slot + k * r.n);
+            o.b = r.b;
+            o.first = r.first;
+            o.n = r.n;
+            o.inverse = r.inverse;
+            o.geo = r.geo;
+            a.recs[pos + k] = o;
+        }
     }
 }
 
 // ---------------------------------------------------------------- launchers
-void launch_bbox(const CloudPtrs *clouds, int B, float *out, hipStream_t s)
-{
-    hipLaunchKernelGGL(bbox_kernel, dim3(B), dim3(1024), 0, s, clouds, out);
-}
-
 static int blocks_for(long long n, int threads, int cap = 65535)
 {
-    long long b = (n + threads - 1) / threads;
-    if (b < 1) b = 1;
-    if (b > cap) b = cap;
-    return (int)b;
+    return (int)std::min<long long>(std::max<long long>((n + threads - 1) / threads, 1), cap);
 }
 
-void launch_grid_keys(const CloudPtrs *clouds, const GridBuild *gb, int B, long long nmax,
-                      unsigned long long *keys, int *vals, int kbits, hipStream_t s)
+static bool table_sort(const ViewArgs &a) { return std::max(tiles_of(a.n[0]), tiles_of(a.n[1])) <= kTableTiles; }
+
+long long view_table_ints(long long n0, long long n1)
 {
-    hipLaunchKernelGGL(grid_keys, dim3(blocks_for(nmax, 256, 4096), B), dim3(256), 0, s, clouds, gb, keys, vals,
-                       kbits);
+    const long long t0 = tiles_of(n0), t1 = tiles_of(n1);
+    const bool table = std::max(t0, t1) <= kTableTiles;
+    return 256 * std::max(1LL, (table ? kMaxPasses : 1) * (t0 + t1));
 }
 
-void launch_morton_keys(const CloudPtrs *clouds, const ClusterBuild *cb, int B, long long nmax,
-                        unsigned long long *keys, int *vals, int bits, hipStream_t s)
+long long view_bsum_ints(long long n0, long long n1)
 {
-    hipLaunchKernelGGL(morton_keys, dim3(blocks_for(nmax, 256, 4096), B), dim3(256), 0, s, clouds, cb, keys,
-                       vals, bits);
+    return (256 * ((long long)tiles_of(n0) + tiles_of(n1)) + kScanTile - 1) / kScanTile + 1;
 }
 
-void launch_gather(const unsigned long long *keys, const int *vals, long long ntot, int cshift,
-                   const CloudPtrs *clouds, const long long *pt_base, const FeatLayout &lay, float4 *pts,
-                   float *feat, int *perm, hipStream_t s)
+void launch_boxes(const ViewArgs &a, hipStream_t s)
 {
-    hipLaunchKernelGGL(gather_points, dim3(blocks_for(ntot, 256)), dim3(256), 0, s, keys, vals, ntot, cshift,
-                       clouds, pt_base, lay, pts, feat, perm);
+    hipLaunchKernelGGL(box_kernel, dim3(a.boxblocks, 2 * a.B), dim3(256), 0, s, a);
 }
 
-void launch_cell_table(const unsigned long long *keys, long long ntot, const GridBuild *gb, int B,
-                       long long max_cells, int kbits, int *cell_start, hipStream_t s)
+void launch_params(const ViewArgs &a, hipStream_t s)
 {
-    hipLaunchKernelGGL(cell_table, dim3(blocks_for(max_cells + 1, 256, 8192), B), dim3(256), 0, s, keys, ntot,
-                       gb, kbits, cell_start);
+    hipLaunchKernelGGL(params_kernel, dim3(1), dim3(1024), 0, s, a);
 }
 
-void launch_chunk_heads(const float4 *pts, const ClusterBuild *cb, const int2 *caps, int B, long long nchunks,
-                        int *head, int2 *span, hipStream_t s)
+void launch_views(const ViewArgs &a, const FeatLayout &lay, double kappa, hipStream_t s)
 {
-    if (nchunks <= 0) return;
-    hipLaunchKernelGGL(chunk_heads, dim3((unsigned)nchunks), dim3(kWave), 0, s, pts, cb, caps, B, nchunks, head, span);
+    int cbits = 0;
+    while ((1LL << cbits) < a.B) ++cbits;
+    // key bits of each side, at most (the device knows the exact number and
+    // skips passes beyond it)
+    const int most[2] = {24 + cbits, 3 * std::min(kMortonBits, (62 - cbits) / 3) + cbits};
+    const int passes = (std::max(most[0], most[1]) + 7) / 8;
+    const int tiles = std::max(tiles_of(a.n[0]), tiles_of(a.n[1]));
+    if (tiles > 0) {
+        if (table_sort(a)) {
+            hipLaunchKernelGGL(key_kernel<true>, dim3(tiles, 2), dim3(kRadixTile), 0, s, a);
+            for (int p = 0; p < passes; ++p) hipLaunchKernelGGL(sort_pass, dim3(tiles, 2), dim3(kRadixTile), 0, s, a, p);
+        } else {
+            hipLaunchKernelGGL(key_kernel<false>, dim3(tiles, 2), dim3(kRadixTile), 0, s, a);
+            const long long ints = 256LL * (tiles_of(a.n[0]) + tiles_of(a.n[1]));
+            for (int p = 0; p < passes; ++p) {
+                hipLaunchKernelGGL(radix_hist, dim3(tiles, 2), dim3(kRadixTile), 0, s, a, p, a.table);
+                launch_exclusive_scan(a.table, a.table, a.bsum, ints, nullptr, s);
+                hipLaunchKernelGGL(radix_scatter, dim3(tiles, 2), dim3(kRadixTile), 0, s, a, p, a.table);
+            }
+        }
+    }
+    const long long items = std::max(a.n[0], a.n[1]) * (lay.d4 / 4 + 1);
+    hipLaunchKernelGGL(view_kernel, dim3(std::max(1024, blocks_for(items, 256, 16384)), 3), dim3(256), 0, s, a, lay);
+    if (a.n[1] > 0)
+        hipLaunchKernelGGL(cluster_kernel, dim3(blocks_for(a.n[1], kClusThreads, 1 << 30)), dim3(kClusThreads), 0, s, a,
+                           kappa);
 }
 
-void launch_cluster_heads(const unsigned long long *keys, long long ntot, const int2 *caps, int cshift,
-                          int *head, int2 *span, hipStream_t s)
+void launch_records(const ViewArgs &a, hipStream_t s)
 {
-    hipLaunchKernelGGL(cluster_heads, dim3(blocks_for(ntot, 256)), dim3(256), 0, s, keys, ntot, caps, cshift, head,
-                       span);
-}
-
-void launch_cluster_emit(const int *head, const int *hidx, const int2 *span, const float4 *pts,
-                         const unsigned long long *keys, int cshift, long long ntot, int2 *clus, double4 *cgeo,
-                         int *cpair, int *tclus, hipStream_t s)
-{
-    hipLaunchKernelGGL(cluster_emit, dim3(blocks_for(ntot, 256)), dim3(256), 0, s, head, hidx, span, pts, keys,
-                       cshift, ntot, clus, cgeo, cpair, tclus);
+    if (a.n[1] > 0) hipLaunchKernelGGL(record_kernel, dim3(blocks_for(a.n[1], 32, 2048)), dim3(256), 0, s, a);
 }
 
 }  // namespace cvo

@@ -11,12 +11,14 @@
 //                  cell_start[k] = first sorted index with cell >= k, so a
 //                  run of cells along x is one contiguous index range.
 //     cluster view (query side): points sorted by a Morton code; a cluster is
-//                  an aligned octree block holding at most cluster_max points,
-//                  with its centre and radius in the cloud's own frame.  A
+//                  a run of at most cluster_max consecutive points (an aligned
+//                  octree block, or part of a fixed-size chunk), with its
+//                  centre and radius in the cloud's own frame.  A
 //                  rigid motion keeps clusters compact, so they are built once
 //                  per lengthscale band, never per iteration.
-//   Several clouds are prepared together by prefixing every sort key with the
-//   cloud index; the plain path is the batch of one.
+//   The views of several pairs are prepared together, both sides in the same
+//   launches, by prefixing every sort key with the pair index; the plain path
+//   is the batch of one.
 #pragma once
 #include <hip/hip_runtime.h>
 #include <stdint.h>
@@ -29,6 +31,12 @@ constexpr int kQueueCap = 80;    // LDS candidate queue per wave
 constexpr int kQueueFlush = 16;  // process the queue once it holds this many (cap >= flush + 64)
 constexpr int kTraceLen = 8;
 constexpr int kRadixTile = 1024;  // keys per workgroup and pass of the radix sort
+constexpr int kTableTiles = 128;  // sorts of at most this many tiles keep a digit table per pass (one launch a pass)
+constexpr int kMaxPasses = 8;     // 8-bit passes over a 64-bit key
+constexpr long long kCellCap = 1LL << 23;  // cells of one cloud's grid
+constexpr int kMortonBits = 16;   // Morton bits per axis
+constexpr int kBoxBlocks = 64;    // partial bounding boxes per cloud
+constexpr int kMinPieceCand = 512;  // candidates of a piece, at least
 constexpr int kRedVals = 48;     // values reduced per pair by the reduction kernel
 constexpr int kRedThreads = 256;
 
@@ -97,10 +105,56 @@ struct alignas(16) GridDesc {
     long long n;
 };
 
-// Clusters of one cloud (query role).
-struct alignas(16) ClusterDesc {
-    int clus_base, nclus;  // clusters [clus_base, clus_base + nclus)
-    int pt_base, n;        // sorted points [pt_base, pt_base + n)
+// Sorted query points of one pair: [pt_base, pt_base + n).
+struct alignas(8) ClusterDesc {
+    int pt_base, n;
+};
+
+// What a view build needs to know of one pair (uploaded; everything else is
+// derived on the device).
+struct alignas(16) PairIn {
+    const float *xx, *xf;  // reference cloud: coordinates, features
+    const float *zx, *zf;  // query cloud
+    long long nx, nz;
+    long long xb, zb;      // first sorted index of each cloud among its side's clouds
+    double rc;             // cutoff radius (infinite: none)
+    double cell_factor, cluster_factor;
+    int cluster_max;
+    int octree;            // cluster rule: 1 octree blocks, 0 halved chunks
+    int inverse;           // 0: queries are Z (pose T), 1: queries are X (pose T^-1)
+    int pad;
+};
+
+// Cluster parameters of one pair, derived from its query cloud's box.
+struct alignas(16) ClusterParam {
+    double ox, oy, oz;     // Morton origin
+    double iq;             // 1 / quantum (edge of a level-0 block)
+    double cap;            // largest cluster bounding-box edge (chunk rule)
+    int level;             // largest octree level of a cluster (octree rule)
+    int pad;
+};
+
+constexpr int kCostBuckets = 512;  // dispatch order of the pieces: heaviest bucket first
+
+// State of one view build, on the device.
+struct BuildInfo {
+    unsigned long long alloc;  // pieces planned (low 32 bits), output slots (high 32 bits)
+    long long cells;           // cell-table entries of all pairs
+    int bad;                   // a cloud has a non-finite coordinate
+    int overflow;              // the cell tables do not fit: nothing after the boxes was done
+    int nclus;                 // clusters of all pairs
+    int kbits, mbits;          // cell-index bits, Morton bits per axis (the pair index sits above)
+    int sbits[2];              // key bits to sort: reference side, query side
+    int hist[kCostBuckets];    // pieces per cost bucket
+};
+
+// One cluster as planned: its geometry, its points, its pieces and slots.
+struct alignas(64) ClusterRec {
+    double4 geo;               // centre (own frame) and radius
+    int first, n;              // sorted points [first, first + n)
+    int np, slot;              // pieces, first output slot
+    int b, inverse;            // pair, pose orientation
+    int code, place;           // cost bucket of its pieces, their place in it
 };
 
 // Feature layout after combining the spec's blocks: all SE columns first
@@ -129,11 +183,13 @@ struct FeatLayout {
 // concatenation of its neighbourhood rows), so heavy clusters are split into
 // pieces of similar work.  One wave per piece, pieces ordered heaviest first.
 // One piece in dispatch order with what its wave needs first, gathered at
-// planning time so the wave's prologue is one load: the piece (cluster, p,
-// np, first output slot), its pair, its cluster's points and geometry.
+// planning time so the wave's prologue is one load: the piece (cluster's
+// first point, p, np, first output slot), its pair, its cluster's points and
+// geometry.
 struct alignas(32) PieceRec {
     int4 pc;
-    int b, first, n, pad;
+    int b, first, n;
+    int inverse;  // nonzero: queries are X points (pose T^-1)
     double4 geo;
 };
 
@@ -141,10 +197,6 @@ struct PairPassArgs {
     // query side (cluster view)
     const float4 *qpts;
     const float *qfeat;
-    const int2 *clus;     // (first sorted index, count)
-    const double4 *cgeo;  // (centre xyz in the query frame, radius)
-    const int *cpair;     // pair of each cluster
-    int nclus;
     const PieceRec *recs; // the pieces in processing order (heaviest first), with their cluster data
     int npieces;
     // reference side (grid view)
@@ -152,10 +204,9 @@ struct PairPassArgs {
     const float *rfeat;
     const int *cell_start;
     const GridDesc *grids;  // per pair
-    // per-pair pose applied to query points (query frame -> reference frame),
-    // and the pose in canonical orientation (Z frame -> X frame)
+    // per-pair poses: T applied to query points, or T^-1 for pieces marked
+    // inverse (the pair set itself is always decided with T)
     const PairState *state;
-    int pose_is_inverse;    // 0: query = Z (pose T); 1: query = X (pose T^-1)
     float sig2;
     double kappa;           // +inf: no cutoff
     // outputs, indexed by piece slot + position of the query in its cluster

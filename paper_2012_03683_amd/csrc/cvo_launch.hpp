@@ -4,60 +4,56 @@
 
 namespace cvo {
 
+// Caller's buffers of one cloud.
 struct CloudPtrs {
     const float *xyz;
     const float *feat;
     long long n;
 };
 
-typedef GridDesc GridBuild;
-
-struct alignas(16) ClusterBuild {
-    double ox, oy, oz;  // Morton origin
-    double q;           // quantum (edge of a level-0 block)
-    long long pt_base;
-    long long n;
-    double cap;           // largest cluster bounding-box edge (chunk rule)
-    long long chunk_base; // first chunk of this cloud (chunk rule)
+// Arguments of the view build.  Side 0: reference clouds (grid view), side 1:
+// query clouds (cluster view); their keys and sorted arrays hold all pairs'
+// points one after another.
+struct ViewArgs {
+    const PairIn *in;
+    int B;
+    long long n[2];               // points per side
+    float *box;                   // 2 B * kBoxBlocks partial boxes of 8 floats
+    int boxblocks;                // partial boxes per cloud
+    GridDesc *grid;               // B
+    ClusterParam *cp;             // B
+    BuildInfo *info;
+    long long cell_cap;           // entries the cell table has room for
+    // keys and values of both sides, [0, n[0]) and [n[0], n[0] + n[1]), and
+    // the buffers the odd passes write
+    unsigned long long *key[2];
+    int *val[2];
+    int *table;                   // digit tables of both sides, or the histogram of a large sort
+    int *bsum;                    // scan scratch of a large sort
+    int *cell_start;
+    float4 *pts[2];
+    float *feat[2];
+    int *perm;                    // query side: sorted -> own cloud's index
+    const PairState *state;       // poses to plan at
+    ClusterRec *clus;
+    int4 *qmap;
+    int work;                     // query x candidate products per piece
+    PieceRec *recs;
+    long long rec_cap;            // records there is room for
 };
+void launch_boxes(const ViewArgs &a, hipStream_t s);
+void launch_params(const ViewArgs &a, hipStream_t s);
+// keys, sort, sorted copies, cell tables, clusters and their plan
+void launch_views(const ViewArgs &a, const FeatLayout &lay, double kappa, hipStream_t s);
+void launch_records(const ViewArgs &a, hipStream_t s);
+long long view_table_ints(long long n0, long long n1);  // entries of ViewArgs.table
+long long view_bsum_ints(long long n0, long long n1);   // entries of ViewArgs.bsum
 
-void launch_bbox(const CloudPtrs *clouds, int B, float *out, hipStream_t s);
-void launch_grid_keys(const CloudPtrs *clouds, const GridBuild *gb, int B, long long nmax,
-                      unsigned long long *keys, int *vals, int kbits, hipStream_t s);
-void launch_morton_keys(const CloudPtrs *clouds, const ClusterBuild *cb, int B, long long nmax,
-                        unsigned long long *keys, int *vals, int bits, hipStream_t s);
 void launch_exclusive_scan(const int *in, int *out, int *bsum, long long n, int *total, hipStream_t s);
-void launch_radix_sort(unsigned long long *keys, int *vals, unsigned long long *ktmp, int *vtmp, int *hist,
-                       int *bsum, long long n, int bits, hipStream_t s, bool *result_in_tmp);
-void launch_gather(const unsigned long long *keys, const int *vals, long long ntot, int cshift,
-                   const CloudPtrs *clouds, const long long *pt_base, const FeatLayout &lay, float4 *pts,
-                   float *feat, int *perm, hipStream_t s);
-void launch_cell_table(const unsigned long long *keys, long long ntot, const GridBuild *gb, int B,
-                       long long max_cells, int kbits, int *cell_start, hipStream_t s);
-void launch_cluster_heads(const unsigned long long *keys, long long ntot, const int2 *caps, int cshift,
-                          int *head, int2 *span, hipStream_t s);
-// Chunk rule: each cloud's Morton-sorted points cut into chunks of at most
-// cluster_max (caps[c].y) consecutive points, each chunk subdivided by
-// halving until every part's bounding box edge is within cb[c].cap.
-void launch_chunk_heads(const float4 *pts, const ClusterBuild *cb, const int2 *caps, int B, long long nchunks,
-                        int *head, int2 *span, hipStream_t s);
-void launch_cluster_emit(const int *head, const int *hidx, const int2 *span, const float4 *pts,
-                         const unsigned long long *keys, int cshift, long long ntot, int2 *clus, double4 *cgeo,
-                         int *cpair, int *tclus, hipStream_t s);
 
 // pair pass: mode 0 = forward moments, 1 = backward (feature gradients)
 // returns false when no kernel exists for the feature layout
 bool launch_pair_pass(const PairPassArgs &a, const FeatLayout &lay, int mode, hipStream_t s);
-void launch_plan_count(const PairPassArgs &a, int work, int *npieces, int *cmax, long long *ccount, hipStream_t s);
-void launch_plan_emit(const PairPassArgs &a, const int *npieces, const int *pbase, const long long *ccount,
-                      int4 *pieces, int *pn, unsigned long long *key, int *val, int2 *cpieces, hipStream_t s);
-void launch_plan_slots(int4 *pieces, const int *tbase, int npieces, hipStream_t s);
-void launch_plan_qmap(const int2 *clus, const int2 *cpieces, const int4 *pieces, int nclus, int4 *qmap,
-                      hipStream_t s);
-// recs[i] = piece porder[i] with its pair and cluster data (dispatch order)
-void launch_plan_records(const int *porder, const int4 *pieces, const int *cpair, const int2 *clus,
-                         const double4 *cgeo, int npieces, PieceRec *recs, hipStream_t s);
-
 
 // Where a query's partial moments live: qmap[j] = (t, n, np, s0) for query j
 // at position t of a cluster of n queries cut into np pieces; the cluster's
@@ -93,6 +89,7 @@ struct BackwardArgs {
     const int *qperm;         // sorted query index -> original index within its cloud
     const double *D;          // 3 per sorted query (scaled units)
     const double *G;          // d4 per sorted query
+    const double *L;          // 1 per sorted query
     const PairState *state;
     int pose_is_inverse;
     FeatLayout lay;
@@ -102,7 +99,9 @@ struct BackwardArgs {
     const float *src_feat;    // the query cloud's own feature rows (original order, n x src_dim), read
                               // for the chain rule through folded LIN blocks
     long long n;
+    double *lsum;             // per block: the sum of its queries' L (may be null)
 };
+int backward_blocks(long long n);
 void launch_backward_finish(const BackwardArgs &a, hipStream_t s);
 
 // point selection (FAST scores, threshold, raster-order compaction)

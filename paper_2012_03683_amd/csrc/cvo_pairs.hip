@@ -31,47 +31,10 @@
 //   * The sub-streams are combined with lane shuffles (fixed order, so the
 //     result is bitwise reproducible) and one lane per query writes its
 //     moments.
+#include "cvo_device.hpp"
 #include "cvo_launch.hpp"
 
-#include <algorithm>
-
 namespace cvo {
-
-__device__ __forceinline__ void wave_sync()
-{
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-}
-
-__device__ __forceinline__ int wave_uniform(int v) { return __builtin_amdgcn_readfirstlane(v); }
-
-// Inclusive scans over the 64 lanes of a wave with DPP row shifts and row
-// broadcasts (no LDS traffic): within each row of 16 lanes a Hillis-Steele
-// scan over shifts 1, 2, 4, 8 (lanes shifted in from outside the row add
-// the identity 0), then row 0's last lane is added to row 1 and row 2's to
-// row 3, then lane 31 to rows 2 and 3.  The max scan needs values >= 0.
-__device__ __forceinline__ int wave_scan_add(int v)
-{
-    v += __builtin_amdgcn_update_dpp(0, v, 0x111, 0xf, 0xf, false);  // row_shr:1
-    v += __builtin_amdgcn_update_dpp(0, v, 0x112, 0xf, 0xf, false);  // row_shr:2
-    v += __builtin_amdgcn_update_dpp(0, v, 0x114, 0xf, 0xf, false);  // row_shr:4
-    v += __builtin_amdgcn_update_dpp(0, v, 0x118, 0xf, 0xf, false);  // row_shr:8
-    v += __builtin_amdgcn_update_dpp(0, v, 0x142, 0xa, 0xf, false);  // row_bcast:15
-    v += __builtin_amdgcn_update_dpp(0, v, 0x143, 0xc, 0xf, false);  // row_bcast:31
-    return v;
-}
-
-__device__ __forceinline__ int wave_scan_max(int v)
-{
-    v = max(v, __builtin_amdgcn_update_dpp(0, v, 0x111, 0xf, 0xf, false));
-    v = max(v, __builtin_amdgcn_update_dpp(0, v, 0x112, 0xf, 0xf, false));
-    v = max(v, __builtin_amdgcn_update_dpp(0, v, 0x114, 0xf, 0xf, false));
-    v = max(v, __builtin_amdgcn_update_dpp(0, v, 0x118, 0xf, 0xf, false));
-    v = max(v, __builtin_amdgcn_update_dpp(0, v, 0x142, 0xa, 0xf, false));
-    v = max(v, __builtin_amdgcn_update_dpp(0, v, 0x143, 0xc, 0xf, false));
-    return v;
-}
 
 // Wave-uniform floating values kept in scalar registers.
 __device__ __forceinline__ float uniform_f(float v)
@@ -109,44 +72,6 @@ __device__ __noinline__ bool canonical_member(const double *T, float x0, float x
     const double s = (dx * dx + dy * dy) + dz * dz;
     return s <= rc2;
 }
-
-// Cells [i0, i1] along one axis covering [c - R, c + R]; false if none.
-// Uses the same floor((p - o) * inv_h) as the binning.
-__device__ __forceinline__ bool axis_range(double c, double R, double o, double inv_h, int n, int &i0, int &i1)
-{
-    const double f0 = floor(((c - R) - o) * inv_h);
-    const double f1 = floor(((c + R) - o) * inv_h);
-    if (!(f1 >= 0.0) || !(f0 <= (double)(n - 1))) return false;
-    i0 = (int)fmax(f0, 0.0);
-    i1 = (int)fmin(f1, (double)(n - 1));
-    return true;
-}
-
-// Geometry shared by the planner and the pass: the cluster centre in the
-// reference frame, the cull radius, and the cell ranges of its neighbourhood.
-struct Neighbourhood {
-    double cx, cy, cz, Rm;
-    int ix0, ix1, iy0, iy1, iz0, iz1;
-    bool any;
-};
-
-__device__ __forceinline__ Neighbourhood neighbourhood(const double *Pm, const double4 g, double rc, bool cut,
-                                                       const GridDesc &gd)
-{
-    Neighbourhood nb;
-    nb.cx = Pm[0] * g.x + Pm[1] * g.y + Pm[2] * g.z + Pm[3];
-    nb.cy = Pm[4] * g.x + Pm[5] * g.y + Pm[6] * g.z + Pm[7];
-    nb.cz = Pm[8] * g.x + Pm[9] * g.y + Pm[10] * g.z + Pm[11];
-    nb.Rm = cut ? (rc + g.w) * (1.0 + 1e-5) : INFINITY;
-    nb.ix0 = 0; nb.ix1 = gd.nx - 1; nb.iy0 = 0; nb.iy1 = gd.ny - 1; nb.iz0 = 0; nb.iz1 = gd.nz - 1;
-    nb.any = gd.n > 0;
-    if (cut && nb.any)
-        nb.any = axis_range(nb.cx, nb.Rm, gd.ox, gd.inv_h, gd.nx, nb.ix0, nb.ix1) &&
-                 axis_range(nb.cy, nb.Rm, gd.oy, gd.inv_h, gd.ny, nb.iy0, nb.iy1) &&
-                 axis_range(nb.cz, nb.Rm, gd.oz, gd.inv_h, gd.nz, nb.iz0, nb.iz1);
-    return nb;
-}
-
 
 template <int SED, int LIND, int MODE> struct PassTraits {
     static constexpr int D = SED + LIND;
@@ -193,7 +118,8 @@ void pair_pass_kernel(const PairPassArgs a)
         const int4 pc = rec.pc;
         const int b = wave_uniform(rec.b);
         const PairState *st = a.state + b;
-        const double *P = a.pose_is_inverse ? st->Tinv : st->T;
+        const int inverse = wave_uniform(rec.inverse);
+        const double *P = inverse ? st->Tinv : st->T;
         double Pm[12];
 #pragma unroll
         for (int k = 0; k < 12; ++k) Pm[k] = P[k];
@@ -286,7 +212,7 @@ void pair_pass_kernel(const PairPassArgs a)
                 if (s > lo) {
                     const float4 rp = a.rpts[__float_as_int(ent[0].w)];
                     const float4 zq2 = a.qpts[pq];
-                    pass = a.pose_is_inverse
+                    pass = inverse
                                ? canonical_member(st->T, zq2.x, zq2.y, zq2.z, rp.x, rp.y, rp.z, rc2)
                                : canonical_member(st->T, rp.x, rp.y, rp.z, zq2.x, zq2.y, zq2.z, rc2);
                 }
@@ -498,142 +424,6 @@ void pair_pass_kernel(const PairPassArgs a)
             }
         }
     }
-}
-
-// ---------------------------------------------------------------- planning
-// Per cluster, at the current pose: the number of candidates of its
-// neighbourhood and how many pieces to cut it into (work per piece about
-// `work` query-candidate products, at least 512 candidates per piece).
-__global__ void plan_count(const PairPassArgs a, int work, int *npieces, int *cmax, long long *ccount)
-{
-    for (int c = blockIdx.x * blockDim.x + threadIdx.x; c < a.nclus; c += gridDim.x * blockDim.x) {
-        const int b = a.cpair[c];
-        const PairState *st = a.state + b;
-        const double *P = a.pose_is_inverse ? st->Tinv : st->T;
-        double Pm[12];
-        for (int k = 0; k < 12; ++k) Pm[k] = P[k];
-        const bool cut = isfinite(a.kappa);
-        const double rc = a.kappa * st->ell;
-        const GridDesc gd = a.grids[b];
-        const Neighbourhood nb = neighbourhood(Pm, a.cgeo[c], rc, cut, gd);
-        long long C = 0;
-        if (nb.any) {
-            const int run = nb.ix1 - nb.ix0 + 1;
-            for (int iz = nb.iz0; iz <= nb.iz1; ++iz)
-                for (int iy = nb.iy0; iy <= nb.iy1; ++iy) {
-                    const long long k0 =
-                        (long long)gd.cell_base + nb.ix0 + (long long)gd.nx * (iy + (long long)gd.ny * iz);
-                    C += a.cell_start[k0 + run] - a.cell_start[k0];
-                }
-        }
-        const int n = a.clus[c].y;
-        const int cm = max(512, work / max(n, 1));
-        const long long np = C > 0 ? (C + cm - 1) / cm : 1;
-        npieces[c] = (int)min(np, 4096LL);
-        cmax[c] = cm;
-        ccount[c] = C;
-    }
-}
-
-// A piece's cost on 16 bits, non-decreasing in the cost: exact below 49152
-// (every piece of the default plan: n <= 64 queries x at most 576), then
-// 1024 steps per doubling.
-constexpr unsigned long long kCostLinear = 49152;
-__device__ __forceinline__ unsigned int piece_cost_code(unsigned long long cost)
-{
-    if (cost < kCostLinear) return (unsigned int)cost;
-    const double q = (log2((double)cost) - log2((double)kCostLinear)) * 1024.0;
-    return (unsigned int)min((double)kCostLinear + floor(q), 65535.0);
-}
-
-// Emit the pieces of each cluster (cluster-major) as (cluster, p, np), their
-// query counts (for the output-slot scan) and a sort key: the heaviest piece
-// gets the smallest key; the stable sort keeps a cluster's pieces together.
-__global__ void plan_emit(const PairPassArgs a, const int *npieces, const int *pbase, const long long *ccount,
-                          int4 *pieces, int *pn, unsigned long long *key, int *val, int2 *cpieces)
-{
-    for (int c = blockIdx.x * blockDim.x + threadIdx.x; c < a.nclus; c += gridDim.x * blockDim.x) {
-        const int np = npieces[c], pb = pbase[c];
-        const int n = a.clus[c].y;
-        const long long C = ccount[c];
-        cpieces[c] = make_int2(pb, np);
-        const long long cand = (C + np - 1) / np;  // candidates per piece
-        for (int p = 0; p < np; ++p) {
-            pieces[pb + p] = make_int4(c, p, np, 0);
-            pn[pb + p] = n;
-            const unsigned long long cost = (unsigned long long)n * (unsigned long long)(cand + 64);
-            key[pb + p] = 0xffffULL - (unsigned long long)piece_cost_code(cost);  // 16-bit key
-            val[pb + p] = pb + p;
-        }
-    }
-}
-
-__global__ void plan_slots(int4 *pieces, const int *tbase, int npieces)
-{
-    for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < npieces; i += gridDim.x * blockDim.x)
-        pieces[i].w = tbase[i];
-}
-
-__global__ void plan_qmap(const int2 *clus, const int2 *cpieces, const int4 *pieces, int nclus, int4 *qmap)
-{
-    for (int c = blockIdx.x * blockDim.x + threadIdx.x; c < nclus; c += gridDim.x * blockDim.x) {
-        const int2 cl = clus[c];
-        const int2 cp = cpieces[c];
-        const int slot0 = pieces[cp.x].w;
-        for (int t = 0; t < cl.y; ++t) qmap[cl.x + t] = make_int4(t, cl.y, cp.y, slot0 + t);
-    }
-}
-
-void launch_plan_qmap(const int2 *clus, const int2 *cpieces, const int4 *pieces, int nclus, int4 *qmap,
-                      hipStream_t s)
-{
-    const int nb = std::max(1, std::min(4096, (nclus + 255) / 256));
-    hipLaunchKernelGGL(plan_qmap, dim3(nb), dim3(256), 0, s, clus, cpieces, pieces, nclus, qmap);
-}
-
-__global__ void plan_records(const int *porder, const int4 *pieces, const int *cpair, const int2 *clus,
-                             const double4 *cgeo, int npieces, PieceRec *recs)
-{
-    for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < npieces; i += gridDim.x * blockDim.x) {
-        const int4 pc = pieces[porder[i]];
-        const int2 cl = clus[pc.x];
-        PieceRec r;
-        r.pc = pc;
-        r.b = cpair[pc.x];
-        r.first = cl.x;
-        r.n = cl.y;
-        r.pad = 0;
-        r.geo = cgeo[pc.x];
-        recs[i] = r;
-    }
-}
-
-void launch_plan_records(const int *porder, const int4 *pieces, const int *cpair, const int2 *clus,
-                         const double4 *cgeo, int npieces, PieceRec *recs, hipStream_t s)
-{
-    if (npieces <= 0) return;
-    const int nb = std::max(1, std::min(4096, (npieces + 255) / 256));
-    hipLaunchKernelGGL(plan_records, dim3(nb), dim3(256), 0, s, porder, pieces, cpair, clus, cgeo, npieces, recs);
-}
-
-void launch_plan_count(const PairPassArgs &a, int work, int *npieces, int *cmax, long long *ccount, hipStream_t s)
-{
-    const int nb = std::max(1, std::min(4096, (a.nclus + 255) / 256));
-    hipLaunchKernelGGL(plan_count, dim3(nb), dim3(256), 0, s, a, work, npieces, cmax, ccount);
-}
-
-void launch_plan_emit(const PairPassArgs &a, const int *npieces, const int *pbase, const long long *ccount,
-                      int4 *pieces, int *pn, unsigned long long *key, int *val, int2 *cpieces, hipStream_t s)
-{
-    const int nb = std::max(1, std::min(4096, (a.nclus + 255) / 256));
-    hipLaunchKernelGGL(plan_emit, dim3(nb), dim3(256), 0, s, a, npieces, pbase, ccount, pieces, pn, key, val,
-                       cpieces);
-}
-
-void launch_plan_slots(int4 *pieces, const int *tbase, int npieces, hipStream_t s)
-{
-    const int nb = std::max(1, std::min(4096, (npieces + 255) / 256));
-    hipLaunchKernelGGL(plan_slots, dim3(nb), dim3(256), 0, s, pieces, tbase, npieces);
 }
 
 // ---------------------------------------------------------------- dispatch

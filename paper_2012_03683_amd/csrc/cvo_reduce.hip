@@ -541,8 +541,9 @@ void launch_reduce(const ReduceArgs &a, int B, hipStream_t s)
 // d(gF F)/d(query point) = gF * R_P^T D / ell^2, with R_P the rotation of
 // the pose that mapped queries into the reference frame (T for Z, T^-1 for
 // X), and feature gradients scaled back from pre-scaled columns.
-__global__ void backward_finish(const BackwardArgs a)
+__global__ __launch_bounds__(256) void backward_finish(const BackwardArgs a)
 {
+    double lacc = 0.0;
     const PairState *st = a.state;
     const double *P = a.pose_is_inverse ? st->Tinv : st->T;
     const double ell = st->ell;
@@ -552,6 +553,8 @@ __global__ void backward_finish(const BackwardArgs a)
          p += (long long)gridDim.x * blockDim.x) {
         const long long o = a.qperm[p];
         const int4 qm = a.map.qmap[p];  // (t, cluster size, pieces, first slot)
+        if (a.lsum)
+            for (int k = 0; k < qm.z; ++k) lacc += a.L[(long long)qm.w + (long long)k * qm.y];
         if (a.dxyz) {
             double d0 = 0.0, d1 = 0.0, d2 = 0.0;
             for (int k = 0; k < qm.z; ++k) {
@@ -601,14 +604,28 @@ __global__ void backward_finish(const BackwardArgs a)
                     }
         }
     }
+    if (a.lsum) {
+        // (fixed order: grid-stride queries per thread, then this tree)
+        __shared__ double sh[256];
+        sh[threadIdx.x] = lacc;
+        __syncthreads();
+        for (int s = 128; s > 0; s >>= 1) {
+            if (threadIdx.x < s) sh[threadIdx.x] += sh[threadIdx.x + s];
+            __syncthreads();
+        }
+        if (threadIdx.x == 0) a.lsum[blockIdx.x] = sh[0];
+    }
+}
+
+int backward_blocks(long long n)
+{
+    const long long nb = (n + 255) / 256;
+    return (int)(nb < 1 ? 1 : (nb > 4096 ? 4096 : nb));
 }
 
 void launch_backward_finish(const BackwardArgs &a, hipStream_t s)
 {
-    long long nb = (a.n + 255) / 256;
-    if (nb < 1) nb = 1;
-    if (nb > 4096) nb = 4096;
-    hipLaunchKernelGGL(backward_finish, dim3((unsigned)nb), dim3(256), 0, s, a);
+    hipLaunchKernelGGL(backward_finish, dim3(backward_blocks(a.n)), dim3(256), 0, s, a);
 }
 
 __global__ __launch_bounds__(256) void sum_doubles(const double *in, long long n, double *out)
