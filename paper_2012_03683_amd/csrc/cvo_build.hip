@@ -151,7 +151,7 @@ __global__ __launch_bounds__(1024) void params_kernel(const ViewArgs a)
                 // octree blocks need 16 quanta per cap; chunks only use the
                 // Morton order, which a finer quantum makes more local
                 const double cap = isfinite(in.rc) ? in.cluster_factor * in.rc : ext * 2.0;
-                int L = in.octree ? 4 : 6;
+                int L = in.octree ? 4 : 5;
                 double q = cap / (double)(1 << L);
                 // quanta needed to cover the box must fit in maxbits per axis
                 if (!(ext / q + 1.0 <= (double)(1 << maxbits))) {
@@ -548,24 +548,89 @@ __device__ inline long long lower_bound_u64(const unsigned long long *a, long lo
     return lo;
 }
 
+// The key that entry k of the joint cell tables counts up to: the entry is
+// the number of keys below it.
+__device__ __forceinline__ unsigned long long entry_key(const ViewArgs &a, int kbits, long long k)
+{
+    int lo = 0, hi = a.B - 1;
+    while (lo < hi) {
+        const int mid = (lo + hi + 1) >> 1;
+        if (a.grid[mid].cell_base <= k) lo = mid; else hi = mid - 1;
+    }
+    return ((unsigned long long)lo << kbits) | (unsigned long long)(k - a.grid[lo].cell_base);
+}
+
+// Number of sorted keys below x, found by one wave: each round the lanes probe
+// 64 evenly spaced keys (three rounds up to 262,144 keys, where a bisection
+// takes 18 dependent loads).
+__device__ __forceinline__ int wave_lower_bound(const unsigned long long *keys, long long n, unsigned long long x)
+{
+    const int lane = threadIdx.x & 63;
+    long long lo = 0, len = n;  // the answer is in [lo, lo + len]
+    while (len > 0) {
+        const long long step = (len + 63) / 64;
+        const long long i = lo + (lane + 1LL) * step - 1;
+        const bool less = i < lo + len && keys[min(i, n - 1)] < x;
+        const int c = __popcll(__ballot(less));  // the first c probes are below x
+        const long long end = lo + len;
+        lo += c * step;
+        len = max(0LL, min(step - 1, end - lo));
+    }
+    return (int)lo;
+}
+
+// The cell tables, 256 consecutive entries per wave and turn: two searches
+// find the run of keys that falls in them.  Most of a grid of surfaces is
+// empty and is filled with one value; elsewhere each lane bisects the run for
+// its four entries at once (their loads overlap).  One bisection per entry
+// over all keys costs 15 dependent loads for each of up to 8 million entries:
+// 40 us at 14,873 points and half-radius cells of 0.15 m, now 7.
+__device__ void cell_entries(const ViewArgs &a)
+{
+    const unsigned long long *keys = a.key[passes_of(a, 0) & 1];
+    const int kbits = a.info->kbits;
+    const long long total = a.info->cells, n = a.n[0];
+    const int lane = threadIdx.x & 63;
+    for (long long k0 = 256LL * (blockIdx.x * 4LL + (threadIdx.x >> 6)); k0 < total; k0 += 1024LL * gridDim.x) {
+        const long long last = min(k0 + 255, total - 1);
+        const int lo = wave_lower_bound(keys, n, entry_key(a, kbits, k0));
+        const int hi = wave_lower_bound(keys, n, entry_key(a, kbits, last));
+        const long long k = k0 + 4 * lane;
+        int e[4] = {lo, lo, lo, lo};
+        if (lo < hi) {
+            unsigned long long x[4];
+#pragma unroll
+            for (int q = 0; q < 4; ++q) x[q] = entry_key(a, kbits, min(k + q, last));
+            int len = hi - lo;
+            while (len > 1) {
+                const int half = len >> 1;
+#pragma unroll
+                for (int q = 0; q < 4; ++q) e[q] += keys[e[q] + half - 1] < x[q] ? half : 0;
+                len -= half;
+            }
+#pragma unroll
+            for (int q = 0; q < 4; ++q) e[q] += keys[e[q]] < x[q] ? 1 : 0;
+        }
+        if (k + 3 <= last) {
+            *reinterpret_cast<int4 *>(a.cell_start + k) = make_int4(e[0], e[1], e[2], e[3]);
+        } else {
+#pragma unroll
+            for (int q = 0; q < 4; ++q)
+                if (k + q <= last) a.cell_start[k + q] = e[q];
+        }
+    }
+}
+
 // blockIdx.y 0 and 1: sorted copies of a side -- the float4 coordinates and
 // the padded feature row, one float4 per thread, so a row is read and written
 // by consecutive threads (destination column k = source column col[k] times
-// scale[k]).  blockIdx.y 2: the cell tables, one lower bound per cell.
+// scale[k]).  blockIdx.y 2: the cell tables.
 __global__ __launch_bounds__(256) void view_kernel(const ViewArgs a, const FeatLayout lay)
 {
     if (a.info->overflow) return;
     const int side = blockIdx.y;
     if (side == 2) {
-        const unsigned long long *keys = a.key[passes_of(a, 0) & 1];
-        const int kbits = a.info->kbits;
-        const long long total = a.info->cells;
-        int b = 0;
-        for (long long k = (long long)blockIdx.x * 256 + threadIdx.x; k < total; k += (long long)gridDim.x * 256) {
-            while (b + 1 < a.B && a.grid[b + 1].cell_base <= k) ++b;
-            const unsigned long long target = ((unsigned long long)b << kbits) | (unsigned long long)(k - a.grid[b].cell_base);
-            a.cell_start[k] = (int)lower_bound_u64(keys, a.n[0], target);
-        }
+        cell_entries(a);
         return;
     }
     __shared__ int s_col[64];
@@ -625,9 +690,9 @@ __device__ __forceinline__ int cost_bucket(unsigned long long cost)
 
 constexpr int kHalo = 64;         // points beside a block that a cluster may reach
 constexpr int kClusThreads = 256;
-constexpr int kClusSpan = kClusThreads + 2 * kHalo;
+constexpr int kClusBlocks = 256;  // blocks up to which a block takes fewer points
 
-// One thread per sorted query point finds the point's cluster; the first
+// A block takes PTS points.  One thread per point finds the point's cluster; the first
 // point of a cluster is its head.
 //   octree rule: the largest aligned Morton block (level <= ClusterParam.level)
 //     holding at most cluster_max points.  Block counts grow with the level, so
@@ -638,27 +703,33 @@ constexpr int kClusSpan = kClusThreads + 2 * kHalo;
 //   chunk rule: chunks of cluster_max consecutive points of the cloud, halved
 //     until the part's bounding box edge is within ClusterParam.cap or the part
 //     is one point.
-// Then 2 to 16 lanes per head count the candidates of its neighbourhood at
+// Then 2 to 64 lanes per head count the candidates of its neighbourhood at
 // the current pose (one grid row per lane and turn), from which its pieces
 // follow: c_max = max(512, work / n) candidates each.  A block reserves its
 // clusters' output slots, records and places in the cost buckets with one
 // atomic each (an atomic per cluster serialises on the few buckets that most
 // clusters of a sparse cloud share: 22 us for 1,900 of them).
+// The kernel is a chain of dependent loads, so fewer points per block (more
+// blocks, more lanes per head) are faster until the blocks' atomics become
+// the bound: blocks of 64 / 256 points take 14.2 / 25.0 us at 15,000 points
+// and 20.5 / 13.3 us at 30,000, so a block takes as few as keep their number
+// within 256.
+template <int PTS>
 __global__ __launch_bounds__(kClusThreads) void cluster_kernel(const ViewArgs a, double kappa)
 {
+    constexpr int kClusSpan = PTS + 2 * kHalo;
     if (a.info->overflow) return;
     __shared__ float4 s_pt[kClusSpan];
     __shared__ unsigned long long s_key[kClusSpan];
-    __shared__ double4 s_geo[kClusThreads];
-    __shared__ int s_first[kClusThreads], s_n[kClusThreads], s_b[kClusThreads], s_np[kClusThreads], s_C[kClusThreads];
-    __shared__ int s_slot[kClusThreads];
+    __shared__ double4 s_geo[PTS];
+    __shared__ int s_first[PTS], s_n[PTS], s_b[PTS], s_np[PTS], s_C[PTS], s_slot[PTS];
     __shared__ int s_hist[kCostBuckets];
     __shared__ int s_w[4], s_w2[4], s_heads;
     __shared__ unsigned long long s_base;
     __shared__ int s_cbase;
     const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
     const long long N = a.n[1];
-    const long long p0 = (long long)blockIdx.x * kClusThreads;
+    const long long p0 = (long long)blockIdx.x * PTS;
     const int buf = passes_of(a, 1) & 1;
     const unsigned long long *keys = a.key[buf] + a.n[0];
     for (int k = tid; k < kClusSpan; k += kClusThreads) {
@@ -673,7 +744,7 @@ __global__ __launch_bounds__(kClusThreads) void cluster_kernel(const ViewArgs a,
     const int shift = 3 * a.info->mbits;
     bool head = false;
     int cnt = 0, b = 0;
-    if (p < N) {
+    if (tid < PTS && p < N) {
         const int me = tid + kHalo;
         const unsigned long long key = s_key[me];
         b = (int)(key >> shift);
@@ -758,8 +829,8 @@ __global__ __launch_bounds__(kClusThreads) void cluster_kernel(const ViewArgs a,
     }
     const int nh = s_heads;
     const bool cut = isfinite(kappa);
-    // lanes per head: as many as leave at most two turns
-    const int lg = nh > 128 ? 1 : (nh > 64 ? 2 : (nh > 32 ? 3 : 4));
+    // lanes per head: as many as leave at most two turns (nh <= 256 / 2)
+    const int lg = nh > 128 ? 1 : (nh > 64 ? 2 : (nh > 32 ? 3 : (nh > 16 ? 4 : (nh > 8 ? 5 : 6))));
     const int G = 1 << lg, lg_ = tid & (G - 1);
     for (int k0 = 0; k0 < nh; k0 += kClusThreads >> lg) {
         const int k = k0 + (tid >> lg);
@@ -929,10 +1000,16 @@ void launch_views(const ViewArgs &a, const FeatLayout &lay, double kappa, hipStr
         }
     }
     const long long items = std::max(a.n[0], a.n[1]) * (lay.d4 / 4 + 1);
-    hipLaunchKernelGGL(view_kernel, dim3(std::max(1024, blocks_for(items, 256, 16384)), 3), dim3(256), 0, s, a, lay);
-    if (a.n[1] > 0)
-        hipLaunchKernelGGL(cluster_kernel, dim3(blocks_for(a.n[1], kClusThreads, 1 << 30)), dim3(kClusThreads), 0, s, a,
-                           kappa);
+    hipLaunchKernelGGL(view_kernel, dim3(std::max(2048, blocks_for(items, 256, 16384)), 3), dim3(256), 0, s, a, lay);
+    if (a.n[1] > 0) {
+        if (a.n[1] <= 64 * kClusBlocks)
+            hipLaunchKernelGGL(cluster_kernel<64>, dim3(blocks_for(a.n[1], 64)), dim3(kClusThreads), 0, s, a, kappa);
+        else if (a.n[1] <= 128 * kClusBlocks)
+            hipLaunchKernelGGL(cluster_kernel<128>, dim3(blocks_for(a.n[1], 128)), dim3(kClusThreads), 0, s, a, kappa);
+        else
+            hipLaunchKernelGGL(cluster_kernel<256>, dim3(blocks_for(a.n[1], 256, 1 << 30)), dim3(kClusThreads), 0, s, a,
+                               kappa);
+    }
 }
 
 void launch_records(const ViewArgs &a, hipStream_t s)
