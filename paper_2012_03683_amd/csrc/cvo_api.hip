@@ -663,7 +663,7 @@ void build_pairs(cvo_context *ctx, Views &v, const std::vector<PairSpec> &pairs,
 
 // ------------------------------------------------------------------ pair pass + reduce
 struct Moments {
-    double *W, *D, *G, *L;
+    double *W, *D, *B;
     float *S;
     int *cnt;
 };
@@ -672,16 +672,13 @@ Moments moments(cvo_context *ctx, const std::string &pre, long long n, int d4, b
 {
     Moments m{};
     n = std::max(n, 1LL);
-    m.W = ctx->get_t<double>(pre + ".W", n);
-    m.D = ctx->get_t<double>(pre + ".D", 3 * n);
-    m.cnt = ctx->get_t<int>(pre + ".cnt", n);
     if (backward) {
-        m.G = ctx->get_t<double>(pre + ".G", n * std::max(d4, 1));
-        m.L = ctx->get_t<double>(pre + ".L", n);
-        m.S = nullptr;
+        m.B = ctx->get_t<double>(pre + ".B", n * (4 + d4));
     } else {
+        m.W = ctx->get_t<double>(pre + ".W", n);
+        m.D = ctx->get_t<double>(pre + ".D", 3 * n);
+        m.cnt = ctx->get_t<int>(pre + ".cnt", n);
         m.S = ctx->get_t<float>(pre + ".S", 6 * n);
-        m.G = m.L = nullptr;
     }
     return m;
 }
@@ -703,8 +700,7 @@ PairPassArgs pass_args(const Views &v, const PairState *st, float sig2, double k
     a.oD = m.D;
     a.oS = m.S;
     a.oCnt = m.cnt;
-    a.oG = m.G;
-    a.oL = m.L;
+    a.oB = m.B;
     a.recs = v.a.recs;
     a.npieces = v.npieces;
     return a;
@@ -1528,35 +1524,35 @@ cvo_status cvo_inner_product_backward(cvo_handle h, const cvo_cloud *X, const cv
             const PairState *d_state = v.a.state;
             Moments m = moments(h, "bm", v.nslots, lay.d4, true);
             run_pair_pass(h, pass_args(v, d_state, lay.sig2, kp->kappa, m), lay, 1);
+            BackwardArgs ba;
+            std::memset(&ba, 0, sizeof(ba));
+            ba.nsides = (int)sides.size();
+            ba.B = m.B;
+            ba.state = d_state;
+            ba.lay = lay;
+            ba.gF = gF;
+            double *part = nullptr;
             for (size_t k = 0; k < sides.size(); ++k) {
                 const bool src = sides[k].inverse;
-                BackwardArgs ba;
-                std::memset(&ba, 0, sizeof(ba));
-                ba.map = SlotMap{v.a.qmap + v.desc[k].pt_base};
-                ba.qperm = v.a.perm + v.desc[k].pt_base;
-                ba.D = m.D;
-                ba.G = m.G;
-                ba.L = m.L;
-                ba.state = d_state;
-                ba.pose_is_inverse = src;
-                ba.lay = lay;
-                ba.gF = gF;
-                ba.dxyz = src ? dX : dZ;
-                ba.dfeat = src ? dU : dV;
-                ba.src_feat = src ? X->feat : Z->feat;
-                ba.n = src ? N : M;
-                const int nb = backward_blocks(ba.n);
-                double *part = !src && dEll ? h->get_t<double>("bsum", nb + 1) : nullptr;
-                ba.lsum = part;
-                launch_backward_finish(ba, h->stream);
-                h->check_launch("backward");
-                if (part) {
-                    launch_sum_doubles(part, nb, part + nb, h->stream);
-                    double sl = 0.0;
-                    h->download(&sl, part + nb, sizeof(double));
-                    const double ascale = kLog2e / (2.0 * kp->ell * kp->ell);
-                    *dEll = gF * sl / (ascale * kp->ell * kp->ell * kp->ell);
-                }
+                BackwardSide &bs = ba.side[k];
+                bs.qmap = v.a.qmap + v.desc[k].pt_base;
+                bs.qperm = v.a.perm + v.desc[k].pt_base;
+                bs.pose_is_inverse = src;
+                bs.n = src ? N : M;
+                bs.dxyz = src ? dX : dZ;
+                bs.dfeat = src ? dU : dV;
+                bs.src_feat = src ? X->feat : Z->feat;
+                if (!src && dEll) bs.lsum = part = h->get_t<double>("bsum", backward_blocks(M) + 1);
+            }
+            launch_backward_finish(ba, h->stream);
+            h->check_launch("backward");
+            if (part) {
+                const int nb = backward_blocks(M);
+                launch_sum_doubles(part, nb, part + nb, h->stream);
+                double sl = 0.0;
+                h->download(&sl, part + nb, sizeof(double));
+                const double ascale = kLog2e / (2.0 * kp->ell * kp->ell);
+                *dEll = gF * sl / (ascale * kp->ell * kp->ell * kp->ell);
             }
         }
         HIP_OK(hipStreamSynchronize(h->stream));

@@ -213,9 +213,11 @@ struct PairPassArgs {
     double *oW;
     double *oD;     // 3 per query
     float *oS;      // 6 per query (forward mode)
-    int *oCnt;
-    double *oG;     // d4 per query (backward mode): feature gradients
-    double *oL;     // 1 per query (backward mode): sum w s'
+    int *oCnt;      // (forward mode)
+    // backward mode: D (3 values), sum w s', then d4 feature gradients.  A piece
+    // of a cluster of n queries owns n slots from its first slot f: value v of
+    // query t is at f (4 + d4) + v n + t
+    double *oB;
 };
 
 }  // namespace cvo

@@ -83,23 +83,25 @@ struct ReduceArgs {
 };
 void launch_reduce(const ReduceArgs &a, int B, hipStream_t s);
 
-// backward post-processing
-struct BackwardArgs {
-    SlotMap map;
+// backward post-processing: one or two sides, each the queries of one cloud
+struct BackwardSide {
+    const int4 *qmap;         // of the side's queries
     const int *qperm;         // sorted query index -> original index within its cloud
-    const double *D;          // 3 per sorted query (scaled units)
-    const double *G;          // d4 per sorted query
-    const double *L;          // 1 per sorted query
-    const PairState *state;
     int pose_is_inverse;
-    FeatLayout lay;
-    double gF;
+    long long n;
     float *dxyz;              // original-order output, n x 3 (may be null)
     float *dfeat;             // original-order output, n x src_dim (may be null)
     const float *src_feat;    // the query cloud's own feature rows (original order, n x src_dim), read
                               // for the chain rule through folded LIN blocks
-    long long n;
     double *lsum;             // per block: the sum of its queries' L (may be null)
+};
+struct BackwardArgs {
+    BackwardSide side[2];
+    int nsides;
+    const double *B;          // per-piece partial values (PairPassArgs.oB)
+    const PairState *state;
+    FeatLayout lay;
+    double gF;
 };
 int backward_blocks(long long n);
 void launch_backward_finish(const BackwardArgs &a, hipStream_t s);

@@ -23,6 +23,8 @@
 // takes the ascent step -- so results are bitwise reproducible.
 #include "cvo_launch.hpp"
 
+#include <algorithm>
+
 namespace cvo {
 
 // accumulator slots (R_LOGW .. R_ZP: the lengthscale objective's sums over
@@ -541,91 +543,97 @@ void launch_reduce(const ReduceArgs &a, int B, hipStream_t s)
 // d(gF F)/d(query point) = gF * R_P^T D / ell^2, with R_P the rotation of
 // the pose that mapped queries into the reference frame (T for Z, T^-1 for
 // X), and feature gradients scaled back from pre-scaled columns.
+// A block takes 64 queries: a wave adds one value's partials over the pieces
+// of all 64 (neighbouring queries are neighbours in memory), the sums meet in
+// LDS, and the rows are written with consecutive threads on consecutive
+// columns.  Bound by reading the partials: 20,011 x 17,389 points of 24
+// columns, both sides: 2 x 63 us with a thread per query and value-strided
+// partials, 35 us for both now.
+constexpr int kBackQ = 64;  // queries per block
+
 __global__ __launch_bounds__(256) void backward_finish(const BackwardArgs a)
 {
-    double lacc = 0.0;
+    extern __shared__ double s_v[];  // value v of query q at v * (kBackQ + 1) + q
+    const BackwardSide &sd = a.side[blockIdx.y];
+    const long long p0 = (long long)blockIdx.x * kBackQ;
+    if (p0 >= sd.n) return;
+    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+    const int d4 = a.lay.d4, nv = 4 + d4;
+    const bool in = p0 + lane < sd.n;
+    const int4 qm = in ? sd.qmap[p0 + lane] : make_int4(0, 0, 0, 0);  // (t, cluster size, pieces, first slot)
+    const long long f0 = qm.w - qm.x;
+    for (int v = wv; v < nv; v += 4) {
+        if (v < 3 ? !sd.dxyz : v == 3 ? !sd.lsum : !sd.dfeat) continue;
+        double x = 0.0;
+        const double *B = a.B + f0 * nv + (long long)v * qm.y + qm.x;
+        for (int k = 0; k < qm.z; ++k) x += B[(long long)k * qm.y * nv];
+        s_v[v * (kBackQ + 1) + lane] = x;
+    }
+    __syncthreads();
     const PairState *st = a.state;
-    const double *P = a.pose_is_inverse ? st->Tinv : st->T;
+    const double *P = sd.pose_is_inverse ? st->Tinv : st->T;
     const double ell = st->ell;
     const double ascale = 1.4426950408889634 / (2.0 * ell * ell);
     const double f = a.gF / (sqrt(ascale) * ell * ell);
-    for (long long p = (long long)blockIdx.x * blockDim.x + threadIdx.x; p < a.n;
-         p += (long long)gridDim.x * blockDim.x) {
-        const long long o = a.qperm[p];
-        const int4 qm = a.map.qmap[p];  // (t, cluster size, pieces, first slot)
-        if (a.lsum)
-            for (int k = 0; k < qm.z; ++k) lacc += a.L[(long long)qm.w + (long long)k * qm.y];
-        if (a.dxyz) {
-            double d0 = 0.0, d1 = 0.0, d2 = 0.0;
-            for (int k = 0; k < qm.z; ++k) {
-                const long long s = (long long)qm.w + (long long)k * qm.y;
-                d0 += a.D[3 * s];
-                d1 += a.D[3 * s + 1];
-                d2 += a.D[3 * s + 2];
-            }
-            for (int k = 0; k < 3; ++k)
-                a.dxyz[3 * o + k] = (float)(f * (P[k] * d0 + P[4 + k] * d1 + P[8 + k] * d2));
-        }
-        if (a.dfeat) {
-            // folded LIN blocks: the gradient of a tensor-product column c
-            // reaches u_b[digit_b(c)] times the other blocks' factors of c
-            double gl[64];
-            if (a.lay.nlin > 0)
-                for (int k = 0; k < 64; ++k) gl[k] = 0.0;
-            const float *f = a.lay.nlin > 0 ? a.src_feat + o * a.lay.src_dim : nullptr;
-            for (int k = 0; k < a.lay.d4; ++k) {
-                const int col = a.lay.col[k];
-                if (col == -1) continue;
-                double gk = 0.0;
-                for (int i = 0; i < qm.z; ++i)
-                    gk += a.G[((long long)qm.w + (long long)i * qm.y) * a.lay.d4 + k];
-                if (col >= 0) {
-                    a.dfeat[o * a.lay.src_dim + col] = (float)(a.gF * gk * a.lay.gscale[k]);
-                } else {
-                    int dig[8];
-                    int cc = k - a.lay.sed;
-                    for (int b = a.lay.nlin - 1; b >= 0; --b) {
-                        dig[b] = cc % a.lay.lin_dim[b];
-                        cc /= a.lay.lin_dim[b];
-                    }
-                    for (int b = 0; b < a.lay.nlin; ++b) {
-                        double other = 1.0;
-                        for (int b2 = 0; b2 < a.lay.nlin; ++b2)
-                            if (b2 != b) other *= (double)f[a.lay.lin_src[b2] + dig[b2]];
-                        gl[a.lay.lin_src[b] + dig[b]] += gk * other;
-                    }
-                }
-            }
-            if (a.lay.nlin > 0)
-                for (int b = 0; b < a.lay.nlin; ++b)
-                    for (int j = 0; j < a.lay.lin_dim[b]; ++j) {
-                        const int col = a.lay.lin_src[b] + j;
-                        a.dfeat[o * a.lay.src_dim + col] = (float)(a.gF * gl[col]);
-                    }
-        }
+    if (sd.lsum && wv == 0) {
+        double l = in ? s_v[3 * (kBackQ + 1) + lane] : 0.0;
+        for (int off = 32; off > 0; off >>= 1) l += __shfl_xor(l, off);
+        if (lane == 0) sd.lsum[blockIdx.x] = l;
     }
-    if (a.lsum) {
-        // (fixed order: grid-stride queries per thread, then this tree)
-        __shared__ double sh[256];
-        sh[threadIdx.x] = lacc;
-        __syncthreads();
-        for (int s = 128; s > 0; s >>= 1) {
-            if (threadIdx.x < s) sh[threadIdx.x] += sh[threadIdx.x + s];
-            __syncthreads();
+    const int nq = (int)min((long long)kBackQ, sd.n - p0);
+    if (sd.dxyz && threadIdx.x < 3 * nq) {
+        const int q = threadIdx.x / 3, k = threadIdx.x % 3;
+        const double d0 = s_v[q], d1 = s_v[kBackQ + 1 + q], d2 = s_v[2 * (kBackQ + 1) + q];
+        sd.dxyz[3LL * sd.qperm[p0 + q] + k] = (float)(f * (P[k] * d0 + P[4 + k] * d1 + P[8 + k] * d2));
+    }
+    if (!sd.dfeat) return;
+    const double *G = s_v + 4 * (kBackQ + 1);
+    for (int i = threadIdx.x; i < nq * d4; i += 256) {
+        const int q = i / d4, k = i - q * d4, col = a.lay.col[k];
+        if (col >= 0)
+            sd.dfeat[(long long)sd.qperm[p0 + q] * a.lay.src_dim + col] =
+                (float)(a.gF * G[k * (kBackQ + 1) + q] * a.lay.gscale[k]);
+    }
+    if (a.lay.nlin > 0 && threadIdx.x < nq) {
+        // folded LIN blocks: the gradient of a tensor-product column c
+        // reaches u_b[digit_b(c)] times the other blocks' factors of c
+        const int q = threadIdx.x;
+        const long long o = sd.qperm[p0 + q];
+        const float *u = sd.src_feat + o * a.lay.src_dim;
+        double gl[64];
+        for (int k = 0; k < 64; ++k) gl[k] = 0.0;
+        for (int k = 0; k < d4; ++k) {
+            if (a.lay.col[k] != -2) continue;
+            const double gk = G[k * (kBackQ + 1) + q];
+            int dig[8];
+            int cc = k - a.lay.sed;
+            for (int b = a.lay.nlin - 1; b >= 0; --b) {
+                dig[b] = cc % a.lay.lin_dim[b];
+                cc /= a.lay.lin_dim[b];
+            }
+            for (int b = 0; b < a.lay.nlin; ++b) {
+                double other = 1.0;
+                for (int b2 = 0; b2 < a.lay.nlin; ++b2)
+                    if (b2 != b) other *= (double)u[a.lay.lin_src[b2] + dig[b2]];
+                gl[a.lay.lin_src[b] + dig[b]] += gk * other;
+            }
         }
-        if (threadIdx.x == 0) a.lsum[blockIdx.x] = sh[0];
+        for (int b = 0; b < a.lay.nlin; ++b)
+            for (int j = 0; j < a.lay.lin_dim[b]; ++j) {
+                const int col = a.lay.lin_src[b] + j;
+                sd.dfeat[o * a.lay.src_dim + col] = (float)(a.gF * gl[col]);
+            }
     }
 }
 
-int backward_blocks(long long n)
-{
-    const long long nb = (n + 255) / 256;
-    return (int)(nb < 1 ? 1 : (nb > 4096 ? 4096 : nb));
-}
+int backward_blocks(long long n) { return (int)((n + kBackQ - 1) / kBackQ); }
 
 void launch_backward_finish(const BackwardArgs &a, hipStream_t s)
 {
-    hipLaunchKernelGGL(backward_finish, dim3(backward_blocks(a.n)), dim3(256), 0, s, a);
+    int nb = 1;
+    for (int k = 0; k < a.nsides; ++k) nb = std::max(nb, backward_blocks(a.side[k].n));
+    const size_t lds = sizeof(double) * (4 + a.lay.d4) * (kBackQ + 1);
+    hipLaunchKernelGGL(backward_finish, dim3(nb, a.nsides), dim3(256), lds, s, a);
 }
 
 __global__ __launch_bounds__(256) void sum_doubles(const double *in, long long n, double *out)
