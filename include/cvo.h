@@ -186,7 +186,11 @@ typedef struct {
                             * Padded feature rows of more than 8 floats: >= 500: 32, 0.5, 0.5;
                             * >= 200: 16, 0.5, 1.0; fewer: 16, 1.0, 1.0.  Rows of at most 8 floats:
                             * >= 100: 32, 0.5, 1.0; fewer: 16, 1.0, 1.5.  Not yet measured: the fields
-                            * above.  One-shot calls always use the fields above. */
+                            * above.  One-shot calls, and a registration's first view, use the
+                            * fields above too -- except that while adaptive is 1 and none of
+                            * cluster_max, cell_factor, cluster_factor and cluster_rule has been
+                            * changed by cvo_set_tuning or chosen by cvo_autotune they use chunk
+                            * clusters 16, 0.5, 1.0 (cvo_evaluate_noalloc always the fields). */
 } cvo_tuning;
 
 /* Per-handle timing of the dominant kernel, measured with HIP events on the

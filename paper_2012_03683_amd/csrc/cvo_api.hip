@@ -94,6 +94,7 @@ struct cvo_context {
     void *pinned = nullptr;
     size_t pinned_cap = 0;
     cvo_tuning tuning{16, 1.0, 0.5, 0.6, 16, 512, CVO_CLUSTER_OCTREE, 1};
+    bool shape_set = false;  // a shape field of `tuning` has been set or tuned
     bool profiling = false;
     cvo_timing timing{0, 0.0, 0, 0, 0, 0, 0, 0};
     std::vector<hipEvent_t> ev_free;
@@ -476,8 +477,18 @@ struct ViewShape {
     }
 };
 
+// The shape of one-shot calls and of a registration's first view.  Until a
+// shape field has been set or tuned it is 16-point chunks, half-radius cells
+// and clusters up to one radius wide: within 12% of the best of 36 shapes at
+// every density measured, where the fields' own defaults are up to 2x off
+// (pair pass, us, this shape / the fields' defaults / the best: stereo 30,000
+// at ell 0.95 190 / 340 / 169, 0.5 91 / 137 / 84, 0.25 44 / 58 / 44, 0.1
+// 31 / 31 / 29; RGB-D 40,000 at 0.1 83 / 143 / 81, 0.05 42 / 55 / 42).  The
+// allocation-free entry point keeps the fields: finer cells would take more of
+// its fixed scratch.
 ViewShape fixed_shape(const cvo_context *ctx)
 {
+    if (ctx->tuning.adaptive && !ctx->shape_set && !ctx->fixed.on) return ViewShape{16, 0.5, 1.0, CVO_CLUSTER_CHUNKS};
     return ViewShape{ctx->tuning.cluster_max, ctx->tuning.cell_factor, ctx->tuning.cluster_factor,
                      ctx->tuning.cluster_rule};
 }
@@ -1581,6 +1592,10 @@ cvo_status cvo_set_tuning(cvo_handle h, const cvo_tuning *in)
         require(in->adaptive == 0 || in->adaptive == 1, "adaptive must be 0 or 1");
         require(in->cluster_rule == CVO_CLUSTER_OCTREE || in->cluster_rule == CVO_CLUSTER_CHUNKS,
                 "cluster_rule must be CVO_CLUSTER_OCTREE or CVO_CLUSTER_CHUNKS");
+        const cvo_tuning &t = h->tuning;
+        if (in->cluster_max != t.cluster_max || in->cell_factor != t.cell_factor ||
+            in->cluster_factor != t.cluster_factor || in->cluster_rule != t.cluster_rule)
+            h->shape_set = true;
         h->tuning = *in;
     });
 }
@@ -1622,10 +1637,13 @@ cvo_status cvo_autotune(cvo_handle h, const cvo_cloud *X, const cvo_cloud *Z, co
             h->tuning.cell_factor = t.cell_factor;
             h->tuning.cluster_factor = t.cluster_factor;
             h->tuning.cluster_rule = t.cluster_rule;
+            h->shape_set = true;
             if (chosen) *chosen = h->tuning;
             return;
         }
         const cvo_tuning base = h->tuning;
+        const bool base_set = h->shape_set;
+        h->shape_set = true;  // every build below uses the shape it sets
         const bool prof = h->profiling;
         const cvo_timing saved = h->timing;
         h->profiling = false;
@@ -1683,6 +1701,7 @@ cvo_status cvo_autotune(cvo_handle h, const cvo_cloud *X, const cvo_cloud *Z, co
                         }
         } catch (...) {
             h->tuning = base;
+            h->shape_set = base_set;
             h->profiling = prof;
             h->timing = saved;
             throw;
