@@ -283,7 +283,9 @@ cvo_status cvo_evaluate_noalloc(cvo_handle h, const cvo_cloud *X, const cvo_clou
 /* Cosine of the angle between f_X and the moved f_Z (eq. (9), Sec. III-C):
  * cos_theta = F(X, Z; T) / (||f_X|| ||f_Z||), where ||f_X||^2 = F(X, X; I) and
  * ||f_Z||^2 = F(Z, Z; I) are the self inner products with the same kernels,
- * lengthscale and cutoff.  Three pair passes on the handle's stream.
+ * lengthscale and cutoff.  The three sums are evaluated together, as three
+ * pairs of one pair pass on the handle's stream (one after another for clouds
+ * of more than 4 million points).
  * sums, if non-NULL, receives {F(X,Z;T), F(X,X;I), F(Z,Z;I)} (host memory).
  * cos_theta is 0 when a squared norm is not positive (an empty cloud).
  * Errors as cvo_inner_product. */

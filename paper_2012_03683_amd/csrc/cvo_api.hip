@@ -922,34 +922,62 @@ void check_align_params(const cvo_align_params *ap)
     require(ap->reserved == 0, "reserved must be 0");
 }
 
-// single forward evaluation
-void evaluate_one(cvo_context *ctx, const cvo_cloud *X, const cvo_cloud *Z, const cvo_feature_spec *spec,
-                  const cvo_kernel_params *kp, const double *T, PairState *out, bool ellobj = false)
+// One forward evaluation of a pair of clouds at a pose.
+struct Evaluation {
+    const cvo_cloud *X, *Z;
+    const double *T;
+    PairState out;
+};
+
+// Forward evaluations with the same spec and kernels, in one build, one pair
+// pass and one reduction.  A pair with an empty cloud keeps its initial state
+// (all sums zero).
+void evaluate_all(cvo_context *ctx, std::vector<Evaluation> &ev, const cvo_feature_spec *spec,
+                  const cvo_kernel_params *kp, bool ellobj = false)
 {
     check_spec(spec);
     const int D = spec_dim(spec);
-    check_cloud(X, D, "X");
-    check_cloud(Z, D, "Z");
-    check_kp(kp);
-    check_pose(T);
-    PairState s0 = init_state(T, kp->ell);
-    if (X->n == 0 || Z->n == 0) {
-        *out = s0;
-        return;
+    for (auto &e : ev) {
+        check_cloud(e.X, D, "X");
+        check_cloud(e.Z, D, "Z");
     }
+    check_kp(kp);
+    std::vector<CloudPtrs> xs, zs;
+    std::vector<PairState> st;
+    std::vector<AlignConst> ac;
+    for (auto &e : ev) {
+        check_pose(e.T);
+        e.out = init_state(e.T, kp->ell);
+        if (e.X->n == 0 || e.Z->n == 0) continue;
+        xs.push_back(to_ptrs(e.X));
+        zs.push_back(to_ptrs(e.Z));
+        st.push_back(e.out);
+        ac.push_back(const_for(nullptr, e.X->n, e.Z->n));
+    }
+    if (xs.empty()) return;
     Problem p;
     p.kappa = kp->kappa;
     p.lay = make_layout(spec, kp->sigma);
     p.sig2 = p.lay.sig2;
     p.ellobj = ellobj ? 1 : 0;
-    AlignConst ac = const_for(nullptr, X->n, Z->n);
-    setup_problem(ctx, p, {to_ptrs(X)}, {to_ptrs(Z)}, {s0}, {ac});
+    setup_problem(ctx, p, xs, zs, st, ac);
     enqueue_iteration(ctx, p, 0, nullptr, 0, ctx->profiling);
-    ctx->download(out, p.d_state, sizeof(PairState));
+    ctx->download(st.data(), p.d_state, sizeof(PairState) * st.size());
+    size_t k = 0;
+    for (auto &e : ev)
+        if (e.X->n != 0 && e.Z->n != 0) e.out = st[k++];
     if (ctx->profiling) {
         ctx->harvest_events();
-        ctx->timing.pair_count += (long long)out->n_pairs;
+        for (auto &s : st) ctx->timing.pair_count += (long long)s.n_pairs;
     }
+}
+
+void evaluate_one(cvo_context *ctx, const cvo_cloud *X, const cvo_cloud *Z, const cvo_feature_spec *spec,
+                  const cvo_kernel_params *kp, const double *T, PairState *out, bool ellobj = false)
+{
+    std::vector<Evaluation> ev{{X, Z, T, PairState{}}};
+    evaluate_all(ctx, ev, spec, kp, ellobj);
+    *out = ev[0].out;
 }
 
 cvo_status fail(cvo_context *ctx, const CvoError &e)
@@ -1280,12 +1308,17 @@ cvo_status cvo_cosine(cvo_handle h, const cvo_cloud *X, const cvo_cloud *Z, cons
     return guarded(h, [&] {
         require(cos_theta != nullptr, "output is NULL");
         static const double I[12] = {1.0, 0.0, 0.0, 0.0, 0.0, 1.0, 0.0, 0.0, 0.0, 0.0, 1.0, 0.0};
-        PairState sxz, sxx, szz;
-        evaluate_one(h, X, Z, spec, kp, T, &sxz);
-        evaluate_one(h, X, X, spec, kp, I, &sxx);
-        evaluate_one(h, Z, Z, spec, kp, I, &szz);
-        const double fxz = (X->n > 0 && Z->n > 0) ? sxz.F : 0.0;
-        const double fxx = X->n > 0 ? sxx.F : 0.0, fzz = Z->n > 0 ? szz.F : 0.0;
+        // The three sums are three pairs of one evaluation (40,000 RGB-D points:
+        // 629 us one by one, 416 us together); one by one where the views of
+        // three pairs would be gigabytes and launches no longer count.
+        std::vector<Evaluation> ev{{X, Z, T, PairState{}}, {X, X, I, PairState{}}, {Z, Z, I, PairState{}}};
+        constexpr int64_t kTogether = int64_t(1) << 22;
+        if (X && Z && X->n <= kTogether && Z->n <= kTogether) {
+            evaluate_all(h, ev, spec, kp);
+        } else {
+            for (auto &e : ev) evaluate_one(h, e.X, e.Z, spec, kp, e.T, &e.out);
+        }
+        const double fxz = ev[0].out.F, fxx = ev[1].out.F, fzz = ev[2].out.F;
         // sqrt of the product: when the three sums coincide (the moved f_Z is
         // f_X) the quotient is exactly 1, as sqrt(fl(F * F)) == F
         *cos_theta = (fxx > 0.0 && fzz > 0.0) ? fxz / std::sqrt(fxx * fzz) : 0.0;
