@@ -674,7 +674,7 @@ void build_pairs(cvo_context *ctx, Views &v, const std::vector<PairSpec> &pairs,
 
 // ------------------------------------------------------------------ pair pass + reduce
 struct Moments {
-    double *W, *D, *B;
+    double *WD, *B;
     float *S;
     int *cnt;
 };
@@ -686,8 +686,7 @@ Moments moments(cvo_context *ctx, const std::string &pre, long long n, int d4, b
     if (backward) {
         m.B = ctx->get_t<double>(pre + ".B", n * (4 + d4));
     } else {
-        m.W = ctx->get_t<double>(pre + ".W", n);
-        m.D = ctx->get_t<double>(pre + ".D", 3 * n);
+        m.WD = ctx->get_t<double>(pre + ".WD", 4 * n);
         m.cnt = ctx->get_t<int>(pre + ".cnt", n);
         m.S = ctx->get_t<float>(pre + ".S", 6 * n);
     }
@@ -707,8 +706,7 @@ PairPassArgs pass_args(const Views &v, const PairState *st, float sig2, double k
     a.state = st;
     a.sig2 = sig2;
     a.kappa = kappa;
-    a.oW = m.W;
-    a.oD = m.D;
+    a.oWD = m.WD;
     a.oS = m.S;
     a.oCnt = m.cnt;
     a.oB = m.B;
@@ -817,8 +815,7 @@ void iteration_args(const Problem &p, int mode, double *trace, long long trace_r
     r.qpts = p.views.a.pts[1];
     r.cdesc = p.views.d_desc;
     r.map = SlotMap{p.views.a.qmap};
-    r.W = p.mom.W;
-    r.D = p.mom.D;
+    r.WD = p.mom.WD;
     r.S = p.mom.S;
     r.cnt = p.mom.cnt;
     r.state = p.d_state;

@@ -51,10 +51,11 @@ __device__ __forceinline__ void in_sgpr(long long v) { asm volatile("" ::"s"(v))
 // Per-pair registration state, resident on the device for the whole ascent.
 struct alignas(16) PairState {
     double T[12];        // current pose [R|t], maps the Z frame into the X frame
-    double Tinv[12];     // inverse pose (used by the source-side backward pass)
+    double Tinv[12];     // inverse of the pose the state starts with (for the source-side backward
+                         // pass; an ascent does not update it)
     double ell;          // current lengthscale
     double i_prev;       // indicator at the previous iteration (NaN: none)
-    double F, i_theta, curv, tau, gnorm, r_max, dF_dell;
+    double F, i_theta, curv, r_max, dF_dell;
     double grad[6];
     double n_pairs;      // |P| of the last evaluation (exact integer in a double)
     double total_pairs;  // sum of |P| over the registration
@@ -209,14 +210,14 @@ struct PairPassArgs {
     const PairState *state;
     float sig2;
     double kappa;           // +inf: no cutoff
-    // outputs, indexed by piece slot + position of the query in its cluster
-    double *oW;
-    double *oD;     // 3 per query
-    float *oS;      // 6 per query (forward mode)
-    int *oCnt;      // (forward mode)
-    // backward mode: D (3 values), sum w s', then d4 feature gradients.  A piece
-    // of a cluster of n queries owns n slots from its first slot f: value v of
-    // query t is at f (4 + d4) + v n + t
+    // Outputs.  A piece of a cluster of n queries owns n slots from its first
+    // slot f, and in each array a block of (values per slot) n entries in which
+    // the values follow one another over the queries: value v of query t is at
+    // (values per slot) f + v n + t.
+    double *oWD;    // forward: W, Dx, Dy, Dz
+    float *oS;      // forward: S00, S01, S02, S11, S12, S22
+    int *oCnt;      // forward: in-cutoff pairs
+    // backward: D (3 values), sum w s', then d4 feature gradients
     double *oB;
 };
 

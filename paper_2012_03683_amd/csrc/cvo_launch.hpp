@@ -57,8 +57,8 @@ bool launch_pair_pass(const PairPassArgs &a, const FeatLayout &lay, int mode, hi
 
 // Where a query's partial moments live: qmap[j] = (t, n, np, s0) for query j
 // at position t of a cluster of n queries cut into np pieces; the cluster's
-// pieces own consecutive blocks of n output slots, so the query's partial of
-// piece k is at slot s0 + k n.  Partials are combined in piece order.
+// pieces own consecutive blocks of n output slots from s0 - t on (see
+// PairPassArgs for the values' places).  Partials are combined in piece order.
 struct SlotMap {
     const int4 *qmap;
 };
@@ -67,8 +67,7 @@ struct ReduceArgs {
     const float4 *qpts;
     const ClusterDesc *cdesc;  // per pair: query points [pt_base, pt_base + n)
     SlotMap map;
-    const double *W;
-    const double *D;
+    const double *WD;          // per-piece partial moments (PairPassArgs.oWD, oS, oCnt)
     const float *S;
     const int *cnt;
     PairState *state;

@@ -418,20 +418,26 @@ void pair_pass_kernel(const PairPassArgs a)
             }
         }
         if (qs == 0 && active) {
-            const long long o = (long long)pc.w + t;
-            const double sg = (double)sig2;  // every output is linear in the kernel weights
+            // every output is linear in the kernel weights; written value by
+            // value over the cluster's queries
+            const double sg = (double)sig2;
+            const long long f = pc.w;
             if (MODE == 0) {
-                a.oW[o] = sg * W;
-                a.oD[3 * o + 0] = sg * Dx;
-                a.oD[3 * o + 1] = sg * Dy;
-                a.oD[3 * o + 2] = sg * Dz;
-                a.oCnt[o] = cnt;
-                float *S = a.oS + 6 * o;
-                S[0] = sig2 * S00; S[1] = sig2 * S01; S[2] = sig2 * S02;
-                S[3] = sig2 * S11; S[4] = sig2 * S12; S[5] = sig2 * S22;
+                double *B = a.oWD + 4 * f + t;
+                B[0] = sg * W;
+                B[n] = sg * Dx;
+                B[2 * n] = sg * Dy;
+                B[3 * n] = sg * Dz;
+                float *S = a.oS + 6 * f + t;
+                S[0] = sig2 * S00;
+                S[n] = sig2 * S01;
+                S[2 * n] = sig2 * S02;
+                S[3 * n] = sig2 * S11;
+                S[4 * n] = sig2 * S12;
+                S[5 * n] = sig2 * S22;
+                a.oCnt[f + t] = cnt;
             } else {
-                // value by value over the cluster's queries
-                double *B = a.oB + (long long)pc.w * (4 + D4) + t;
+                double *B = a.oB + f * (4 + D4) + t;
                 B[0] = sg * Dx;
                 B[n] = sg * Dy;
                 B[2 * n] = sg * Dz;

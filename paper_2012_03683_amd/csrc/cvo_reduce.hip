@@ -34,64 +34,54 @@ enum {
     R_ZS = 31, R_ZZ = 34, R_LOGW = 40, R_RSUM = 41, R_ZP = 42, R_END = 48
 };
 
-// Solve G d = g for a symmetric positive definite 6x6 G by Cholesky
-// (G = L L^T), fully unrolled so everything stays in registers; false if a
-// pivot is not positive.  Each pivot is inverted once and the solves
-// multiply by the inverse (6 divisions on the serial chain instead of 27).
-__device__ bool chol_solve6(const double G[36], const double g[6], double d[6])
+// Solve G d = g for the kinetic-energy metric of the moving cloud,
+// G = [[(tr S + mu) I - S, C], [C^T, I]] with c = mean z', C = [c]_x,
+// S = mean z' z'^T and mu = 1e-6 (tr S + 1e-12).  The lower right block is the
+// identity, so eliminating v leaves a 3x3 system with M = (tr K + mu) I - K in
+// the covariance K = S - c c^T, solved by cofactors: one division on the
+// serial chain where a 6x6 Cholesky has six square roots and six divisions.
+// False if G (equivalently M) is not positive definite.
+__device__ __forceinline__ bool metric_solve(const double *tot, double im, const double g[6], double d[6])
 {
-    double L[6][6], inv[6];
-#pragma unroll
-    for (int i = 0; i < 6; ++i) {
-#pragma unroll
-        for (int j = 0; j <= i; ++j) {
-            double s = G[6 * i + j];
-#pragma unroll
-            for (int k = 0; k < j; ++k) s -= L[i][k] * L[j][k];
-            if (i == j) {
-                if (!(s > 0.0)) return false;
-                L[i][i] = sqrt(s);
-                inv[i] = 1.0 / L[i][i];
-            } else {
-                L[i][j] = s * inv[j];
-            }
-        }
-    }
-    double y[6];
-#pragma unroll
-    for (int i = 0; i < 6; ++i) {
-        double s = g[i];
-#pragma unroll
-        for (int k = 0; k < i; ++k) s -= L[i][k] * y[k];
-        y[i] = s * inv[i];
-    }
-#pragma unroll
-    for (int i = 5; i >= 0; --i) {
-        double s = y[i];
-#pragma unroll
-        for (int k = i + 1; k < 6; ++k) s -= L[k][i] * d[k];
-        d[i] = s * inv[i];
-    }
+    const double c0 = tot[R_ZS] * im, c1 = tot[R_ZS + 1] * im, c2 = tot[R_ZS + 2] * im;
+    const double s00 = tot[R_ZZ + 0] * im, s11 = tot[R_ZZ + 3] * im, s22 = tot[R_ZZ + 5] * im;
+    const double mu = 1e-6 * (s00 + s11 + s22 + 1e-12);
+    const double k00 = s00 - c0 * c0, k11 = s11 - c1 * c1, k22 = s22 - c2 * c2;
+    const double m00 = k11 + k22 + mu, m11 = k00 + k22 + mu, m22 = k00 + k11 + mu;
+    const double m01 = c0 * c1 - tot[R_ZZ + 1] * im;
+    const double m02 = c0 * c2 - tot[R_ZZ + 2] * im;
+    const double m12 = c1 * c2 - tot[R_ZZ + 4] * im;
+    const double a00 = m11 * m22 - m12 * m12, a01 = m02 * m12 - m01 * m22, a02 = m01 * m12 - m02 * m11;
+    const double a11 = m00 * m22 - m02 * m02, a12 = m01 * m02 - m00 * m12, a22 = m00 * m11 - m01 * m01;
+    const double det = m00 * a00 + m01 * a01 + m02 * a02;
+    if (!(m00 > 0.0 && a22 > 0.0 && det > 0.0)) return false;
+    // r = g_w - c x g_v;  d_w = M^-1 r;  d_v = g_v + c x d_w
+    const double r0 = g[0] - (c1 * g[5] - c2 * g[4]);
+    const double r1 = g[1] - (c2 * g[3] - c0 * g[5]);
+    const double r2 = g[2] - (c0 * g[4] - c1 * g[3]);
+    const double id = 1.0 / det;
+    d[0] = (a00 * r0 + a01 * r1 + a02 * r2) * id;
+    d[1] = (a01 * r0 + a11 * r1 + a12 * r2) * id;
+    d[2] = (a02 * r0 + a12 * r1 + a22 * r2) * id;
+    d[3] = g[3] + (c1 * d[2] - c2 * d[1]);
+    d[4] = g[4] + (c2 * d[0] - c0 * d[2]);
+    d[5] = g[5] + (c0 * d[1] - c1 * d[0]);
     return true;
 }
 
 // xi^T H xi for the reduced 6x6 curvature matrix
-__device__ double quad_form(const double *tot, const double xi[6])
+__device__ __forceinline__ double quad_form(const double *tot, const double xi[6])
 {
-    const double Hww[3][3] = {{tot[R_HWW + 0], tot[R_HWW + 1], tot[R_HWW + 2]},
-                              {tot[R_HWW + 1], tot[R_HWW + 3], tot[R_HWW + 4]},
-                              {tot[R_HWW + 2], tot[R_HWW + 4], tot[R_HWW + 5]}};
-    const double Hvv[3][3] = {{tot[R_HVV + 0], tot[R_HVV + 1], tot[R_HVV + 2]},
-                              {tot[R_HVV + 1], tot[R_HVV + 3], tot[R_HVV + 4]},
-                              {tot[R_HVV + 2], tot[R_HVV + 4], tot[R_HVV + 5]}};
-    double q = 0.0;
-#pragma unroll
-    for (int r = 0; r < 3; ++r)
-#pragma unroll
-        for (int k = 0; k < 3; ++k)
-            q += xi[r] * Hww[r][k] * xi[k] + 2.0 * xi[r] * tot[R_HWV + 3 * r + k] * xi[3 + k] +
-                 xi[3 + r] * Hvv[r][k] * xi[3 + k];
-    return q;
+    const double *w = tot + R_HWW, *x = tot + R_HWV, *v = tot + R_HVV;
+    const double a = xi[0], b = xi[1], c = xi[2], p = xi[3], q = xi[4], r = xi[5];
+    // rows of H_ww w + 2 H_wv v and of H_vv v
+    const double h0 = w[0] * a + w[1] * b + w[2] * c + 2.0 * (x[0] * p + x[1] * q + x[2] * r);
+    const double h1 = w[1] * a + w[3] * b + w[4] * c + 2.0 * (x[3] * p + x[4] * q + x[5] * r);
+    const double h2 = w[2] * a + w[4] * b + w[5] * c + 2.0 * (x[6] * p + x[7] * q + x[8] * r);
+    const double h3 = v[0] * p + v[1] * q + v[2] * r;
+    const double h4 = v[1] * p + v[3] * q + v[4] * r;
+    const double h5 = v[2] * p + v[4] * q + v[5] * r;
+    return (a * h0 + b * h1 + c * h2) + (p * h3 + q * h4 + r * h5);
 }
 
 // SE(3) exponential of xi = (omega, v): R = I + a W + b W^2, V = I + b W + c W^2,
@@ -102,15 +92,15 @@ __device__ void exp_se3(const double xi[6], double E[12])
 {
     const double w0 = xi[0], w1 = xi[1], w2 = xi[2];
     const double th2 = w0 * w0 + w1 * w1 + w2 * w2;
-    const double th = sqrt(th2);
     double ca, cb, cc;
-    if (th < 1e-2) {
+    if (th2 < 1e-4) {
         const double th4 = th2 * th2, th6 = th4 * th2;
         // (reciprocal factorials as constants: multiplications, not divisions)
         ca = 1.0 - th2 * (1.0 / 6.0) + th4 * (1.0 / 120.0) - th6 * (1.0 / 5040.0);
         cb = 0.5 - th2 * (1.0 / 24.0) + th4 * (1.0 / 720.0) - th6 * (1.0 / 40320.0);
         cc = 1.0 / 6.0 - th2 * (1.0 / 120.0) + th4 * (1.0 / 5040.0) - th6 * (1.0 / 362880.0);
     } else {
+        const double th = sqrt(th2);
         const double sh = sin(0.5 * th);
         ca = sin(th) / th;
         cb = 2.0 * sh * sh / th2;
@@ -135,101 +125,74 @@ __device__ void exp_se3(const double xi[6], double E[12])
     for (int r = 0; r < 3; ++r) E[4 * r + 3] = V[r][0] * xi[3] + V[r][1] * xi[4] + V[r][2] * xi[5];
 }
 
-__device__ void compose_left(const double E[12], double T[12])
+// The gradient of the reduced sums.
+__device__ __forceinline__ void gradient(const double *tot, double il2, double g[6])
 {
-    double O[12];
-#pragma unroll
-    for (int r = 0; r < 3; ++r) {
-#pragma unroll
-        for (int k = 0; k < 3; ++k) O[4 * r + k] = E[4 * r] * T[k] + E[4 * r + 1] * T[4 + k] + E[4 * r + 2] * T[8 + k];
-        O[4 * r + 3] = E[4 * r] * T[3] + E[4 * r + 1] * T[7] + E[4 * r + 2] * T[11] + E[4 * r + 3];
-    }
-#pragma unroll
-    for (int k = 0; k < 12; ++k) T[k] = O[k];
-}
-
-__device__ void invert_pose(const double T[12], double Ti[12])
-{
-#pragma unroll
-    for (int r = 0; r < 3; ++r) {
-#pragma unroll
-        for (int k = 0; k < 3; ++k) Ti[4 * r + k] = T[4 * k + r];
-        Ti[4 * r + 3] = -(T[r] * T[3] + T[4 + r] * T[7] + T[8 + r] * T[11]);
-    }
-}
-
-// Finish one pair: publish the evaluation, and in step mode take the step.
-// Works on register copies of the state and constants (one batch of loads,
-// one batch of stores) rather than on global memory field by field.
-__device__ __forceinline__ void finalize_local(PairState &st, const AlignConst &ac, const double *tot,
-                                               double *trace, long long trace_rows, int mode)
-{
-    const double ell = st.ell;
-    const double il1 = 1.0 / ell;
-    const double il2 = il1 * il1;
-    double g[6];
 #pragma unroll
     for (int k = 0; k < 3; ++k) {
         g[k] = tot[R_OM + k] * il2;
         g[3 + k] = tot[R_V + k] * il2;
     }
-    const double curv = quad_form(tot, g);
+}
+
+// Publish an evaluation of one pair.
+__device__ void publish_evaluation(PairState *st, const AlignConst &ac, const double *tot)
+{
+    const double ell = st->ell;
+    const double il1 = 1.0 / ell;
+    const double il2 = il1 * il1;
+    double g[6];
+    gradient(tot, il2, g);
+    const double F = tot[R_F];
+    st->F = F;
+    st->i_theta = (ac.sqrt_nm > 0.0) ? F / ac.sqrt_nm : 0.0;
+    st->curv = quad_form(tot, g);
+    st->r_max = tot[R_RMAX];
+    st->dF_dell = tot[R_TRS] * il2 * il1;
+    st->n_pairs = tot[R_N];
+#pragma unroll
+    for (int k = 0; k < 6; ++k) st->grad[k] = g[k];
+    // lengthscale objective J = sum log W_j - 3 |Z+| log ell (all zero
+    // unless its sums were reduced)
+    const double mp = tot[R_ZP];
+    st->J = mp > 0.0 ? tot[R_LOGW] - 3.0 * mp * log(ell) : 0.0;
+    st->dJ_dell = mp > 0.0 ? tot[R_RSUM] * il2 * il1 - 3.0 * mp * il1 : 0.0;
+    st->ell_ml = mp > 0.0 ? sqrt(tot[R_RSUM] / (3.0 * mp)) : 0.0;
+    st->zplus = mp;
+}
+
+// What an ascent step reads of the pair's state.
+struct StepIn {
+    double T[12], ell, i_prev, total_pairs, rc_build;
+    long long it;
+    int cls_built;
+};
+
+// One ascent step of one pair (same decision sequence as the definition it
+// follows): reads s, writes the fields of *st that later iterations and the
+// host read.  One thread runs it, and its time is the number of instructions
+// on that thread, so it computes nothing else: no evaluation fields, no
+// inverse pose (only the backward uses one).
+__device__ __forceinline__ void ascent_step(PairState *st, const StepIn &s, const AlignConst &ac, const double *tot,
+                                            double *trace, long long trace_rows)
+{
+    const double ell = s.ell;
+    const double il1 = 1.0 / ell;
+    double g[6];
+    gradient(tot, il1 * il1, g);
     const double F = tot[R_F];
     const double np = tot[R_N];
     const double ind = (ac.sqrt_nm > 0.0) ? F / ac.sqrt_nm : 0.0;
-    st.F = F;
-    st.i_theta = ind;
-    st.curv = curv;
-    st.r_max = tot[R_RMAX];
-    st.dF_dell = tot[R_TRS] * il2 * il1;
-    st.n_pairs = np;
-    {
-        // lengthscale objective J = sum log W_j - 3 |Z+| log ell (all zero
-        // unless its sums were reduced)
-        const double mp = tot[R_ZP];
-        st.J = 0.0;
-        st.dJ_dell = 0.0;
-        st.ell_ml = 0.0;
-        if (mp > 0.0) {
-            st.J = tot[R_LOGW] - 3.0 * mp * log(ell);
-            st.dJ_dell = tot[R_RSUM] * il2 * il1 - 3.0 * mp * il1;
-            st.ell_ml = sqrt(tot[R_RSUM] / (3.0 * mp));
-        }
-        st.zplus = mp;
-    }
-#pragma unroll
-    for (int k = 0; k < 6; ++k) st.grad[k] = g[k];
+    st->F = F;
+    st->i_theta = ind;
+    st->n_pairs = np;
     const double gn2 = g[0] * g[0] + g[1] * g[1] + g[2] * g[2] + g[3] * g[3] + g[4] * g[4] + g[5] * g[5];
-    st.gnorm = sqrt(gn2);
-    if (mode == 0) return;
-
-    // ---- ascent step (same decision sequence as the definition it follows)
-    if (np == 0.0) { st.status = ST_NO_OVERLAP; st.done = 1; return; }
-    if (gn2 == 0.0) { st.status = ST_STATIONARY; st.done = 1; return; }
-    // direction: the Riemannian gradient G^-1 g.  Kinetic-energy metric of
-    // the moving cloud: G = [[tr(S) I - S + mu I, [c]_x], [[c]_x^T, I]] with
-    // c = mean z', S = mean z' z'^T, mu = 1e-6 (tr S + 1e-12).
+    if (np == 0.0) { st->status = ST_NO_OVERLAP; st->done = 1; return; }
+    if (gn2 == 0.0) { st->status = ST_STATIONARY; st->done = 1; return; }
+    // direction: the Riemannian gradient G^-1 g
     double d[6];
     if (ac.metric == 0) {
-        const double im = ac.inv_m;
-        const double c[3] = {tot[R_ZS] * im, tot[R_ZS + 1] * im, tot[R_ZS + 2] * im};
-        const double S[3][3] = {{tot[R_ZZ + 0] * im, tot[R_ZZ + 1] * im, tot[R_ZZ + 2] * im},
-                                {tot[R_ZZ + 1] * im, tot[R_ZZ + 3] * im, tot[R_ZZ + 4] * im},
-                                {tot[R_ZZ + 2] * im, tot[R_ZZ + 4] * im, tot[R_ZZ + 5] * im}};
-        const double trs = S[0][0] + S[1][1] + S[2][2];
-        const double mu = 1e-6 * (trs + 1e-12);
-        const double Cx[3][3] = {{0.0, -c[2], c[1]}, {c[2], 0.0, -c[0]}, {-c[1], c[0], 0.0}};
-        double G[36];
-#pragma unroll
-        for (int r = 0; r < 3; ++r)
-#pragma unroll
-            for (int k = 0; k < 3; ++k) {
-                G[6 * r + k] = (r == k ? trs + mu : 0.0) - S[r][k];
-                G[6 * r + 3 + k] = Cx[r][k];
-                G[6 * (3 + r) + k] = Cx[k][r];
-                G[6 * (3 + r) + 3 + k] = (r == k) ? 1.0 : 0.0;
-            }
-        if (!chol_solve6(G, g, d)) { st.status = ST_STATIONARY; st.done = 1; return; }
+        if (!metric_solve(tot, ac.inv_m, g, d)) { st->status = ST_STATIONARY; st->done = 1; return; }
     } else {
 #pragma unroll
         for (int k = 0; k < 6; ++k) d[k] = g[k];
@@ -245,10 +208,14 @@ __device__ __forceinline__ void finalize_local(PairState &st, const AlignConst &
 #pragma unroll
     for (int k = 0; k < 6; ++k) xi[k] = tau * d[k];
     exp_se3(xi, E);
-    compose_left(E, st.T);
-    invert_pose(st.T, st.Tinv);
-    st.tau = tau;
-    const long long it = st.it;
+#pragma unroll
+    for (int r = 0; r < 3; ++r) {
+#pragma unroll
+        for (int k = 0; k < 3; ++k)
+            st->T[4 * r + k] = E[4 * r] * s.T[k] + E[4 * r + 1] * s.T[4 + k] + E[4 * r + 2] * s.T[8 + k];
+        st->T[4 * r + 3] = E[4 * r] * s.T[3] + E[4 * r + 1] * s.T[7] + E[4 * r + 2] * s.T[11] + E[4 * r + 3];
+    }
+    const long long it = s.it;
     if (trace && it < trace_rows) {
         double *tr = trace + it * kTraceLen;
         tr[0] = (double)it;
@@ -260,63 +227,68 @@ __device__ __forceinline__ void finalize_local(PairState &st, const AlignConst &
         tr[6] = np;
         tr[7] = curv_d;
     }
-    st.it = it + 1;
-    st.total_pairs += np;
+    st->it = it + 1;
+    st->total_pairs = s.total_pairs + np;
+    double next = ell;  // lengthscale of the next iteration
     if (ac.ell_sched) {
         // replay of a given lengthscale sequence: no annealing or convergence decisions
         if (it + 1 >= ac.n_sched) {
-            st.status = ST_MAX_ITER;
-            st.done = 1;
+            st->status = ST_MAX_ITER;
+            st->done = 1;
             return;
         }
-        st.ell = ac.ell_sched[it + 1];
+        next = ac.ell_sched[it + 1];
+        st->ell = next;
     } else if (ac.ell_mode == 1 && !ac.fixed_iters) {
         // adaptive lengthscale: the objective's maximiser at this iteration's
         // (T, ell), clamped to [ell_min, ell_init] and to one factor `decay`
-        double next = ell;
-        if (st.ell_ml > 0.0) {
+        const double mp = tot[R_ZP];
+        const double ml = mp > 0.0 ? sqrt(tot[R_RSUM] / (3.0 * mp)) : 0.0;
+        if (ml > 0.0) {
             double lo = ac.decay * ell, hi = ell / ac.decay;
             if (lo < ac.ell_min) lo = ac.ell_min;
             if (hi > ac.ell_init) hi = ac.ell_init;
-            next = st.ell_ml < lo ? lo : (st.ell_ml > hi ? hi : st.ell_ml);
+            next = ml < lo ? lo : (ml > hi ? hi : ml);
         }
         const bool still = fabs(next - ell) <= ac.ind_rel_tol * ell;
-        st.ell = next;
+        st->ell = next;
         if (still && tau * nw < ac.eps_rot && tau * nv < ac.eps_trans) {
-            st.status = ST_CONVERGED;
-            st.done = 1;
+            st->status = ST_CONVERGED;
+            st->done = 1;
             return;
         }
     } else if (!ac.fixed_iters) {
-        const double ip = st.i_prev;
+        const double ip = s.i_prev;
         if (isfinite(ip) && fabs(ind - ip) <= ac.ind_rel_tol * fabs(ind) && ell > ac.ell_min) {
             const double e2 = ac.decay * ell;
-            st.ell = e2 > ac.ell_min ? e2 : ac.ell_min;
-            st.i_prev = NAN;
+            next = e2 > ac.ell_min ? e2 : ac.ell_min;
+            st->ell = next;
+            st->i_prev = NAN;
         } else {
-            st.i_prev = ind;
+            st->i_prev = ind;
         }
-        if (st.ell == ac.ell_min && tau * nw < ac.eps_rot && tau * nv < ac.eps_trans) {
-            st.status = ST_CONVERGED;
-            st.done = 1;
+        if (next == ac.ell_min && tau * nw < ac.eps_rot && tau * nv < ac.eps_trans) {
+            st->status = ST_CONVERGED;
+            st->done = 1;
             return;
         }
     }
     if (it + 1 >= ac.max_iter) {
-        st.status = ST_MAX_ITER;
-        st.done = 1;
+        st->status = ST_MAX_ITER;
+        st->done = 1;
         return;
     }
     // the views no longer fit: the cutoff shrank past the rebuild ratio, or
     // the pair density fell to a lower class.  Decided from the iterates
     // alone, so where views change does not depend on how many iterations
     // are enqueued between host checks.
-    if (isfinite(ac.kappa) && ac.kappa * st.ell < ac.rebuild_ratio * st.rc_build) st.pause = 1;
-    // (an adaptive lengthscale may also grow: rebuild once the cutoff has
-    // grown by the same ratio)
-    if (isfinite(ac.kappa) && ac.rebuild_ratio < 1.0 && ac.kappa * st.ell * ac.rebuild_ratio > st.rc_build)
-        st.pause = 1;
-    if (ac.adaptive && st.cls_built >= 0 && density_class(np * ac.inv_m, ac.cls_t) < st.cls_built) st.pause = 1;
+    // (An adaptive lengthscale may also grow: rebuild once the cutoff has
+    // grown by the same ratio.)
+    const bool cut = isfinite(ac.kappa);
+    if ((cut && ac.kappa * next < ac.rebuild_ratio * s.rc_build) ||
+        (cut && ac.rebuild_ratio < 1.0 && ac.kappa * next * ac.rebuild_ratio > s.rc_build) ||
+        (ac.adaptive && s.cls_built >= 0 && density_class(np * ac.inv_m, ac.cls_t) < s.cls_built))
+        st->pause = 1;
 }
 
 static_assert(kRedThreads == 256 && R_END == 48 && R_END <= kRedVals, "reduction layout");
@@ -362,26 +334,62 @@ __global__ __launch_bounds__(kRedThreads) void reduce_kernel(const ReduceArgs a)
         acc[R_ZZ + 4] += z[1] * z[2];
         acc[R_ZZ + 5] += z[2] * z[2];
         // the query's partial moments of its cluster's pieces, in piece
-        // order: piece k's is at slot first + k n.  One piece per loop trip:
-        // the other queries' threads keep the memory system busy, and
-        // unrolling the loop with predicated loads (2, 4, ... pieces in
-        // flight) was slower at every density
+        // order: piece k's block starts at slot f0 + k n.  A query's thread
+        // waits on memory most of its time (30,000 queries are 118 blocks),
+        // so the next piece is requested before this one is added, in two
+        // sets of registers: 30,000 queries of about 16 pieces 19.9 -> 15.2 us,
+        // 4 pieces 8.8 -> 8.0 us.  Three or four in flight gain 1 us more in the
+        // first case and lose as much in sparse ones (6.0 -> 7.0 us).
         int nj = 0;
         double Wt = 0.0, D0 = 0.0, D1 = 0.0, D2 = 0.0;
         double S0 = 0.0, S1 = 0.0, S2 = 0.0, S3 = 0.0, S4 = 0.0, S5 = 0.0;
-        for (int k = 0; k < qm.z; ++k) {
-            const long long o = (long long)qm.w + (long long)k * qm.y;
-            nj += a.cnt[o];
-            Wt += a.W[o];
-            D0 += a.D[3 * o + 0];
-            D1 += a.D[3 * o + 1];
-            D2 += a.D[3 * o + 2];
-            S0 += (double)a.S[6 * o + 0];
-            S1 += (double)a.S[6 * o + 1];
-            S2 += (double)a.S[6 * o + 2];
-            S3 += (double)a.S[6 * o + 3];
-            S4 += (double)a.S[6 * o + 4];
-            S5 += (double)a.S[6 * o + 5];
+        const int n = qm.y;
+        const double *wd = a.WD + 4LL * (qm.w - qm.x) + qm.x;
+        const float *sm = a.S + 6LL * (qm.w - qm.x) + qm.x;
+        const int *ct = a.cnt + qm.w;
+        struct Part {
+            double w, dx, dy, dz;
+            float s0, s1, s2, s3, s4, s5;
+            int c;
+        };
+        auto load = [&]() {
+            return Part{wd[0], wd[n], wd[2 * n], wd[3 * n], sm[0], sm[n], sm[2 * n], sm[3 * n], sm[4 * n], sm[5 * n], ct[0]};
+        };
+        auto add = [&](const Part &p) {
+            nj += p.c;
+            Wt += p.w;
+            D0 += p.dx;
+            D1 += p.dy;
+            D2 += p.dz;
+            S0 += (double)p.s0;
+            S1 += (double)p.s1;
+            S2 += (double)p.s2;
+            S3 += (double)p.s3;
+            S4 += (double)p.s4;
+            S5 += (double)p.s5;
+        };
+        int left = qm.z;  // pieces not yet loaded
+        auto step = [&]() {
+            if (--left > 0) {
+                wd += 4 * n;
+                sm += 6 * n;
+                ct += n;
+            }
+        };
+        if (left > 0) {
+            Part p0 = load(), p1;
+            for (;;) {
+                step();
+                p1 = load();  // (past the end: the last piece again, not added)
+                __builtin_amdgcn_sched_barrier(0);
+                add(p0);
+                if (left <= 0) break;
+                step();
+                p0 = load();
+                __builtin_amdgcn_sched_barrier(0);
+                add(p1);
+                if (left <= 0) break;
+            }
         }
         if (nj == 0) return;
         const double Dt[3] = {D0 * isc, D1 * isc, D2 * isc};
@@ -440,7 +448,7 @@ __global__ __launch_bounds__(kRedThreads) void reduce_kernel(const ReduceArgs a)
     // adds the entries s, s + 8, ... of its value, and an 8-lane shuffle tree
     // finishes.  Fixed order throughout.
     constexpr int kChunk = 24, kStripes = 8;
-    __shared__ double red[kChunk][kRedThreads];
+    __shared__ double red[kChunk][kRedThreads + 8];  // (rows 64 bytes apart in the banks)
     const int tid = threadIdx.x;
     double *part = a.partials + (long long)b * a.nblk * kRedVals + blockIdx.x;  // value-major
     {
@@ -477,20 +485,35 @@ __global__ __launch_bounds__(kRedThreads) void reduce_kernel(const ReduceArgs a)
 // finishes the pair.  Fixed order throughout.  A separate launch rather than
 // a last-block ticket: the kernel boundary makes the partials visible to
 // every XCD without a device-scope fence in each block of the first stage.
+template <bool STEP>
 __global__ __launch_bounds__(kRedThreads) void reduce_finish_kernel(const ReduceArgs a)
 {
     const int b = blockIdx.x;
-    PairState *st = a.state + b;
     __shared__ double tot[R_END];
     const int tid = threadIdx.x;
     // thread 0 holds the pair's state and constants in registers from the
     // start, so their loads overlap those of the partials; a skipped pair's
-    // partials are read but not used
-    PairState s;
+    // partials are read but not used.  (Vector loads: the addresses are made
+    // opaque, as this many scalar loads go out in five dependent rounds.)
+    PairState *st = a.state + b;
+    const AlignConst *cp = a.ac + b;
+    asm volatile("" : "+v"(st), "+v"(cp));
+    int skip = 1;
+    StepIn s;
     AlignConst ac;
     if (tid == 0) {
-        s = *st;
-        ac = a.ac[b];
+        skip = st->done | st->pause;
+        ac = *cp;
+        if (STEP) {
+#pragma unroll
+            for (int k = 0; k < 12; ++k) s.T[k] = st->T[k];
+            s.ell = st->ell;
+            s.i_prev = st->i_prev;
+            s.total_pairs = st->total_pairs;
+            s.rc_build = st->rc_build;
+            s.it = st->it;
+            s.cls_built = st->cls_built;
+        }
     }
     const int kv = tid >> 5, sl = tid & 31;
     const double *pb = a.partials + (long long)b * a.nblk * kRedVals;
@@ -523,11 +546,11 @@ __global__ __launch_bounds__(kRedThreads) void reduce_finish_kernel(const Reduce
         if (sl == 0) tot[8 * c + kv] = x;
     }
     __syncthreads();
-    if (tid == 0 && !(s.done | s.pause)) {
-        finalize_local(s, ac, tot, a.trace ? a.trace + (long long)b * a.trace_rows * kTraceLen : nullptr,
-                       a.trace_rows, a.mode);
-        *st = s;
-    }
+    if (skip) return;  // (threads other than 0, and pairs that are done or paused)
+    if (STEP)
+        ascent_step(st, s, ac, tot, a.trace ? a.trace + (long long)b * a.trace_rows * kTraceLen : nullptr, a.trace_rows);
+    else
+        publish_evaluation(st, ac, tot);
 }
 
 void launch_reduce(const ReduceArgs &a, int B, hipStream_t s)
@@ -536,7 +559,10 @@ void launch_reduce(const ReduceArgs &a, int B, hipStream_t s)
         hipLaunchKernelGGL(reduce_kernel<true>, dim3(a.nblk, B), dim3(kRedThreads), 0, s, a);
     else
         hipLaunchKernelGGL(reduce_kernel<false>, dim3(a.nblk, B), dim3(kRedThreads), 0, s, a);
-    hipLaunchKernelGGL(reduce_finish_kernel, dim3(B), dim3(kRedThreads), 0, s, a);
+    if (a.mode)
+        hipLaunchKernelGGL(reduce_finish_kernel<true>, dim3(B), dim3(kRedThreads), 0, s, a);
+    else
+        hipLaunchKernelGGL(reduce_finish_kernel<false>, dim3(B), dim3(kRedThreads), 0, s, a);
 }
 
 // ---------------------------------------------------------------- backward
