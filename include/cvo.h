@@ -177,7 +177,9 @@ typedef struct {
     double cell_factor;    /* grid cell edge / cutoff radius, in [0.25, 4] */
     double cluster_factor; /* cluster edge cap / cutoff radius, in [0.05, 2] */
     double rebuild_ratio;  /* rebuild grids when cutoff < rebuild_ratio * cutoff at build, in (0, 1] */
-    int32_t unroll;        /* iterations enqueued per host check / per captured graph, 1..64 */
+    int32_t unroll;        /* iterations per captured graph (batched registrations), 1..64; a single
+                            * registration enqueues at most min(unroll, 4) iterations ahead of the
+                            * progress its device loop has reported */
     int32_t piece_work;    /* query x candidate products per unit of pair-pass work, 256..2^24 */
     int32_t cluster_rule;  /* how query clusters are formed: CVO_CLUSTER_OCTREE or CVO_CLUSTER_CHUNKS */
     int32_t adaptive;      /* 0 or 1.  1: a registration re-chooses cluster_max, cell_factor,

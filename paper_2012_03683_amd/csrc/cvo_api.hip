@@ -184,6 +184,35 @@ struct cvo_context {
         }
         return pinned;
     }
+    // Pinned memory that kernels post to (none in the allocation-free mode).
+    HostMail *mail_ = nullptr;
+    unsigned long long builds = 0;  // view builds announced through it
+    HostMail *mail()
+    {
+        if (fixed.on) return nullptr;
+        if (!mail_) {
+            void *p = nullptr;
+            HIP_OK(hipHostMalloc(&p, sizeof(HostMail), hipHostMallocDefault));
+            std::memset(p, 0, sizeof(HostMail));
+            mail_ = static_cast<HostMail *>(p);
+        }
+        return mail_;
+    }
+    // Spins until `seen` says so, and asks the runtime now and then whether the
+    // stream has run dry (or failed) without it: false then.
+    template <class F> bool spin_until(F &&seen)
+    {
+        for (unsigned n = 1;; ++n) {
+            if (seen()) return true;
+            __builtin_ia32_pause();
+            if (n % 4096 == 0) {
+                const hipError_t e = hipStreamQuery(stream);
+                if (e == hipSuccess) return seen();
+                if (e != hipErrorNotReady) HIP_OK(e);
+                (void)hipGetLastError();  // (not ready is no error of a later check)
+            }
+        }
+    }
     // Host -> device copies are staged in a pinned ring and not waited for.
     // A ring slot is written again only after the stream that reads it has
     // been synchronised (the ring restarts then), so a pending copy never
@@ -240,6 +269,13 @@ struct cvo_context {
         if (stream == ring_stream) ring_off = 0;
         std::memcpy(dst, h, bytes);
     }
+    // waits for the stream (which also frees the ring)
+    void wait()
+    {
+        timing.host_waits += 1;
+        HIP_OK(hipStreamSynchronize(stream));
+        if (stream == ring_stream) ring_off = 0;
+    }
     void check_launch(const char *what)
     {
         hipError_t e = hipGetLastError();
@@ -291,6 +327,8 @@ struct cvo_context {
         bufs.clear();
         if (pinned) hipHostFree(pinned);
         pinned = nullptr;
+        if (mail_) hipHostFree(mail_);
+        mail_ = nullptr;
         if (ring) hipHostFree(ring);
         ring = nullptr;
         ring_off = ring_cap = 0;
@@ -653,9 +691,22 @@ void build_pairs(cvo_context *ctx, Views &v, const std::vector<PairSpec> &pairs,
         a.rec_cap = ctx->fixed.on ? 0 : (long long)ctx->room<PieceRec>("v.recs");
         if (!ctx->fixed.on) launch_params(a, ctx->stream);
         launch_views(a, lay, kappa, ctx->stream);
-        if (a.rec_cap) launch_records(a, ctx->stream);
+        a.mail = ctx->mail();
+        a.build = ++ctx->builds;
+        if (a.mail) launch_records(a, ctx->stream);
         ctx->check_launch("view build");
-        ctx->download(&info, a.info, sizeof(info));
+        // (posted by the record kernel: a third of the wait of a copy and a
+        // stream synchronisation)
+        if (a.mail && ctx->spin_until([&] { return __atomic_load_n(&a.mail->build, __ATOMIC_ACQUIRE) == a.build; })) {
+            ctx->timing.host_waits += 1;
+            info.alloc = a.mail->alloc;
+            info.cells = a.mail->cells;
+            info.bad = a.mail->bad;
+            info.overflow = a.mail->overflow;
+        } else {
+            ctx->download(&info, a.info, sizeof(info));
+        }
+        a.mail = nullptr;
         require(info.bad == 0, "a cloud has non-finite coordinates");
         require(info.cells < (1LL << 31), "cell tables too large");
         if (!info.overflow) break;
@@ -831,11 +882,13 @@ void iteration_args(const Problem &p, int mode, double *trace, long long trace_r
     r.one_query = (long long)p.nblk * kRedThreads >= mx;
 }
 
-void enqueue_iteration(cvo_context *ctx, Problem &p, int mode, double *trace, long long trace_rows, bool timed)
+void enqueue_iteration(cvo_context *ctx, Problem &p, int mode, double *trace, long long trace_rows, bool timed,
+                       HostMail *mail = nullptr)
 {
     PairPassArgs a;
     ReduceArgs r;
     iteration_args(p, mode, trace, trace_rows, a, r);
+    r.mail = mail;
     if (timed) run_pair_pass(ctx, a, p.lay, 0);
     else {
         if (!launch_pair_pass(a, p.lay, 0, ctx->stream))
@@ -958,8 +1011,15 @@ void evaluate_all(cvo_context *ctx, std::vector<Evaluation> &ev, const cvo_featu
     p.sig2 = p.lay.sig2;
     p.ellobj = ellobj ? 1 : 0;
     setup_problem(ctx, p, xs, zs, st, ac);
-    enqueue_iteration(ctx, p, 0, nullptr, 0, ctx->profiling);
-    ctx->download(st.data(), p.d_state, sizeof(PairState) * st.size());
+    HostMail *mail = st.size() <= kMailStates ? ctx->mail() : nullptr;
+    if (mail) std::memset(mail->state, 0, sizeof(PairState) * st.size());
+    enqueue_iteration(ctx, p, 0, nullptr, 0, ctx->profiling, mail);
+    if (mail) {
+        ctx->wait();
+        std::memcpy(st.data(), mail->state, sizeof(PairState) * st.size());
+    } else {
+        ctx->download(st.data(), p.d_state, sizeof(PairState) * st.size());
+    }
     size_t k = 0;
     for (auto &e : ev)
         if (e.X->n != 0 && e.Z->n != 0) e.out = st[k++];
@@ -1002,6 +1062,8 @@ template <class F> cvo_status guarded(cvo_context *ctx, F &&f)
 }
 
 // ------------------------------------------------------------------ ascent driver
+constexpr int kRunAhead = 4;  // iterations of one registration enqueued ahead of its posted progress
+
 void align_many(cvo_context *ctx, const std::vector<CloudPtrs> &X, const std::vector<CloudPtrs> &Z,
                 const cvo_feature_spec *spec, const std::vector<cvo_align_params> &prm,
                 const std::vector<const double *> &T0, std::vector<PairState> &final_state, double *trace_host,
@@ -1051,7 +1113,6 @@ void align_many(cvo_context *ctx, const std::vector<CloudPtrs> &X, const std::ve
     // not another batch (the loop below otherwise ends only when every pair
     // is done).
     std::vector<PairState> ref = st;
-    size_t timed_done = 0;  // pending timed launches of batches already waited for
     for (;;) {
         if (probe) {
             enqueue_iteration(ctx, p, 1, d_trace, trace_rows, ctx->profiling);
@@ -1081,12 +1142,36 @@ void align_many(cvo_context *ctx, const std::vector<CloudPtrs> &X, const std::ve
             ctx->timing.graph_launches += 1;
             ctx->timing.evaluations += U;
         } else {
-            for (int u = 0; u < U; ++u) enqueue_iteration(ctx, p, 1, d_trace, trace_rows, ctx->profiling);
+            // One registration: iterations are enqueued a few ahead of the
+            // last step the device has posted, until it posts that the pair
+            // is done or pauses.  No iteration is enqueued beyond the last
+            // one there can be, the stream never runs dry between host
+            // checks, and at most kRunAhead iterations find a pair that has
+            // stopped (each still costs its launches, 7-13 us).
+            HostMail *mail = ctx->mail();
+            const long long it0 = ref[0].it;
+            __atomic_store_n(&mail->progress, (unsigned long long)it0 << 2, __ATOMIC_RELEASE);
+            const long long most = d_sched ? n_sched : (long long)prm[0].max_iter;
+            const long long ahead = std::min(kRunAhead, U);
+            long long sent = it0, timed = 0;
+            auto posted = [&] { return __atomic_load_n(&mail->progress, __ATOMIC_ACQUIRE); };
+            for (;;) {
+                const unsigned long long w = posted();
+                if (w & 3) break;
+                const long long at = (long long)(w >> 2);
+                if (sent - at < ahead) {
+                    if (sent >= most) break;
+                    enqueue_iteration(ctx, p, 1, d_trace, trace_rows, ctx->profiling, mail);
+                    ++sent;
+                } else {
+                    // (launch times of steps taken are read while others run)
+                    for (; ctx->profiling && timed + 1 < at - it0; ++timed) ctx->harvest_events(1);
+                    if (!ctx->spin_until([&] { return posted() != w; })) break;
+                }
+            }
         }
-        // the previous batch's launch times are read while this batch runs
-        if (ctx->profiling) ctx->harvest_events(timed_done);
         ctx->download(now.data(), p.d_state, sizeof(PairState) * B);
-        timed_done = ctx->ev_pending.size();
+        if (ctx->profiling) ctx->harvest_events();
         for (int b = 0; b < B; ++b)
             if (!ref[b].done && !ref[b].pause && !now[b].done && now[b].it <= ref[b].it)
                 throw CvoError(CVO_ERR_DEVICE, "pair " + std::to_string(b) +
@@ -1111,10 +1196,7 @@ void align_many(cvo_context *ctx, const std::vector<CloudPtrs> &X, const std::ve
             changed = true;
         }
         probe = false;
-        if (all_done) {
-            if (ctx->profiling) ctx->harvest_events();
-            break;
-        }
+        if (all_done) break;
         if (rebuild) build_views(ctx, p, X, Z, ell_build, shape);
         if (changed) ctx->upload(p.d_state, now.data(), sizeof(PairState) * B);
         ref = now;

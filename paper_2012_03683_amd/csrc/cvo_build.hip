@@ -911,13 +911,21 @@ __global__ __launch_bounds__(kClusThreads) void cluster_kernel(const ViewArgs a,
 
 // The pieces' records, bucket by bucket (heaviest first; a cluster's pieces
 // together): 16 lanes per cluster write them.  Nothing is written when there
-// is no room for all of them.
+// is no room for all of them.  The build's counts are posted to the host first.
 __global__ __launch_bounds__(256) void record_kernel(const ViewArgs a)
 {
     static_assert(kCostBuckets == 512, "two buckets per thread");
     __shared__ int s_base[kCostBuckets];
     __shared__ int s_w[4];
     const BuildInfo *f = a.info;
+    if (a.mail && blockIdx.x == 0 && threadIdx.x == 0) {
+        HostMail *m = a.mail;
+        __hip_atomic_store(&m->alloc, f->alloc, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+        __hip_atomic_store(&m->cells, f->cells, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+        __hip_atomic_store(&m->bad, f->bad, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+        __hip_atomic_store(&m->overflow, f->overflow, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+        __hip_atomic_store(&m->build, a.build, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
+    }
     if (f->overflow || (long long)(unsigned)f->alloc > a.rec_cap) return;
     const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6, l16 = tid & 15;
     const int h0 = f->hist[2 * tid], h1 = f->hist[2 * tid + 1];
@@ -1014,7 +1022,7 @@ void launch_views(const ViewArgs &a, const FeatLayout &lay, double kappa, hipStr
 
 void launch_records(const ViewArgs &a, hipStream_t s)
 {
-    if (a.n[1] > 0) hipLaunchKernelGGL(record_kernel, dim3(blocks_for(a.n[1], 32, 2048)), dim3(256), 0, s, a);
+    hipLaunchKernelGGL(record_kernel, dim3(blocks_for(a.n[1], 32, 2048)), dim3(256), 0, s, a);
 }
 
 }  // namespace cvo

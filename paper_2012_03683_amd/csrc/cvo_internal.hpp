@@ -149,6 +149,23 @@ struct BuildInfo {
     int hist[kCostBuckets];    // pieces per cost bucket
 };
 
+// What kernels tell a waiting host without a copy: pinned host memory, written
+// with system-scope stores.
+constexpr int kMailStates = 4;
+struct alignas(64) HostMail {
+    // the head of BuildInfo, then the number of the build it belongs to
+    unsigned long long alloc;
+    long long cells;
+    int bad, overflow;
+    unsigned long long build;
+    unsigned long long pad[4];
+    // one registration's progress: steps taken << 2 | paused << 1 | done
+    unsigned long long progress;
+    unsigned long long pad2[7];
+    // evaluations of up to kMailStates pairs (the evaluation's fields only)
+    PairState state[kMailStates];
+};
+
 // One cluster as planned: its geometry, its points, its pieces and slots.
 struct alignas(64) ClusterRec {
     double4 geo;               // centre (own frame) and radius

@@ -40,6 +40,8 @@ struct ViewArgs {
     int work;                     // query x candidate products per piece
     PieceRec *recs;
     long long rec_cap;            // records there is room for
+    HostMail *mail;               // record_kernel posts the build's counts here (may be null)
+    unsigned long long build;     // its number
 };
 void launch_boxes(const ViewArgs &a, hipStream_t s);
 void launch_params(const ViewArgs &a, hipStream_t s);
@@ -75,6 +77,7 @@ struct ReduceArgs {
     double *partials;          // B * kRedVals * nblk (per pair value-major: value v of block k at v * nblk + k)
     double *trace;             // B * trace_rows * kTraceLen, may be null
     long long trace_rows;
+    HostMail *mail;            // progress (steps of one pair) or evaluations (B <= kMailStates); may be null
     int nblk;
     int mode;                  // 0: evaluate only, 1: evaluate and take an ascent step
     int ellobj;                // nonzero: also reduce the lengthscale objective's sums

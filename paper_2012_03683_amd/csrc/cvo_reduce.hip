@@ -136,7 +136,7 @@ __device__ __forceinline__ void gradient(const double *tot, double il2, double g
 }
 
 // Publish an evaluation of one pair.
-__device__ void publish_evaluation(PairState *st, const AlignConst &ac, const double *tot)
+__device__ void publish_evaluation(PairState *st, PairState *host, const AlignConst &ac, const double *tot)
 {
     const double ell = st->ell;
     const double il1 = 1.0 / ell;
@@ -144,21 +144,31 @@ __device__ void publish_evaluation(PairState *st, const AlignConst &ac, const do
     double g[6];
     gradient(tot, il2, g);
     const double F = tot[R_F];
-    st->F = F;
-    st->i_theta = (ac.sqrt_nm > 0.0) ? F / ac.sqrt_nm : 0.0;
-    st->curv = quad_form(tot, g);
-    st->r_max = tot[R_RMAX];
-    st->dF_dell = tot[R_TRS] * il2 * il1;
-    st->n_pairs = tot[R_N];
-#pragma unroll
-    for (int k = 0; k < 6; ++k) st->grad[k] = g[k];
+    const double ind = (ac.sqrt_nm > 0.0) ? F / ac.sqrt_nm : 0.0;
+    const double curv = quad_form(tot, g);
+    const double dl = tot[R_TRS] * il2 * il1;
     // lengthscale objective J = sum log W_j - 3 |Z+| log ell (all zero
     // unless its sums were reduced)
     const double mp = tot[R_ZP];
-    st->J = mp > 0.0 ? tot[R_LOGW] - 3.0 * mp * log(ell) : 0.0;
-    st->dJ_dell = mp > 0.0 ? tot[R_RSUM] * il2 * il1 - 3.0 * mp * il1 : 0.0;
-    st->ell_ml = mp > 0.0 ? sqrt(tot[R_RSUM] / (3.0 * mp)) : 0.0;
-    st->zplus = mp;
+    const double J = mp > 0.0 ? tot[R_LOGW] - 3.0 * mp * log(ell) : 0.0;
+    const double dJ = mp > 0.0 ? tot[R_RSUM] * il2 * il1 - 3.0 * mp * il1 : 0.0;
+    const double ml = mp > 0.0 ? sqrt(tot[R_RSUM] / (3.0 * mp)) : 0.0;
+    auto put = [&](PairState *o) {
+        o->F = F;
+        o->i_theta = ind;
+        o->curv = curv;
+        o->r_max = tot[R_RMAX];
+        o->dF_dell = dl;
+        o->n_pairs = tot[R_N];
+#pragma unroll
+        for (int k = 0; k < 6; ++k) o->grad[k] = g[k];
+        o->J = J;
+        o->dJ_dell = dJ;
+        o->ell_ml = ml;
+        o->zplus = mp;
+    };
+    put(st);
+    if (host) put(host);  // (read after the stream has been waited for)
 }
 
 // What an ascent step reads of the pair's state.
@@ -170,10 +180,10 @@ struct StepIn {
 
 // One ascent step of one pair (same decision sequence as the definition it
 // follows): reads s, writes the fields of *st that later iterations and the
-// host read.  One thread runs it, and its time is the number of instructions
+// host read, and returns 1 if the pair is done, 2 if it pauses, else 0.  One thread runs it, and its time is the number of instructions
 // on that thread, so it computes nothing else: no evaluation fields, no
 // inverse pose (only the backward uses one).
-__device__ __forceinline__ void ascent_step(PairState *st, const StepIn &s, const AlignConst &ac, const double *tot,
+__device__ __forceinline__ int ascent_step(PairState *st, const StepIn &s, const AlignConst &ac, const double *tot,
                                             double *trace, long long trace_rows)
 {
     const double ell = s.ell;
@@ -187,12 +197,12 @@ __device__ __forceinline__ void ascent_step(PairState *st, const StepIn &s, cons
     st->i_theta = ind;
     st->n_pairs = np;
     const double gn2 = g[0] * g[0] + g[1] * g[1] + g[2] * g[2] + g[3] * g[3] + g[4] * g[4] + g[5] * g[5];
-    if (np == 0.0) { st->status = ST_NO_OVERLAP; st->done = 1; return; }
-    if (gn2 == 0.0) { st->status = ST_STATIONARY; st->done = 1; return; }
+    if (np == 0.0) { st->status = ST_NO_OVERLAP; st->done = 1; return 1; }
+    if (gn2 == 0.0) { st->status = ST_STATIONARY; st->done = 1; return 1; }
     // direction: the Riemannian gradient G^-1 g
     double d[6];
     if (ac.metric == 0) {
-        if (!metric_solve(tot, ac.inv_m, g, d)) { st->status = ST_STATIONARY; st->done = 1; return; }
+        if (!metric_solve(tot, ac.inv_m, g, d)) { st->status = ST_STATIONARY; st->done = 1; return 1; }
     } else {
 #pragma unroll
         for (int k = 0; k < 6; ++k) d[k] = g[k];
@@ -235,7 +245,7 @@ __device__ __forceinline__ void ascent_step(PairState *st, const StepIn &s, cons
         if (it + 1 >= ac.n_sched) {
             st->status = ST_MAX_ITER;
             st->done = 1;
-            return;
+            return 1;
         }
         next = ac.ell_sched[it + 1];
         st->ell = next;
@@ -255,7 +265,7 @@ __device__ __forceinline__ void ascent_step(PairState *st, const StepIn &s, cons
         if (still && tau * nw < ac.eps_rot && tau * nv < ac.eps_trans) {
             st->status = ST_CONVERGED;
             st->done = 1;
-            return;
+            return 1;
         }
     } else if (!ac.fixed_iters) {
         const double ip = s.i_prev;
@@ -270,13 +280,13 @@ __device__ __forceinline__ void ascent_step(PairState *st, const StepIn &s, cons
         if (next == ac.ell_min && tau * nw < ac.eps_rot && tau * nv < ac.eps_trans) {
             st->status = ST_CONVERGED;
             st->done = 1;
-            return;
+            return 1;
         }
     }
     if (it + 1 >= ac.max_iter) {
         st->status = ST_MAX_ITER;
         st->done = 1;
-        return;
+        return 1;
     }
     // the views no longer fit: the cutoff shrank past the rebuild ratio, or
     // the pair density fell to a lower class.  Decided from the iterates
@@ -287,8 +297,11 @@ __device__ __forceinline__ void ascent_step(PairState *st, const StepIn &s, cons
     const bool cut = isfinite(ac.kappa);
     if ((cut && ac.kappa * next < ac.rebuild_ratio * s.rc_build) ||
         (cut && ac.rebuild_ratio < 1.0 && ac.kappa * next * ac.rebuild_ratio > s.rc_build) ||
-        (ac.adaptive && s.cls_built >= 0 && density_class(np * ac.inv_m, ac.cls_t) < s.cls_built))
+        (ac.adaptive && s.cls_built >= 0 && density_class(np * ac.inv_m, ac.cls_t) < s.cls_built)) {
         st->pause = 1;
+        return 2;
+    }
+    return 0;
 }
 
 static_assert(kRedThreads == 256 && R_END == 48 && R_END <= kRedVals, "reduction layout");
@@ -547,10 +560,15 @@ __global__ __launch_bounds__(kRedThreads) void reduce_finish_kernel(const Reduce
     }
     __syncthreads();
     if (skip) return;  // (threads other than 0, and pairs that are done or paused)
-    if (STEP)
-        ascent_step(st, s, ac, tot, a.trace ? a.trace + (long long)b * a.trace_rows * kTraceLen : nullptr, a.trace_rows);
-    else
-        publish_evaluation(st, ac, tot);
+    if (STEP) {
+        const int end =
+            ascent_step(st, s, ac, tot, a.trace ? a.trace + (long long)b * a.trace_rows * kTraceLen : nullptr, a.trace_rows);
+        if (a.mail)
+            __hip_atomic_store(&a.mail->progress, (unsigned long long)(s.it + 1) << 2 | (unsigned long long)end,
+                               __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+    } else {
+        publish_evaluation(st, a.mail ? &a.mail->state[b] : nullptr, ac, tot);
+    }
 }
 
 void launch_reduce(const ReduceArgs &a, int B, hipStream_t s)
