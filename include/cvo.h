@@ -164,8 +164,8 @@ typedef struct {
 } cvo_eval;
 
 /* Query clusters (cvo_tuning.cluster_rule): OCTREE takes the largest aligned
- * Morton (octree) block with at most cluster_max points and an edge within
- * cluster_factor * r_c; CHUNKS cuts the Morton-ordered points into runs of
+ * octree block with at most cluster_max points and an edge within
+ * cluster_factor * r_c; CHUNKS cuts the points in curve order into runs of
  * cluster_max and halves a run until its bounding box edge is within
  * cluster_factor * r_c (parts of cluster_max / 2^k points). */
 #define CVO_CLUSTER_OCTREE 0

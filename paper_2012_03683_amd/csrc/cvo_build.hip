@@ -6,14 +6,14 @@
 // Both sides of all pairs go through the same launches:
 //   box_kernel        partial bounding boxes and the non-finite check
 //   params_kernel     grids, cluster parameters and key widths from the boxes
-//   key_kernel        cell index (reference side) / Morton code (query side)
+//   key_kernel        cell index (reference side) / Hilbert index (query side)
 //                     of every point, and the first pass's digit counts
 //   sort_pass         one 8-bit pass of a stable LSD radix sort per launch
 //   (radix_hist, scan_*, radix_scatter: the passes of large sorts)
 //   view_kernel       sorted float4 copies, padded and pre-scaled feature
 //                     rows, and the dense first-index-per-cell table
-//   cluster_kernel    query clusters, their candidate counts at the current
-//                     pose, their pieces and output slots, the query map
+//   cluster_kernel    query clusters, their candidate counts at the current pose
+//   plan_kernel       their pieces and output slots, the query map
 //   record_kernel     the pieces in dispatch order, heaviest bucket first
 // What bounds them is latency, not bytes (30,000 + 30,000 points with 24
 // feature columns move under 20 MB in all), so the chain is made short: both
@@ -91,7 +91,7 @@ __global__ __launch_bounds__(1024) void params_kernel(const ViewArgs a)
     __shared__ int s_bad, s_mbits, s_max;
     const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
     const int cbits = bits_for((unsigned long long)(a.B - 1));
-    const int maxbits = min(kMortonBits, (62 - cbits) / 3);
+    const int maxbits = min(kCurveBits, (62 - cbits) / 3);
     if (threadIdx.x == 0) { s_bad = 0; s_mbits = 1; s_max = 1; }
     for (int i = threadIdx.x; i < kCostBuckets; i += 1024) a.info->hist[i] = 0;
     long long base = 0;  // (thread 0)
@@ -149,7 +149,7 @@ __global__ __launch_bounds__(1024) void params_kernel(const ViewArgs a)
                 atomicMax(&s_max, (int)nc);
             } else {
                 // octree blocks need 16 quanta per cap; chunks only use the
-                // Morton order, which a finer quantum makes more local
+                // order along the curve, which a finer quantum makes more local
                 const double cap = isfinite(in.rc) ? in.cluster_factor * in.rc : ext * 2.0;
                 int L = in.octree ? 4 : 5;
                 double q = cap / (double)(1 << L);
@@ -189,6 +189,7 @@ __global__ __launch_bounds__(1024) void params_kernel(const ViewArgs a)
         f.bad = s_bad;
         f.overflow = base > a.cell_cap;
         f.nclus = 0;
+        f.cand = 0;
         f.kbits = bits_for((unsigned long long)s_max);  // the cell count itself must fit
         f.mbits = min(s_mbits, maxbits);
         f.sbits[0] = f.kbits + cbits;
@@ -218,6 +219,39 @@ __device__ inline unsigned long long spread3(unsigned long long v)
     v = (v | (v << 4)) & 0x10c30c30c30c30c3ULL;
     v = (v | (v << 2)) & 0x1249249249249249ULL;
     return v;
+}
+
+// Index of a quantised point along a Hilbert curve of `bits` bits per axis (the
+// transpose method of J. Skilling, "Programming the Hilbert curve", 2004).  Like
+// a Morton code its leading 3 k bits name an octree block, but consecutive blocks
+// always touch, so runs of points are more compact: the pairs within the cutoff
+// among those a cluster's cull lets through rise from 0.58 to 0.62 (RGB-D 40,000,
+// ell 0.1), 0.40 to 0.45 (ell 0.05), 0.50 to 0.55 (stereo 30,000, ell 0.1).
+__device__ inline unsigned long long hilbert3(unsigned x, unsigned y, unsigned z, int bits)
+{
+    unsigned X[3] = {x, y, z};
+    for (unsigned q = 1u << (bits - 1); q > 1; q >>= 1) {
+        const unsigned p = q - 1;
+#pragma unroll
+        for (int i = 0; i < 3; ++i) {
+            if (X[i] & q) {
+                X[0] ^= p;
+            } else {
+                const unsigned t = (X[0] ^ X[i]) & p;
+                X[0] ^= t;
+                X[i] ^= t;
+            }
+        }
+    }
+    X[1] ^= X[0];
+    X[2] ^= X[1];
+    unsigned t = 0;
+    for (unsigned q = 1u << (bits - 1); q > 1; q >>= 1)
+        if (X[2] & q) t ^= q - 1;
+    X[0] ^= t;
+    X[1] ^= t;
+    X[2] ^= t;
+    return spread3(X[2]) | (spread3(X[1]) << 1) | (spread3(X[0]) << 2);
 }
 
 // The pair of global point i of a side (xb / zb ascend; empty clouds skipped).
@@ -273,10 +307,8 @@ __global__ __launch_bounds__(1024) void key_kernel(const ViewArgs a)
         } else {
             const ClusterParam &g = a.cp[b];
             const int lim = 1 << a.info->mbits;
-            const unsigned long long qx = (unsigned long long)cell_of(xyz[0], g.ox, g.iq, lim);
-            const unsigned long long qy = (unsigned long long)cell_of(xyz[1], g.oy, g.iq, lim);
-            const unsigned long long qz = (unsigned long long)cell_of(xyz[2], g.oz, g.iq, lim);
-            key = spread3(qx) | (spread3(qy) << 1) | (spread3(qz) << 2);
+            key = hilbert3(cell_of(xyz[0], g.ox, g.iq, lim), cell_of(xyz[1], g.oy, g.iq, lim),
+                           cell_of(xyz[2], g.oz, g.iq, lim), a.info->mbits);
             key |= (unsigned long long)b << (3 * a.info->mbits);
         }
         const long long o = (side ? a.n[0] : 0) + i;
@@ -694,7 +726,7 @@ constexpr int kClusBlocks = 256;  // blocks up to which a block takes fewer poin
 
 // A block takes PTS points.  One thread per point finds the point's cluster; the first
 // point of a cluster is its head.
-//   octree rule: the largest aligned Morton block (level <= ClusterParam.level)
+//   octree rule: the largest aligned octree block (level <= ClusterParam.level)
 //     holding at most cluster_max points.  Block counts grow with the level, so
 //     every point of a block makes the same choice, and a block of at most 64
 //     points lies within the staged neighbours: its ends are found by walking
@@ -704,11 +736,7 @@ constexpr int kClusBlocks = 256;  // blocks up to which a block takes fewer poin
 //     until the part's bounding box edge is within ClusterParam.cap or the part
 //     is one point.
 // Then 2 to 64 lanes per head count the candidates of its neighbourhood at
-// the current pose (one grid row per lane and turn), from which its pieces
-// follow: c_max = max(512, work / n) candidates each.  A block reserves its
-// clusters' output slots, records and places in the cost buckets with one
-// atomic each (an atomic per cluster serialises on the few buckets that most
-// clusters of a sparse cloud share: 22 us for 1,900 of them).
+// the current pose (one grid row per lane and turn).
 // The kernel is a chain of dependent loads, so fewer points per block (more
 // blocks, more lanes per head) are faster until the blocks' atomics become
 // the bound: blocks of 64 / 256 points take 14.2 / 25.0 us at 15,000 points
@@ -721,12 +749,9 @@ __global__ __launch_bounds__(kClusThreads) void cluster_kernel(const ViewArgs a,
     if (a.info->overflow) return;
     __shared__ float4 s_pt[kClusSpan];
     __shared__ unsigned long long s_key[kClusSpan];
-    __shared__ double4 s_geo[PTS];
-    __shared__ int s_first[PTS], s_n[PTS], s_b[PTS], s_np[PTS], s_C[PTS], s_slot[PTS];
-    __shared__ int s_hist[kCostBuckets];
-    __shared__ int s_w[4], s_w2[4], s_heads;
-    __shared__ unsigned long long s_base;
-    __shared__ int s_cbase;
+    __shared__ Geo s_geo[PTS];
+    __shared__ int s_first[PTS], s_n[PTS], s_b[PTS], s_C[PTS];
+    __shared__ int s_w[4], s_heads, s_cbase;
     const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
     const long long N = a.n[1];
     const long long p0 = (long long)blockIdx.x * PTS;
@@ -738,7 +763,6 @@ __global__ __launch_bounds__(kClusThreads) void cluster_kernel(const ViewArgs a,
         s_pt[k] = in ? a.pts[1][p] : make_float4(0.f, 0.f, 0.f, 0.f);
         s_key[k] = in ? keys[p] : ~0ULL;
     }
-    for (int k = tid; k < kCostBuckets; k += kClusThreads) s_hist[k] = 0;
     __syncthreads();
     const long long p = p0 + tid;
     const int shift = 3 * a.info->mbits;
@@ -820,7 +844,7 @@ __global__ __launch_bounds__(kClusThreads) void cluster_kernel(const ViewArgs a,
             // inflate so FP64 rounding of the transformed centre and points can
             // never place a member outside the sphere
             const double r = sqrt(r2) * (1.0 + 1e-12) + 1e-12 * (mag + 1.0);
-            s_geo[k] = make_double4(cc[0], cc[1], cc[2], r);
+            s_geo[k] = Geo{cc[0], cc[1], cc[2], r};
             s_first[k] = (int)p;
             s_n[k] = cnt;
             s_b[k] = b;
@@ -846,67 +870,108 @@ __global__ __launch_bounds__(kClusThreads) void cluster_kernel(const ViewArgs a,
             const Neighbourhood nb = neighbourhood(Pm, s_geo[k], kappa * st->ell, cut, gd);
             if (nb.any) {
                 const int nyr = nb.iy1 - nb.iy0 + 1, nrows = nyr * (nb.iz1 - nb.iz0 + 1);
-                const int run = nb.ix1 - nb.ix0 + 1;
+                const BallRows br = ball_rows(nb, gd, cut);
 #pragma unroll 4
                 for (int r = lg_; r < nrows; r += G) {
                     const int iy = nb.iy0 + r % nyr, iz = nb.iz0 + r / nyr;
-                    const long long c0 =
-                        (long long)gd.cell_base + nb.ix0 + (long long)gd.nx * (iy + (long long)gd.ny * iz);
-                    C += a.cell_start[c0 + run] - a.cell_start[c0];
+                    int i0, i1;
+                    if (!row_cells(nb, br, iy, iz, i0, i1)) continue;
+                    const long long c0 = (long long)gd.cell_base + (long long)gd.nx * (iy + (long long)gd.ny * iz);
+                    C += a.cell_start[c0 + i1 + 1] - a.cell_start[c0 + i0];
                 }
             }
         }
         for (int off = G >> 1; off > 0; off >>= 1) C += __shfl_xor(C, off);
-        if (lg_ == 0 && k < nh) {
-            const int cm = max(kMinPieceCand, a.work / s_n[k]);
-            s_np[k] = C > 0 ? min((C + cm - 1) / cm, 4096) : 1;
-            s_C[k] = C;
-        }
+        if (lg_ == 0 && k < nh) s_C[k] = C;
     }
     __syncthreads();
-    // output slots and records (thread k: head k)
-    const int np = tid < nh ? s_np[tid] : 0;
-    const int ns = tid < nh ? np * s_n[tid] : 0;
+    const int C = tid < nh ? s_C[tid] : 0;
+    const int ic = wave_scan_add(C);
+    if (lane == 63) s_w[wv] = ic;
+    __syncthreads();
+    if (tid == 0 && nh > 0) {
+        s_cbase = atomicAdd(&a.info->nclus, nh);
+        atomicAdd(&a.info->cand, (unsigned long long)s_w[0] + s_w[1] + s_w[2] + s_w[3]);
+    }
+    __syncthreads();
+    if (tid < nh) {
+        ClusterRec r;
+        r.geo = s_geo[tid];
+        r.first = s_first[tid];
+        r.n = s_n[tid];
+        r.cand = C;
+        r.np = r.slot = r.code = r.place = 0;
+        r.b = s_b[tid];
+        r.inverse = a.in[r.b].inverse;
+        r.pad[0] = r.pad[1] = r.pad[2] = 0;
+        a.clus[s_cbase + tid] = r;
+    }
+}
+
+// The pieces of every cluster, c_max = max(floor, work / n) candidates each (the
+// floor from the candidates of all clusters, see kPieceTarget), their output
+// slots, their places in the dispatch order's cost buckets and the query map.
+// A block reserves slots and bucket places for its 256 clusters with one
+// atomic each (an atomic per cluster serialises on the few buckets that most
+// clusters of a sparse cloud share: 22 us for 1,900 of them).
+__global__ __launch_bounds__(256) void plan_kernel(const ViewArgs a)
+{
+    if (a.info->overflow) return;
+    const int nclus = a.info->nclus;
+    const int c0 = blockIdx.x * 256;
+    if (c0 >= nclus) return;
+    __shared__ int s_first[256], s_n[256], s_np[256], s_slot[256];
+    __shared__ int s_hist[kCostBuckets];
+    __shared__ int s_w[4], s_w2[4];
+    __shared__ unsigned long long s_base;
+    const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
+    const unsigned long long even = (a.info->cand / kPieceTarget + 63) & ~63ULL;
+    const int floor_ = (int)min(max(even, (unsigned long long)kPieceFew), (unsigned long long)kPieceMany);
+    for (int k = tid; k < kCostBuckets; k += 256) s_hist[k] = 0;
+    ClusterRec *rec = a.clus + c0 + tid;
+    const bool in = c0 + tid < nclus;
+    int n = 0, np = 0, C = 0, first = 0;
+    if (in) {
+        n = rec->n;
+        C = rec->cand;
+        first = rec->first;
+        const int cm = max(floor_, a.work / n);
+        np = C > 0 ? min((C + cm - 1) / cm, 4096) : 1;
+    }
+    const int ns = np * n;
     const int ip = wave_scan_add(np), is = wave_scan_add(ns);
     if (lane == 63) { s_w[wv] = ip; s_w2[wv] = is; }
+    __syncthreads();
     int code = 0, place = 0;
-    if (tid < nh) {
-        const int cand = (s_C[tid] + np - 1) / np;  // candidates per piece
-        code = kCostBuckets - 1 - cost_bucket((unsigned long long)s_n[tid] * (unsigned long long)(cand + 64));
+    if (in) {
+        const int cand = (C + np - 1) / np;  // candidates per piece
+        code = kCostBuckets - 1 - cost_bucket((unsigned long long)n * (unsigned long long)(cand + 64));
         place = atomicAdd(&s_hist[code], np);
     }
     __syncthreads();
-    for (int k = tid; k < kCostBuckets; k += kClusThreads)
+    for (int k = tid; k < kCostBuckets; k += 256)
         if (s_hist[k] > 0) s_hist[k] = atomicAdd(&a.info->hist[k], s_hist[k]);
     if (tid == 0) {
         const unsigned long long tp = s_w[0] + s_w[1] + s_w[2] + s_w[3];
         const unsigned long long ts = s_w2[0] + s_w2[1] + s_w2[2] + s_w2[3];
-        s_base = nh > 0 ? atomicAdd(&a.info->alloc, tp | ts << 32) : 0ULL;
-        s_cbase = nh > 0 ? atomicAdd(&a.info->nclus, nh) : 0;
+        s_base = atomicAdd(&a.info->alloc, tp | ts << 32);
     }
     __syncthreads();
-    if (tid < nh) {
-        int slot = (int)(s_base >> 32) + is - ns;
-        for (int w = 0; w < wv; ++w) slot += s_w2[w];
-        s_slot[tid] = slot;
-        const int n = s_n[tid];
-        ClusterRec r;
-        r.geo = s_geo[tid];
-        r.first = s_first[tid];
-        r.n = n;
-        r.np = np;
-        r.slot = slot;
-        r.b = s_b[tid];
-        r.inverse = a.in[r.b].inverse;
-        r.code = code;
-        r.place = s_hist[code] + place;
-        a.clus[s_cbase + tid] = r;
+    int slot = (int)(s_base >> 32) + is - ns;
+    for (int w = 0; w < wv; ++w) slot += s_w2[w];
+    s_first[tid] = first;
+    s_n[tid] = n;
+    s_np[tid] = np;
+    s_slot[tid] = slot;
+    if (in) {
+        rec->np = np;
+        rec->slot = slot;
+        rec->code = code;
+        rec->place = s_hist[code] + place;
     }
     __syncthreads();
-    for (int k = tid >> 4; k < nh; k += kClusThreads / 16) {
-        const int n = s_n[k], first = s_first[k];
-        for (int t = tid & 15; t < n; t += 16) a.qmap[first + t] = make_int4(t, n, s_np[k], s_slot[k] + t);
-    }
+    for (int k = tid >> 4; k < 256; k += 16)
+        for (int t = tid & 15; t < s_n[k]; t += 16) a.qmap[s_first[k] + t] = make_int4(t, s_n[k], s_np[k], s_slot[k] + t);
 }
 
 // The pieces' records, bucket by bucket (heaviest first; a cluster's pieces
@@ -990,7 +1055,7 @@ void launch_views(const ViewArgs &a, const FeatLayout &lay, double kappa, hipStr
     while ((1LL << cbits) < a.B) ++cbits;
     // key bits of each side, at most (the device knows the exact number and
     // skips passes beyond it)
-    const int most[2] = {24 + cbits, 3 * std::min(kMortonBits, (62 - cbits) / 3) + cbits};
+    const int most[2] = {24 + cbits, 3 * std::min(kCurveBits, (62 - cbits) / 3) + cbits};
     const int passes = (std::max(most[0], most[1]) + 7) / 8;
     const int tiles = std::max(tiles_of(a.n[0]), tiles_of(a.n[1]));
     if (tiles > 0) {
@@ -1017,6 +1082,7 @@ void launch_views(const ViewArgs &a, const FeatLayout &lay, double kappa, hipStr
         else
             hipLaunchKernelGGL(cluster_kernel<256>, dim3(blocks_for(a.n[1], 256, 1 << 30)), dim3(kClusThreads), 0, s, a,
                                kappa);
+        hipLaunchKernelGGL(plan_kernel, dim3(blocks_for(a.n[1], 256, 1 << 30)), dim3(256), 0, s, a);
     }
 }
 

@@ -60,7 +60,7 @@ struct Neighbourhood {
     bool any;
 };
 
-__device__ __forceinline__ Neighbourhood neighbourhood(const double *Pm, const double4 g, double rc, bool cut,
+__device__ __forceinline__ Neighbourhood neighbourhood(const double *Pm, const Geo &g, double rc, bool cut,
                                                        const GridDesc &gd)
 {
     Neighbourhood nb;
@@ -75,6 +75,49 @@ __device__ __forceinline__ Neighbourhood neighbourhood(const double *Pm, const d
                  axis_range(nb.cy, nb.Rm, gd.oy, gd.inv_h, gd.ny, nb.iy0, nb.iy1) &&
                  axis_range(nb.cz, nb.Rm, gd.oz, gd.inv_h, gd.nz, nb.iz0, nb.iz1);
     return nb;
+}
+
+// The cells of one grid row (iy, iz) along x that the cull ball reaches: rows
+// of the ball's bounding box that the ball misses, and the ends of the others,
+// hold about a fifth of the box's points on a surface.
+// In units of cells relative to the centre's cell, in FP32 (small integers
+// and fractions): the radius is longer, and a row's half width again, by 1e-5
+// of itself and 1e-3 of a cell, far more than the rounding here or in the binning.
+// A ball of millions of cells, whose ends an int may not hold, is not trimmed.
+// Pair pass on RGB-D 40,000 at ell 0.1: 75 -> 68 us.
+struct BallRows {
+    int cx, cy, cz;      // cell of the centre
+    float fx, fy, fz;    // its place in it, in [0, 1)
+    float R2;            // squared radius
+    bool trim;
+};
+
+__device__ __forceinline__ BallRows ball_rows(const Neighbourhood &nb, const GridDesc &gd, bool cut)
+{
+    BallRows r;
+    const double x = (nb.cx - gd.ox) * gd.inv_h, y = (nb.cy - gd.oy) * gd.inv_h, z = (nb.cz - gd.oz) * gd.inv_h;
+    const double ix = floor(x), iy = floor(y), iz = floor(z);
+    r.cx = (int)ix; r.cy = (int)iy; r.cz = (int)iz;
+    r.fx = (float)(x - ix); r.fy = (float)(y - iy); r.fz = (float)(z - iz);
+    const float R = (float)(nb.Rm * gd.inv_h * (1.0 + 1e-5)) + 1e-3f;
+    r.R2 = R * R;
+    r.trim = cut && R < 2097152.0f;
+    return r;
+}
+
+// [i0, i1] within [nb.ix0, nb.ix1]; false if the ball misses the row
+__device__ __forceinline__ bool row_cells(const Neighbourhood &nb, const BallRows &b, int iy, int iz, int &i0, int &i1)
+{
+    i0 = nb.ix0;
+    i1 = nb.ix1;
+    if (!b.trim) return true;
+    const float y = (float)(iy - b.cy) - b.fy, z = (float)(iz - b.cz) - b.fz;  // the row's near edges
+    const float dy = fmaxf(fmaxf(y, -1.0f - y), 0.0f), dz = fmaxf(fmaxf(z, -1.0f - z), 0.0f);
+    const float w2 = fmaf(-dz, dz, fmaf(-dy, dy, b.R2));
+    const float w = fmaf(__builtin_amdgcn_sqrtf(fmaxf(w2, 0.0f)), 1.0f + 1e-5f, 1e-3f);
+    i0 = max(nb.ix0, b.cx + (int)floorf(b.fx - w));
+    i1 = min(nb.ix1, b.cx + (int)floorf(b.fx + w));
+    return w2 >= 0.0f && i0 <= i1;
 }
 
 }  // namespace cvo

@@ -10,7 +10,7 @@
 //                  row-major index of a uniform cell grid; a dense table
 //                  cell_start[k] = first sorted index with cell >= k, so a
 //                  run of cells along x is one contiguous index range.
-//     cluster view (query side): points sorted by a Morton code; a cluster is
+//     cluster view (query side): points sorted along a Hilbert curve; a cluster is
 //                  a run of at most cluster_max consecutive points (an aligned
 //                  octree block, or part of a fixed-size chunk), with its
 //                  centre and radius in the cloud's own frame.  A
@@ -34,9 +34,18 @@ constexpr int kRadixTile = 1024;  // keys per workgroup and pass of the radix so
 constexpr int kTableTiles = 128;  // sorts of at most this many tiles keep a digit table per pass (one launch a pass)
 constexpr int kMaxPasses = 8;     // 8-bit passes over a 64-bit key
 constexpr long long kCellCap = 1LL << 23;  // cells of one cloud's grid
-constexpr int kMortonBits = 16;   // Morton bits per axis
+constexpr int kCurveBits = 16;    // bits per axis of the query order's curve
 constexpr int kBoxBlocks = 64;    // partial bounding boxes per cloud
-constexpr int kMinPieceCand = 512;  // candidates of a piece, at least
+// Candidates of a piece, at least: as many as leave about kPieceTarget pieces,
+// within [kPieceFew, kPieceMany].  The chip holds 4,096-5,120 waves of the pair
+// pass at once.  With fewer pieces than that the longest piece is the pass, so
+// short pieces win; with many more, a piece's fixed cost and its partials do.
+// Pair pass + reduction, us, at least 512 / 256 / 128 candidates / this rule:
+// stereo 15,000 at ell 0.1 37.9 / 27.0 / 22.6 / 22.3, 30,000 at 0.1 41.6 / 31.5 /
+// 34.2 / 31.3, 30,000 at 0.95 208 / 233 / 266 / 212, RGB-D 10,000 at 0.1 33.6 /
+// 25.0 / 22.3 / 21.8, 40,000 at 0.1 75 / 81 / 99 / 75.  kPieceTarget 8,000 / 6,000
+// / 5,000: stereo 8,000 at 0.95 41.6 / 37.5 / 37.2 against 37.2 here.
+constexpr int kPieceFew = 128, kPieceMany = 512, kPieceTarget = 4000;
 constexpr int kRedVals = 48;     // values reduced per pair by the reduction kernel
 constexpr int kRedThreads = 256;
 
@@ -46,6 +55,7 @@ enum Status { ST_RUNNING = 0, ST_CONVERGED = 1, ST_MAX_ITER = 2, ST_NO_OVERLAP =
 // is issued here (with the others of its round) and not sunk past a branch.
 __device__ __forceinline__ void in_sgpr(int v) { asm volatile("" ::"s"(v)); }
 __device__ __forceinline__ void in_sgpr(double v) { asm volatile("" ::"s"(v)); }
+__device__ __forceinline__ void in_sgpr(float v) { asm volatile("" ::"s"(v)); }
 __device__ __forceinline__ void in_sgpr(long long v) { asm volatile("" ::"s"(v)); }
 
 // Per-pair registration state, resident on the device for the whole ascent.
@@ -128,7 +138,7 @@ struct alignas(16) PairIn {
 
 // Cluster parameters of one pair, derived from its query cloud's box.
 struct alignas(16) ClusterParam {
-    double ox, oy, oz;     // Morton origin
+    double ox, oy, oz;     // origin of the curve's cube
     double iq;             // 1 / quantum (edge of a level-0 block)
     double cap;            // largest cluster bounding-box edge (chunk rule)
     int level;             // largest octree level of a cluster (octree rule)
@@ -144,7 +154,8 @@ struct BuildInfo {
     int bad;                   // a cloud has a non-finite coordinate
     int overflow;              // the cell tables do not fit: nothing after the boxes was done
     int nclus;                 // clusters of all pairs
-    int kbits, mbits;          // cell-index bits, Morton bits per axis (the pair index sits above)
+    unsigned long long cand;   // candidates of all clusters
+    int kbits, mbits;          // cell-index bits, curve bits per axis (the pair index sits above)
     int sbits[2];              // key bits to sort: reference side, query side
     int hist[kCostBuckets];    // pieces per cost bucket
 };
@@ -166,13 +177,21 @@ struct alignas(64) HostMail {
     PairState state[kMailStates];
 };
 
+// Geometry of a cluster in its own frame: the centre of its bounding box and
+// the radius of its points about it.
+struct Geo {
+    double x, y, z, w;
+};
+
 // One cluster as planned: its geometry, its points, its pieces and slots.
-struct alignas(64) ClusterRec {
-    double4 geo;               // centre (own frame) and radius
+struct alignas(16) ClusterRec {
+    Geo geo;
     int first, n;              // sorted points [first, first + n)
+    int cand;                  // candidates at the planning pose
     int np, slot;              // pieces, first output slot
     int b, inverse;            // pair, pose orientation
     int code, place;           // cost bucket of its pieces, their place in it
+    int pad[3];
 };
 
 // Feature layout after combining the spec's blocks: all SE columns first
@@ -204,11 +223,11 @@ struct FeatLayout {
 // planning time so the wave's prologue is one load: the piece (cluster's
 // first point, p, np, first output slot), its pair, its cluster's points and
 // geometry.
-struct alignas(32) PieceRec {
+struct alignas(16) PieceRec {
     int4 pc;
     int b, first, n;
     int inverse;  // nonzero: queries are X points (pose T^-1)
-    double4 geo;
+    Geo geo;
 };
 
 struct PairPassArgs {

@@ -11,9 +11,9 @@
 //   * Lanes are split into SUB = 64 / n' sub-streams (n' = n rounded up to a
 //     power of two); lane (q, t) pairs query t with every SUB-th candidate, so
 //     all 64 lanes stay busy for clusters of any size.
-//   * Candidates are the reference points in the grid cells overlapping the
-//     box around the ball of radius r_c + rho (rho: cluster radius).  The
-//     box's x-runs of cells are contiguous in the sorted reference array; up
+//   * Candidates are the reference points in the grid cells that the ball of
+//     radius r_c + rho (rho: cluster radius) reaches.  Their
+//     x-runs of cells are contiguous in the sorted reference array; up
 //     to 64 runs are measured at once (one per lane), prefix-summed, and
 //     their points loaded 64 at a time (each position finds its run by a
 //     running max over the runs' first positions; both scans use DPP, not
@@ -50,26 +50,36 @@ __device__ __forceinline__ double uniform_d(double v)
     return __longlong_as_double(((long long)hi << 32) | (unsigned int)lo);
 }
 
+// The largest power of two that is at most v (v > 0, normal).
+__device__ __forceinline__ double pow2_below(double v)
+{
+    return __longlong_as_double(__double_as_longlong(v) & 0x7ff0000000000000LL);
+}
+
 // Membership of (x, z) in the pair set, decided exactly as the set is defined:
 // z'_r = ((R_r0 z0 + R_r1 z1) + R_r2 z2) + t_r, d = x - z',
 // s = (dx dx + dy dy) + dz dz, member iff s <= rc2; every operation is a
 // separately rounded IEEE double (contraction into FMA is switched off).
-__device__ __noinline__ bool canonical_member(const double *T, float x0, float x1, float x2, float z0,
-                                              float z1, float z2, double rc2)
+// One axis per loop trip, coordinates read from memory: this path is rare, and
+// its registers (or a call's) would otherwise add to those of the loop around it.
+__device__ __forceinline__ bool canonical_member(const double *T, const float4 *xp, const float4 *zp, double rc2)
 {
 #pragma clang fp contract(off)
-    const double a0 = (double)z0, a1 = (double)z1, a2 = (double)z2;
-    double zt[3];
+    const float *x = reinterpret_cast<const float *>(xp);
+    const float *z = reinterpret_cast<const float *>(zp);
+    double s = 0.0;
+#pragma unroll 1
     for (int r = 0; r < 3; ++r) {
-        const double p = T[4 * r + 0] * a0;
-        const double q = T[4 * r + 1] * a1;
-        const double u = T[4 * r + 2] * a2;
-        zt[r] = ((p + q) + u) + T[4 * r + 3];
+        double t = T[4 * r + 0] * (double)z[0];
+        const double q = T[4 * r + 1] * (double)z[1];
+        t = t + q;
+        const double u = T[4 * r + 2] * (double)z[2];
+        t = t + u;
+        t = t + T[4 * r + 3];
+        const double d = (double)x[r] - t;
+        const double dd = d * d;
+        s = (r == 0) ? dd : s + dd;
     }
-    const double dx = (double)x0 - zt[0];
-    const double dy = (double)x1 - zt[1];
-    const double dz = (double)x2 - zt[2];
-    const double s = (dx * dx + dy * dy) + dz * dz;
     return s <= rc2;
 }
 
@@ -126,7 +136,7 @@ void pair_pass_kernel(const PairPassArgs a)
         for (int k = 0; k < 12; ++k) Pm[k] = P[k];
         const double ell = st->ell;
         const int2 cl = make_int2(rec.first, rec.n);
-        const double4 g = rec.geo;
+        const Geo g = rec.geo;
         const GridDesc gd = a.grids[b];
         __builtin_amdgcn_sched_barrier(0);  // (the exit test below must not be scheduled between these loads)
         const int skip = st->done | st->pause;
@@ -170,7 +180,17 @@ void pair_pass_kernel(const PairPassArgs a)
         const double rc = a.kappa * ell;
         const double rc2 = rc * rc;
         const Neighbourhood nb = neighbourhood(Pm, g, rc, cut, gd);
-        const double cx = uniform_d(nb.cx), cy = uniform_d(nb.cy), cz = uniform_d(nb.cz);
+        // Coordinates are taken relative to the transformed centre rounded to
+        // a grid of at most 1/256 of the cutoff (a power of two): the FP32
+        // offsets of the reference points then stay what they are while the
+        // pose moves by less than that, instead of being rounded anew each
+        // iteration, and with the queries' rounding taken off D at the end
+        // the gradient is smooth in the pose.
+        const double q0 = pow2_below(fmax((cut ? rc : ell) * (1.0 / 256.0), 1e-240));
+        const double q1 = 1.0 / q0;
+        const double cx = uniform_d(rint(nb.cx * q1) * q0), cy = uniform_d(rint(nb.cy * q1) * q0),
+                     cz = uniform_d(rint(nb.cz * q1) * q0);
+        const double Rq = nb.Rm + q0;  // cull radius about that point
 
         // thresholds in scaled units: s' <= lo is certainly in P, s' > hi is
         // certainly out; between them the FP64 definition decides.  The band
@@ -179,13 +199,12 @@ void pair_pass_kernel(const PairPassArgs a)
         float hi = INFINITY, lo = INFINITY, cull2 = INFINITY;
         if (cut) {
             const double u = 5.9604644775390625e-8;
-            const double G = u * (8.0 * (4.0 * (1.0 + g.w / rc) + 3.0) + 4.0);
+            const double G = u * (8.0 * (4.0 * (1.0 + (g.w + q0) / rc) + 3.0) + 4.0);
             const double r2s = rc2 * ascale;
             hi = uniform_f((float)(r2s * (1.0 + G)));
             lo = uniform_f((float)(r2s * (1.0 - G)));
-            cull2 = uniform_f((float)(nb.Rm * nb.Rm * ascale));
+            cull2 = uniform_f((float)(Rq * Rq * ascale));
         }
-
         const double zpx = Pm[0] * zq.x + Pm[1] * zq.y + Pm[2] * zq.z + Pm[3];
         const double zpy = Pm[4] * zq.x + Pm[5] * zq.y + Pm[6] * zq.z + Pm[7];
         const double zpz = Pm[8] * zq.x + Pm[9] * zq.y + Pm[10] * zq.z + Pm[11];
@@ -211,11 +230,8 @@ void pair_pass_kernel(const PairPassArgs a)
             if (valid && active && s <= hi) {
                 bool pass = true;
                 if (s > lo) {
-                    const float4 rp = a.rpts[__float_as_int(ent[0].w)];
-                    const float4 zq2 = a.qpts[pq];
-                    pass = inverse
-                               ? canonical_member(st->T, zq2.x, zq2.y, zq2.z, rp.x, rp.y, rp.z, rc2)
-                               : canonical_member(st->T, rp.x, rp.y, rp.z, zq2.x, zq2.y, zq2.z, rc2);
+                    const float4 *rp = a.rpts + __float_as_int(ent[0].w), *qp = a.qpts + pq;
+                    pass = canonical_member(st->T, inverse ? qp : rp, inverse ? rp : qp, rc2);
                 }
                 if (pass) {
                     float E = s;
@@ -321,17 +337,20 @@ void pair_pass_kernel(const PairPassArgs a)
         if (nb.any) {
             const int nyr = nb.iy1 - nb.iy0 + 1;
             const int nrows = nyr * (nb.iz1 - nb.iz0 + 1);
-            const int run = nb.ix1 - nb.ix0 + 1;
+            const BallRows br = ball_rows(nb, gd, cut);
             int base = 0;  // candidates in earlier row batches
             for (int rb = 0; rb < nrows; rb += kWave) {
                 const int r = rb + lane;
                 int rs = 0, len = 0;
                 if (r < nrows) {
                     const int iy = nb.iy0 + r % nyr, iz = nb.iz0 + r / nyr;
-                    const long long k0 =
-                        (long long)gd.cell_base + nb.ix0 + (long long)gd.nx * (iy + (long long)gd.ny * iz);
-                    rs = a.cell_start[k0];
-                    len = a.cell_start[k0 + run] - rs;
+                    int i0, i1;
+                    if (row_cells(nb, br, iy, iz, i0, i1)) {
+                        const long long k0 =
+                            (long long)gd.cell_base + (long long)gd.nx * (iy + (long long)gd.ny * iz);
+                        rs = a.cell_start[k0 + i0];
+                        len = a.cell_start[k0 + i1 + 1] - rs;
+                    }
                 }
                 const int incl = wave_scan_add(len);
                 const int total = __builtin_amdgcn_readlane(incl, kWave - 1);
@@ -397,6 +416,12 @@ void pair_pass_kernel(const PairPassArgs a)
 #pragma unroll
             for (int k = 0; k < SED; ++k) Gf[MODE == 1 ? k : 0] -= Wd * (double)vf[k];
         }
+        float4 ze = make_float4(0.f, 0.f, 0.f, 0.f);
+        if (MODE == 0) {  // the query's point again: it need not stay in registers over the walk
+            int pe = pq;
+            asm volatile("" : "+v"(pe));
+            ze = a.qpts[pe];
+        }
         // combine the sub-streams of each query (fixed shuffle order)
         for (int off = np2; off < kWave; off <<= 1) {
             W += __shfl_xor(W, off);
@@ -418,6 +443,18 @@ void pair_pass_kernel(const PairPassArgs a)
             }
         }
         if (qs == 0 && active) {
+            if (MODE == 0 && W != 0.0) {
+                // the query's rounding (e: rounded less exact) taken off D to
+                // first order: dD/dz = -(W I - 2 ln 2 sum w d d^T).  What is
+                // left of the gradient's error is the reference points' rounding.
+                const double ex = (double)zrx - (Pm[0] * ze.x + Pm[1] * ze.y + Pm[2] * ze.z + Pm[3] - cx) * sc;
+                const double ey = (double)zry - (Pm[4] * ze.x + Pm[5] * ze.y + Pm[6] * ze.z + Pm[7] - cy) * sc;
+                const double ez = (double)zrz - (Pm[8] * ze.x + Pm[9] * ze.y + Pm[10] * ze.z + Pm[11] - cz) * sc;
+                const double l2 = 2.0 * 0.6931471805599453;
+                Dx += W * ex - l2 * (S00 * ex + S01 * ey + S02 * ez);
+                Dy += W * ey - l2 * (S01 * ex + S11 * ey + S12 * ez);
+                Dz += W * ez - l2 * (S02 * ex + S12 * ey + S22 * ez);
+            }
             // every output is linear in the kernel weights; written value by
             // value over the cluster's queries
             const double sg = (double)sig2;
