@@ -104,13 +104,10 @@ void pair_pass_kernel(const PairPassArgs a)
     // the feature row
     constexpr int E4 = 1 + F4;
     __shared__ float4 s_q[kWavesPerBlock][kQueueCap * E4];
-    __shared__ int s_rs[kWavesPerBlock][kWave];
-    __shared__ int s_rx[kWavesPerBlock][kWave];
     __shared__ int s_row[kWavesPerBlock][kWave];
 
     const int lane = threadIdx.x & (kWave - 1);
     const int wv = threadIdx.x / kWave;
-    const unsigned long long lt_mask = (lane == 0) ? 0ULL : (~0ULL >> (64 - lane));
     const float sig2 = a.sig2;
     const bool cut = isfinite(a.kappa);
 
@@ -205,6 +202,7 @@ void pair_pass_kernel(const PairPassArgs a)
             lo = uniform_f((float)(r2s * (1.0 - G)));
             cull2 = uniform_f((float)(Rq * Rq * ascale));
         }
+        if (!active) hi = -1.0f;  // (takes no pair)
         const double zpx = Pm[0] * zq.x + Pm[1] * zq.y + Pm[2] * zq.z + Pm[3];
         const double zpy = Pm[4] * zq.x + Pm[5] * zq.y + Pm[6] * zq.z + Pm[7];
         const double zpz = Pm[8] * zq.x + Pm[9] * zq.y + Pm[10] * zq.z + Pm[11];
@@ -223,19 +221,72 @@ void pair_pass_kernel(const PairPassArgs a)
         // W and D are summed in FP32 over one queue flush (at most kQueueCap
         // terms per lane) and added to the FP64 accumulators after it.
         float w32 = 0.f, dx32 = 0.f, dy32 = 0.f, dz32 = 0.f;
-        // one candidate entry (at `ent`; its offset d from the query and
-        // squared distance s already taken) against this lane's query;
-        // `valid` false only in the tail of a flush, for lanes past its end
-        auto pair_term = [&](float dx, float dy, float dz, float s, const float4 *ent, bool valid) {
-            if (valid && active && s <= hi) {
-                bool pass = true;
-                if (s > lo) {
+        // One candidate entry (at `ent`; its offset d from the query and
+        // squared distance s already taken) against this lane's query.  The
+        // lanes that take it are held as a mask, so a comparison's result is
+        // used as the wave writes it: the count is a scalar one, the rare
+        // exact check a scalar branch.  (The FP32 VALU issues 90% of the time
+        // in dense bands, so instructions are what counts: 38 -> 33 per pair
+        // with five SE columns, with the loop below.  30,000 stereo points,
+        // ell 0.95: 202 -> 188 us; 40,000 RGB-D, 0.1: 68 -> 64 us.)
+        // `valid`: the lanes that have an entry (all but in the tail of a flush).
+        auto pair_term = [&](float dx, float dy, float dz, float s, const float4 *ent, unsigned long long valid) {
+            unsigned long long take = __builtin_amdgcn_ballot_w64(s <= hi) & valid;
+            const unsigned long long near = __builtin_amdgcn_ballot_w64(s > lo) & take;
+            if (near) {
+                bool in = true;
+                if (__builtin_amdgcn_inverse_ballot_w64(near)) {
                     const float4 *rp = a.rpts + __float_as_int(ent[0].w), *qp = a.qpts + pq;
-                    pass = canonical_member(st->T, inverse ? qp : rp, inverse ? rp : qp, rc2);
+                    in = canonical_member(st->T, inverse ? qp : rp, inverse ? rp : qp, rc2);
                 }
-                if (pass) {
-                    float E = s;
-                    float lin = 0.0f, lin1 = 0.0f;  // even / odd LIN columns: two shorter FMA chains
+                take &= __builtin_amdgcn_ballot_w64(in);
+            }
+            cnt += __popcll(take);
+            if (__builtin_amdgcn_inverse_ballot_w64(take)) {
+                float E = s;
+                float lin = 0.0f, lin1 = 0.0f;  // even / odd LIN columns: two shorter FMA chains
+#pragma unroll
+                for (int f = 0; f < F4; ++f) {
+                    const float4 u4 = ent[1 + f];
+                    const float uu[4] = {u4.x, u4.y, u4.z, u4.w};
+#pragma unroll
+                    for (int q = 0; q < 4; ++q) {
+                        const int d = 4 * f + q;
+                        if (d < SED) {
+                            const float df = uu[q] - vf[d];
+                            E = fmaf(df, df, E);
+                        } else if (d < D) {
+                            if ((d - SED) & 1) lin1 = fmaf(uu[q], vf[d], lin1);
+                            else lin = fmaf(uu[q], vf[d], lin);
+                        }
+                    }
+                }
+                lin += lin1;
+                // sigma^2 prod sigma_b^2 is applied once per query at the end
+                const float wnl = __builtin_amdgcn_exp2f(-E);
+                const float w = (LIND > 0) ? wnl * lin : wnl;
+                w32 += w;
+                const float wx = w * dx, wy = w * dy, wz = w * dz;
+                dx32 += wx;
+                dy32 += wy;
+                dz32 += wz;
+                if (MODE == 0) {
+                    S00 = fmaf(wx, dx, S00);
+                    S01 = fmaf(wx, dy, S01);
+                    S02 = fmaf(wx, dz, S02);
+                    S11 = fmaf(wy, dy, S11);
+                    S12 = fmaf(wy, dz, S12);
+                    S22 = fmaf(wz, dz, S22);
+                } else {
+                    // FP64 products and sums: one conversion and one FMA per
+                    // column.  SE columns sum w u here and take v W off at
+                    // the end (W summed in FP64 for it): sum w (u - v).
+                    // 5 SE + 19 LIN, 30,000 points, both sides: 763 -> 723 us
+                    // at ell 0.95, 149 -> 144 us at 0.25 against an FP32
+                    // product, a conversion and an add per column
+                    const double wd = (double)w, wn = (double)wnl;
+                    Wd += wd;
+                    Ls = fma(wd, (double)s, Ls);
 #pragma unroll
                     for (int f = 0; f < F4; ++f) {
                         const float4 u4 = ent[1 + f];
@@ -243,84 +294,41 @@ void pair_pass_kernel(const PairPassArgs a)
 #pragma unroll
                         for (int q = 0; q < 4; ++q) {
                             const int d = 4 * f + q;
-                            if (d < SED) {
-                                const float df = uu[q] - vf[d];
-                                E = fmaf(df, df, E);
-                            } else if (d < D) {
-                                if ((d - SED) & 1) lin1 = fmaf(uu[q], vf[d], lin1);
-                                else lin = fmaf(uu[q], vf[d], lin);
-                            }
-                        }
-                    }
-                    lin += lin1;
-                    // sigma^2 prod sigma_b^2 is applied once per query at the end
-                    const float wnl = __builtin_amdgcn_exp2f(-E);
-                    const float w = (LIND > 0) ? wnl * lin : wnl;
-                    w32 += w;
-                    const float wx = w * dx, wy = w * dy, wz = w * dz;
-                    dx32 += wx;
-                    dy32 += wy;
-                    dz32 += wz;
-                    cnt += 1;
-                    if (MODE == 0) {
-                        S00 = fmaf(wx, dx, S00);
-                        S01 = fmaf(wx, dy, S01);
-                        S02 = fmaf(wx, dz, S02);
-                        S11 = fmaf(wy, dy, S11);
-                        S12 = fmaf(wy, dz, S12);
-                        S22 = fmaf(wz, dz, S22);
-                    } else {
-                        // FP64 products and sums: one conversion and one FMA per
-                        // column.  SE columns sum w u here and take v W off at
-                        // the end (W summed in FP64 for it): sum w (u - v).
-                        // 5 SE + 19 LIN, 30,000 points, both sides: 763 -> 723 us
-                        // at ell 0.95, 149 -> 144 us at 0.25 against an FP32
-                        // product, a conversion and an add per column
-                        const double wd = (double)w, wn = (double)wnl;
-                        Wd += wd;
-                        Ls = fma(wd, (double)s, Ls);
-#pragma unroll
-                        for (int f = 0; f < F4; ++f) {
-                            const float4 u4 = ent[1 + f];
-                            const float uu[4] = {u4.x, u4.y, u4.z, u4.w};
-#pragma unroll
-                            for (int q = 0; q < 4; ++q) {
-                                const int d = 4 * f + q;
-                                if (MODE == 1 && d < D) Gf[d] = fma(d < SED ? wd : wn, (double)uu[q], Gf[d]);
-                            }
+                            if (MODE == 1 && d < D) Gf[d] = fma(d < SED ? wd : wn, (double)uu[q], Gf[d]);
                         }
                     }
                 }
             }
         };
         // Lane (q, t) walks entries q, q + SUB, ...: first the rows of SUB
-        // entries that every sub-stream has (a wave-uniform loop, the next
-        // entry's coordinates read while this one is used), then the last,
-        // partial row.
+        // entries that every sub-stream has, two per trip of a wave-uniform
+        // loop (the next entry's coordinates read while this one is used, in
+        // registers that take turns), then what is left, row by row.
         auto process = [&](int qn_) {
             w32 = 0.f, dx32 = 0.f, dy32 = 0.f, dz32 = 0.f;
             const int qn = wave_uniform(qn_);
             const int nfull = wave_uniform(qn >> (6 - lg));  // qn / SUB
             const float4 *ent = &s_q[wv][qs * E4];
             const int step = SUB * E4;
-            float4 e = ent[0];
-            for (int it = 0; it < nfull; ++it) {
-                const float dx = e.x - zrx, dy = e.y - zry, dz = e.z - zrz;
-                const float s = fmaf(dz, dz, fmaf(dy, dy, dx * dx));
-                const float4 *cur = ent;
-                ent += (it + 1 < nfull) ? step : 0;  // (the last row re-reads itself)
-                e = *ent;
-                pair_term(dx, dy, dz, s, cur, true);
-            }
-            const int done = wave_uniform(nfull << (6 - lg));
-            if (done < qn) {
-                const int kt = qs + done;
-                const bool in = kt < qn;
-                const float4 *tl = &s_q[wv][(in ? kt : 0) * E4];
-                const float4 c = *tl;
+            auto one = [&](const float4 c, const float4 *at, unsigned long long in) {
                 const float dx = c.x - zrx, dy = c.y - zry, dz = c.z - zrz;
                 const float s = fmaf(dz, dz, fmaf(dy, dy, dx * dx));
-                pair_term(dx, dy, dz, s, tl, in);
+                pair_term(dx, dy, dz, s, at, in);
+            };
+            float4 e0 = ent[0];
+            for (int it = 0; it < nfull - 1; it += 2) {
+                const float4 *odd = ent + step;
+                const float4 e1 = *odd;
+                one(e0, ent, ~0ULL);
+                ent = odd + ((it + 3 < nfull) ? step : 0);  // (the last pair re-reads its second row)
+                e0 = *ent;
+                one(e1, odd, ~0ULL);
+            }
+            for (int k0 = wave_uniform((nfull & ~1) << (6 - lg)); k0 < qn; k0 += SUB) {
+                const int kt = qs + k0;
+                const bool in = kt < qn;
+                const float4 *tl = &s_q[wv][(in ? kt : 0) * E4];
+                one(*tl, tl, __builtin_amdgcn_ballot_w64(in));
             }
             W += (double)w32;
             Dx += (double)dx32;
@@ -358,14 +366,11 @@ void pair_pass_kernel(const PairPassArgs a)
                 int k = base / kWave;
                 k += ((pidx - k) % pstride + pstride) % pstride;
                 if (k * kWave < base + total) {
-                    s_rs[wv][lane] = rs;
-                    s_rx[wv][lane] = incl - len;
                     s_row[wv][lane] = 0;  // marks left by earlier chunks of this batch never exceed a later chunk's rows
                     wave_sync();
                     for (; k * kWave < base + total; k += pstride) {
                         // the part of chunk k inside this batch of rows
                         const int m = k * kWave - base + lane;
-                        bool keep = false;
                         int src = 0;
                         float x0 = 0.f, x1 = 0.f, x2 = 0.f;
                         // the row (cell run) of each position of the chunk: every
@@ -380,21 +385,25 @@ void pair_pass_kernel(const PairPassArgs a)
                         }
                         wave_sync();
                         const int row_ = wave_scan_max(s_row[wv][lane]);
-                        if (m >= 0 && m < total) {
-                            src = s_rs[wv][row_] + (m - s_rx[wv][row_]);
+                        const int first = __shfl(rs - (incl - len), row_);  // its points start at first + (position)
+                        const unsigned long long in_row = __builtin_amdgcn_ballot_w64((unsigned)m < (unsigned)total);
+                        float r2 = 0.f;
+                        if (__builtin_amdgcn_inverse_ballot_w64(in_row)) {
+                            src = first + m;
                             const float4 xp = a.rpts[src];
                             x0 = (float)(((double)xp.x - cx) * sc);
                             x1 = (float)(((double)xp.y - cy) * sc);
                             x2 = (float)(((double)xp.z - cz) * sc);
-                            keep = fmaf(x2, x2, fmaf(x1, x1, x0 * x0)) <= cull2;
+                            r2 = fmaf(x2, x2, fmaf(x1, x1, x0 * x0));
                         }
-                        const unsigned long long mask = __ballot(keep);
-                        if (keep) {
-                            const int slot = qn + __popcll(mask & lt_mask);
-                            s_q[wv][slot * E4] = make_float4(x0, x1, x2, __int_as_float(src));
+                        const unsigned long long mask = __builtin_amdgcn_ballot_w64(r2 <= cull2) & in_row;
+                        if (__builtin_amdgcn_inverse_ballot_w64(mask)) {
+                            const int slot = __builtin_amdgcn_mbcnt_hi((unsigned)(mask >> 32),
+                                                                       __builtin_amdgcn_mbcnt_lo((unsigned)mask, qn));
+                            s_q[wv][__umul24(slot, E4)] = make_float4(x0, x1, x2, __int_as_float(src));
                             const float4 *fr = reinterpret_cast<const float4 *>(a.rfeat) + (long long)src * F4;
 #pragma unroll
-                            for (int f = 0; f < F4; ++f) s_q[wv][slot * E4 + 1 + f] = fr[f];
+                            for (int f = 0; f < F4; ++f) s_q[wv][__umul24(slot, E4) + 1 + f] = fr[f];
                         }
                         qn += __popcll(mask);
                         wave_sync();
@@ -428,7 +437,6 @@ void pair_pass_kernel(const PairPassArgs a)
             Dx += __shfl_xor(Dx, off);
             Dy += __shfl_xor(Dy, off);
             Dz += __shfl_xor(Dz, off);
-            cnt += __shfl_xor(cnt, off);
             if (MODE == 0) {
                 S00 += __shfl_xor(S00, off);
                 S01 += __shfl_xor(S01, off);
@@ -472,7 +480,7 @@ void pair_pass_kernel(const PairPassArgs a)
                 S[3 * n] = sig2 * S11;
                 S[4 * n] = sig2 * S12;
                 S[5 * n] = sig2 * S22;
-                a.oCnt[f + t] = cnt;
+                a.oCnt[f + t] = t == 0 ? cnt : 0;  // counted for the wave
             } else {
                 double *B = a.oB + f * (4 + D4) + t;
                 B[0] = sg * Dx;

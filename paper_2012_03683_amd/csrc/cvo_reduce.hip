@@ -404,7 +404,10 @@ __global__ __launch_bounds__(kRedThreads) void reduce_kernel(const ReduceArgs a)
                 if (left <= 0) break;
             }
         }
-        if (nj == 0) return;
+        acc[R_N] += (double)nj;  // (a piece's pairs are all counted at its first query)
+        if (Wt == 0.0 && D0 == 0.0 && D1 == 0.0 && D2 == 0.0 && S0 == 0.0 && S1 == 0.0 && S2 == 0.0 && S3 == 0.0 &&
+            S4 == 0.0 && S5 == 0.0)
+            return;
         const double Dt[3] = {D0 * isc, D1 * isc, D2 * isc};
         const double S6[6] = {S0 * ia, S1 * ia, S2 * ia, S3 * ia, S4 * ia, S5 * ia};
         acc[R_F] += Wt;
@@ -415,7 +418,6 @@ __global__ __launch_bounds__(kRedThreads) void reduce_kernel(const ReduceArgs a)
         for (int k = 0; k < 3; ++k) acc[R_V + k] += Dt[k];
         const double trs = S6[0] + S6[3] + S6[5];
         acc[R_TRS] += trs;
-        acc[R_N] += (double)nj;
         if (a.ellobj && Wt > 0.0) {
             acc[R_LOGW] += log(Wt);
             acc[R_RSUM] += trs / Wt;
