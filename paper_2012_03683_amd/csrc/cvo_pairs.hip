@@ -347,6 +347,10 @@ void pair_pass_kernel(const PairPassArgs a)
             const int nrows = nyr * (nb.iz1 - nb.iz0 + 1);
             const BallRows br = ball_rows(nb, gd, cut);
             int base = 0;  // candidates in earlier row batches
+            // (the query's features have arrived: waited for here, not by the
+            // pair loop, whose wait would take in the next chunk's points)
+#pragma unroll
+            for (int f = 0; f < VF; ++f) asm volatile("" : "+v"(vf[f]));
             for (int rb = 0; rb < nrows; rb += kWave) {
                 const int r = rb + lane;
                 int rs = 0, len = 0;
@@ -368,43 +372,52 @@ void pair_pass_kernel(const PairPassArgs a)
                 if (k * kWave < base + total) {
                     s_row[wv][lane] = 0;  // marks left by earlier chunks of this batch never exceed a later chunk's rows
                     wave_sync();
-                    for (; k * kWave < base + total; k += pstride) {
-                        // the part of chunk k inside this batch of rows
-                        const int m = k * kWave - base + lane;
-                        int src = 0;
-                        float x0 = 0.f, x1 = 0.f, x2 = 0.f;
+                    // The part of chunk k inside this batch of rows: its lanes, and
+                    // their points on the way.  They are asked for before the
+                    // queue is walked for the chunk before (40,000 RGB-D points,
+                    // ell 0.1: 65 -> 63 us).  Holding the features of the chunk
+                    // at hand over that request too costs 8 to 24 registers and
+                    // the occupancy with them (71 us).
+                    unsigned long long in_row = 0;
+                    int src = 0;
+                    float4 xp = make_float4(0.f, 0.f, 0.f, 0.f);
+                    auto fetch = [&]() {
+                        const int c0 = k * kWave - base, m = c0 + lane;
                         // the row (cell run) of each position of the chunk: every
                         // non-empty row reaching into the chunk marks its first
                         // position in it with its index, and a running max over
                         // the positions (on all lanes, before the branch below)
                         // fills in the rest
-                        {
-                            const int c0 = k * kWave - base;
-                            const int rx = incl - len;
-                            if (len > 0 && rx < c0 + kWave && rx + len > c0) s_row[wv][max(rx - c0, 0)] = lane;
-                        }
+                        const int rx = incl - len;
+                        if (len > 0 && rx < c0 + kWave && rx + len > c0) s_row[wv][max(rx - c0, 0)] = lane;
                         wave_sync();
                         const int row_ = wave_scan_max(s_row[wv][lane]);
-                        const int first = __shfl(rs - (incl - len), row_);  // its points start at first + (position)
-                        const unsigned long long in_row = __builtin_amdgcn_ballot_w64((unsigned)m < (unsigned)total);
-                        float r2 = 0.f;
+                        const int first = __shfl(rs - rx, row_);  // its points start at first + (position)
+                        in_row = __builtin_amdgcn_ballot_w64((unsigned)m < (unsigned)total);
                         if (__builtin_amdgcn_inverse_ballot_w64(in_row)) {
                             src = first + m;
-                            const float4 xp = a.rpts[src];
-                            x0 = (float)(((double)xp.x - cx) * sc);
-                            x1 = (float)(((double)xp.y - cy) * sc);
-                            x2 = (float)(((double)xp.z - cz) * sc);
-                            r2 = fmaf(x2, x2, fmaf(x1, x1, x0 * x0));
+                            xp = a.rpts[src];
                         }
+                    };
+                    fetch();
+                    for (;;) {
+                        const float x0 = (float)(((double)xp.x - cx) * sc);
+                        const float x1 = (float)(((double)xp.y - cy) * sc);
+                        const float x2 = (float)(((double)xp.z - cz) * sc);
+                        const float r2 = fmaf(x2, x2, fmaf(x1, x1, x0 * x0));
                         const unsigned long long mask = __builtin_amdgcn_ballot_w64(r2 <= cull2) & in_row;
+                        const int cur = src;
                         if (__builtin_amdgcn_inverse_ballot_w64(mask)) {
                             const int slot = __builtin_amdgcn_mbcnt_hi((unsigned)(mask >> 32),
                                                                        __builtin_amdgcn_mbcnt_lo((unsigned)mask, qn));
-                            s_q[wv][__umul24(slot, E4)] = make_float4(x0, x1, x2, __int_as_float(src));
-                            const float4 *fr = reinterpret_cast<const float4 *>(a.rfeat) + (long long)src * F4;
+                            s_q[wv][__umul24(slot, E4)] = make_float4(x0, x1, x2, __int_as_float(cur));
+                            const float4 *fr = reinterpret_cast<const float4 *>(a.rfeat) + (long long)cur * F4;
 #pragma unroll
                             for (int f = 0; f < F4; ++f) s_q[wv][__umul24(slot, E4) + 1 + f] = fr[f];
                         }
+                        k += pstride;
+                        const bool more = k * kWave < base + total;
+                        if (more) fetch();
                         qn += __popcll(mask);
                         wave_sync();
                         if (qn >= kQueueFlush) {
@@ -412,6 +425,7 @@ void pair_pass_kernel(const PairPassArgs a)
                             qn = 0;
                             wave_sync();
                         }
+                        if (!more) break;
                     }
                     wave_sync();
                 }
