@@ -1592,14 +1592,14 @@ cvo_status cvo_select_points(cvo_handle h, const uint8_t *gray, const float *dep
         a.cap = max_points;
         a.key = h->get_t<short>("sel.key", npix);
         a.score = score;
-        a.hist = h->get_t<int>("sel.hist", 256);
+        a.hist = h->get_t<int>("sel.hist", select_hist_ints());
         a.res = h->get_t<int>("sel.res", 2);
         a.bcount = h->get_t<int>("sel.bcount", nb);
         a.boff = h->get_t<int>("sel.boff", nb);
         a.bsum = h->get_t<int>("sel.bsum", nb / 2048 + 2);
         a.xyz = xyz;
         a.fout = feat_out;
-        HIP_OK(hipMemsetAsync(a.hist, 0, 256 * sizeof(int), h->stream));
+        HIP_OK(hipMemsetAsync(a.hist, 0, select_hist_ints() * sizeof(int), h->stream));
         launch_select(a, h->stream);
         h->check_launch("point selection");
         int res[2];

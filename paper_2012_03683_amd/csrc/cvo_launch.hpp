@@ -119,14 +119,15 @@ struct SelectArgs {
     int cap;               // largest selection allowed
     short *key;            // H x W scratch: score if the pixel has depth, else -1
     short *score;          // H x W scores for the caller (may be null)
-    int *hist;             // 256, zero on entry
+    int *hist;             // select_hist_ints(), zero on entry
     int *res;              // (threshold, count)
-    int *bcount, *boff, *bsum;  // per 256-pixel block counts, their exclusive scan, scan scratch
+    int *bcount, *boff, *bsum;  // counts per select_blocks() block, their exclusive scan, scan scratch
     float *xyz;            // cap x 3
     float *fout;           // cap x D
 };
 void launch_select(const SelectArgs &a, hipStream_t s);
 int select_blocks(long long npix);
+int select_hist_ints();
 void launch_sum_doubles(const double *in, long long n, double *out, hipStream_t s);
 
 }  // namespace cvo

@@ -14,18 +14,30 @@
 //              256-bin histogram of the scores gives every count; the
 //              threshold is the smallest t with count(t) <= cap.
 //
-// Kernels: score + histogram (64 x 4 pixel tiles staged in LDS with a 3-pixel
-// halo), threshold (one workgroup), per-block selected counts, an exclusive
-// scan of those, and the emit pass (wave ballots give each selected pixel its
-// rank).  All integer work, so the selection is exact.
+// Kernels: score + histogram (64 x 16 pixel tiles staged in LDS with a 3-pixel
+// halo), threshold and per-block selected counts, and the emit pass (wave
+// ballots give each selected pixel its rank).  All integer work, so the
+// selection is exact.
+//
+// An image of 1241 x 376 is 3 MB, a few microseconds; what it takes is launches
+// and atomics: with three launches after the clear of the histogram instead of
+// seven, 108 -> 81 us a call.
+#include "cvo_device.hpp"
 #include "cvo_launch.hpp"
 
 namespace cvo {
 
 namespace {
-constexpr int kTX = 64, kTY = 4;  // score tile: one wave per row of the tile
+constexpr int kTX = 64, kTY = 4, kTRows = 16;  // score tile: 64 x 16 pixels, 4 per thread
 constexpr int kHalo = 3;
-constexpr int kSelThreads = 256;
+constexpr int kSelThreads = 256, kSelPix = 1024;  // pixels per workgroup of the count and emit passes
+// Copies of the histogram, by workgroup: adds to one address take about 11 ns
+// each, one after the other (1,880 tiles of 64 x 4 adding to one copy: 20 us).
+constexpr int kHistCopies = 16;
+// Images of at most this many count blocks (2 megapixels): every emit block adds
+// up the counts before it by itself, at most 8 per thread, which is cheaper
+// than the three launches of a scan; larger ones scan.
+constexpr int kDirectBlocks = 2048;
 }  // namespace
 
 __global__ __launch_bounds__(kTX *kTY) void fast_score_kernel(const uint8_t *gray, const float *depth, int W, int H,
@@ -33,28 +45,30 @@ __global__ __launch_bounds__(kTX *kTY) void fast_score_kernel(const uint8_t *gra
                                                                int *hist)
 {
     // int cells: byte cells would put four neighbours in one LDS bank
-    __shared__ int tile[kTY + 2 * kHalo][kTX + 2 * kHalo];
+    __shared__ int tile[kTRows + 2 * kHalo][kTX + 2 * kHalo];
     __shared__ int lh[256];
     const int tx = threadIdx.x, ty = threadIdx.y, tid = ty * kTX + tx;
-    const int u0 = blockIdx.x * kTX, v0 = blockIdx.y * kTY;
+    const int u0 = blockIdx.x * kTX, v0 = blockIdx.y * kTRows;
     lh[tid] = 0;
-    for (int i = tid; i < (kTY + 2 * kHalo) * (kTX + 2 * kHalo); i += kTX * kTY) {
+    for (int i = tid; i < (kTRows + 2 * kHalo) * (kTX + 2 * kHalo); i += kTX * kTY) {
         const int r = i / (kTX + 2 * kHalo), c = i % (kTX + 2 * kHalo);
         const int u = u0 + c - kHalo, v = v0 + r - kHalo;
         tile[r][c] = (u >= 0 && u < W && v >= 0 && v < H) ? (int)gray[(long long)v * W + u] : 0;
     }
     __syncthreads();
-    const int u = u0 + tx, v = v0 + ty;
-    if (u < W && v < H) {
+    const int u = u0 + tx;
+    for (int row = ty; row < kTRows; row += kTY) {
+        const int v = v0 + row;
+        if (u >= W || v >= H) break;
         int s = -1;
         if (u >= kHalo && v >= kHalo && u < W - kHalo && v < H - kHalo) {
             // the radius-3 circle, (du, dv) in circular order
             constexpr int du[16] = {0, 1, 2, 3, 3, 3, 2, 1, 0, -1, -2, -3, -3, -3, -2, -1};
             constexpr int dv[16] = {-3, -3, -2, -1, 0, 1, 2, 3, 3, 3, 2, 1, 0, -1, -2, -3};
-            const int c = tile[ty + kHalo][tx + kHalo];
+            const int c = tile[row + kHalo][tx + kHalo];
             int r[16];
 #pragma unroll
-            for (int k = 0; k < 16; ++k) r[k] = tile[ty + kHalo + dv[k]][tx + kHalo + du[k]];
+            for (int k = 0; k < 16; ++k) r[k] = tile[row + kHalo + dv[k]][tx + kHalo + du[k]];
             // min and max of every circular window of 9: windows of 2, 4, 8, then 9
             int a2[16], b2[16], a4[16], b4[16];
 #pragma unroll
@@ -82,87 +96,133 @@ __global__ __launch_bounds__(kTX *kTY) void fast_score_kernel(const uint8_t *gra
         if (valid && s >= 0) atomicAdd(&lh[s], 1);
     }
     __syncthreads();
-    if (lh[tid]) atomicAdd(&hist[tid], lh[tid]);
+    if (lh[tid]) atomicAdd(&hist[(blockIdx.y * gridDim.x + blockIdx.x) % kHistCopies * 256 + tid], lh[tid]);
 }
 
-// res = (threshold, count): count(t) = sum of hist[s >= t] by a suffix scan;
-// the threshold is the smallest t with count(t) <= cap (hist[255] is always
-// 0, as scores never exceed 254, so t = 255 always qualifies).
-__global__ __launch_bounds__(256) void select_threshold_kernel(const int *hist, int cap, int *res)
+// res = (threshold, count): count(t) = sum of hist[s >= t]; the threshold is
+// the smallest t with count(t) <= cap (hist[255] is always 0, as scores never
+// exceed 254, so t = 255 always qualifies).  Every workgroup finds it for
+// itself (thread i holds count(255 - i), which grows with i) and counts its
+// selected pixels.
+__global__ __launch_bounds__(kSelThreads) void select_count_kernel(const short *key, long long npix, const int *hist,
+                                                                   int cap, int *res, int *bcount)
 {
-    __shared__ int cnt[256];
-    __shared__ int best;
-    const int t = threadIdx.x;
-    cnt[t] = hist[t];
-    if (t == 0) best = 255;
-    __syncthreads();
-    for (int off = 1; off < 256; off <<= 1) {
-        const int add = (t + off < 256) ? cnt[t + off] : 0;
-        __syncthreads();
-        cnt[t] += add;
-        __syncthreads();
+    __shared__ int s_w[4], s_cnt[256];
+    const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
+    int k[kSelPix / kSelThreads];
+#pragma unroll
+    for (int j = 0; j < kSelPix / kSelThreads; ++j) {
+        const long long p = (long long)blockIdx.x * kSelPix + j * kSelThreads + tid;
+        k[j] = p < npix ? (int)key[p] : -1;
     }
-    if (cnt[t] <= cap) atomicMin(&best, t);
+    int h = 0;
+#pragma unroll
+    for (int c = 0; c < kHistCopies; ++c) h += hist[c * 256 + 255 - tid];
+    h = wave_scan_add(h);
+    if (lane == 63) s_w[wv] = h;
     __syncthreads();
-    if (t == 0) {
-        res[0] = best;
-        res[1] = cnt[best];
+    for (int w = 0; w < wv; ++w) h += s_w[w];
+    s_cnt[tid] = h;
+    const int ok = __syncthreads_count(h <= cap);
+    const int t = 256 - ok;
+    int n = 0;
+#pragma unroll
+    for (int j = 0; j < kSelPix / kSelThreads; ++j) n += __syncthreads_count(k[j] >= t);
+    if (tid == 0) {
+        bcount[blockIdx.x] = n;
+        if (blockIdx.x == 0) {
+            res[0] = t;
+            res[1] = s_cnt[ok - 1];
+        }
     }
-}
-
-__global__ __launch_bounds__(kSelThreads) void select_count_kernel(const short *key, long long npix, const int *res,
-                                                                   int *bcount)
-{
-    const long long p = (long long)blockIdx.x * kSelThreads + threadIdx.x;
-    const int t = res[0];
-    const int n = __syncthreads_count(p < npix && key[p] >= t);
-    if (threadIdx.x == 0) bcount[blockIdx.x] = n;
 }
 
 // Row r of the output takes the r-th selected pixel in raster order:
 // z = depth, x = (u - cx) z / fx, y = (v - cy) z / fy, each operation a
 // rounded IEEE double (no contraction), then rounded to FP32; the feature row
 // is copied unchanged.
+// A block's selected pixels are contiguous rows of the output: the features are
+// copied by all threads, value by value.
+template <bool DIRECT>
 __global__ __launch_bounds__(kSelThreads) void select_emit_kernel(const short *key, const float *depth,
                                                                   const float *feat, long long npix, int W, int D,
                                                                   double fx, double fy, double cx, double cy,
-                                                                  const int *res, const int *boff, float *xyz,
+                                                                  const int *res, const int *before, float *xyz,
                                                                   float *fout)
 {
 #pragma clang fp contract(off)
-    __shared__ int wsum[kSelThreads / 64];
-    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
-    const long long p = (long long)blockIdx.x * kSelThreads + threadIdx.x;
+    constexpr int kRows = kSelPix / kSelThreads;
+    __shared__ int s_cnt[kRows][kSelThreads / 64], s_w[kSelThreads / 64];
+    __shared__ int s_pix[kSelPix];
+    const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
+    const long long base = (long long)blockIdx.x * kSelPix;
     const int t = res[0];
-    const bool sel = p < npix && key[p] >= t;
-    const unsigned long long m = __ballot(sel);
-    if (lane == 0) wsum[wv] = __popcll(m);
+    bool sel[kRows];
+    unsigned long long m[kRows];
+#pragma unroll
+    for (int j = 0; j < kRows; ++j) {
+        const long long p = base + j * kSelThreads + tid;
+        sel[j] = p < npix && key[p] >= t;
+        m[j] = __ballot(sel[j]);
+        if (lane == 0) s_cnt[j][wv] = __popcll(m[j]);
+    }
+    long long r0 = 0;  // rows of the blocks before this one
+    if (DIRECT) {
+        int c = 0;
+        for (int i = tid; i < (int)blockIdx.x; i += kSelThreads) c += before[i];
+        c = wave_scan_add(c);
+        if (lane == 63) s_w[wv] = c;
+    } else {
+        r0 = before[blockIdx.x];
+    }
     __syncthreads();
-    if (!sel) return;
-    long long r = boff[blockIdx.x] + __popcll(m & ((1ULL << lane) - 1ULL));
-    for (int w = 0; w < wv; ++w) r += wsum[w];
-    const int u = (int)(p % W), v = (int)(p / W);
-    const float zf = depth[p];
-    const double z = (double)zf;
-    xyz[3 * r + 0] = (float)((((double)u - cx) * z) / fx);
-    xyz[3 * r + 1] = (float)((((double)v - cy) * z) / fy);
-    xyz[3 * r + 2] = zf;
-    for (int k = 0; k < D; ++k) fout[r * D + k] = feat[p * D + k];
+    if (DIRECT)
+        for (int w = 0; w < kSelThreads / 64; ++w) r0 += s_w[w];
+    int n = 0;
+#pragma unroll
+    for (int j = 0; j < kRows; ++j)
+        for (int w = 0; w < kSelThreads / 64; ++w) {
+            if (w == wv && sel[j]) {
+                const int r = n + __popcll(m[j] & ((1ULL << lane) - 1ULL));
+                const long long p = base + j * kSelThreads + tid;
+                s_pix[r] = j * kSelThreads + tid;
+                const int u = (int)(p % W), v = (int)(p / W);
+                const float zf = depth[p];
+                const double z = (double)zf;
+                float *o = xyz + 3 * (r0 + r);
+                o[0] = (float)((((double)u - cx) * z) / fx);
+                o[1] = (float)((((double)v - cy) * z) / fy);
+                o[2] = zf;
+            }
+            n += s_cnt[j][w];
+        }
+    if (D == 0) return;
+    __syncthreads();
+    for (int e = tid; e < n * D; e += kSelThreads) {
+        const int r = e / D;
+        fout[r0 * D + e] = feat[(base + s_pix[r]) * D + (e - r * D)];
+    }
 }
+
+int select_blocks(long long npix) { return (int)((npix + kSelPix - 1) / kSelPix); }
+int select_hist_ints() { return 256 * kHistCopies; }
 
 void launch_select(const SelectArgs &a, hipStream_t s)
 {
     const long long npix = (long long)a.W * a.H;
-    hipLaunchKernelGGL(fast_score_kernel, dim3((a.W + kTX - 1) / kTX, (a.H + kTY - 1) / kTY), dim3(kTX, kTY), 0, s,
-                       a.gray, a.depth, a.W, a.H, a.dmin, a.dmax, a.key, a.score, a.hist);
-    hipLaunchKernelGGL(select_threshold_kernel, dim3(1), dim3(256), 0, s, a.hist, a.cap, a.res);
-    const int nb = (int)((npix + kSelThreads - 1) / kSelThreads);
-    hipLaunchKernelGGL(select_count_kernel, dim3(nb), dim3(kSelThreads), 0, s, a.key, npix, a.res, a.bcount);
+    hipLaunchKernelGGL(fast_score_kernel, dim3((a.W + kTX - 1) / kTX, (a.H + kTRows - 1) / kTRows), dim3(kTX, kTY), 0,
+                       s, a.gray, a.depth, a.W, a.H, a.dmin, a.dmax, a.key, a.score, a.hist);
+    const int nb = select_blocks(npix);
+    hipLaunchKernelGGL(select_count_kernel, dim3(nb), dim3(kSelThreads), 0, s, a.key, npix, a.hist, a.cap, a.res,
+                       a.bcount);
+    if (nb <= kDirectBlocks) {
+        hipLaunchKernelGGL(select_emit_kernel<true>, dim3(nb), dim3(kSelThreads), 0, s, a.key, a.depth, a.feat, npix,
+                           a.W, a.D, a.fx, a.fy, a.cx, a.cy, a.res, a.bcount, a.xyz, a.fout);
+        return;
+    }
     launch_exclusive_scan(a.bcount, a.boff, a.bsum, nb, nullptr, s);
-    hipLaunchKernelGGL(select_emit_kernel, dim3(nb), dim3(kSelThreads), 0, s, a.key, a.depth, a.feat, npix, a.W, a.D,
-                       a.fx, a.fy, a.cx, a.cy, a.res, a.boff, a.xyz, a.fout);
+    hipLaunchKernelGGL(select_emit_kernel<false>, dim3(nb), dim3(kSelThreads), 0, s, a.key, a.depth, a.feat, npix, a.W,
+                       a.D, a.fx, a.fy, a.cx, a.cy, a.res, a.boff, a.xyz, a.fout);
 }
-
-int select_blocks(long long npix) { return (int)((npix + kSelThreads - 1) / kSelThreads); }
 
 }  // namespace cvo
