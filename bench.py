@@ -45,11 +45,12 @@ def ops_per_pair(n_se, n_lin):
     kernel's inner loop issues them: squared distance 6 (3 sub, 1 mul, 2 fma),
     cutoff test 1, exp2 4 (quarter rate), W and D 7 (1 add, 3 mul, 3 add; the
     FP64 conversion happens once per queue flush, not per pair), second
-    moments S 6 (fma), pair count 1  = 25;  + 2 per SE column (sub, fma);
+    moments S 6 (fma)  = 24;  + 2 per SE column (sub, fma);
     + per LIN block: 1 fma per column, 1 add joining the dot's two FMA
-    chains, 1 multiply of the weight.  5 SE + 19 LIN: 25 + 10 + 21 = 56.
-    Loop control and the exact-recheck compare are not counted."""
-    return 25 + 2 * n_se + (n_lin + 2 if n_lin else 0)
+    chains, 1 multiply of the weight.  5 SE + 19 LIN: 24 + 10 + 21 = 55.
+    Loop control, the exact-recheck compare and the pair count (scalar, per
+    wave) are not counted."""
+    return 24 + 2 * n_se + (n_lin + 2 if n_lin else 0)
 
 
 KERNEL_SOURCES = ("paper_2012_03683_amd/csrc/cvo_pairs.hip", "paper_2012_03683_amd/csrc/cvo_device.hpp",
