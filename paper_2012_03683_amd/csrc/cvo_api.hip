@@ -517,11 +517,11 @@ struct ViewShape {
 
 // The shape of one-shot calls and of a registration's first view.  Until a
 // shape field has been set or tuned it is 16-point chunks, half-radius cells
-// and clusters up to one radius wide: within 12% of the best of 36 shapes at
-// every density measured, where the fields' own defaults are up to 2x off
+// and clusters up to one radius wide: within 15% of the best of 27 shapes at
+// every density measured, where the fields' own defaults are up to 1.8x off
 // (pair pass, us, this shape / the fields' defaults / the best: stereo 30,000
-// at ell 0.95 190 / 340 / 169, 0.5 91 / 137 / 84, 0.25 44 / 58 / 44, 0.1
-// 31 / 31 / 29; RGB-D 40,000 at 0.1 83 / 143 / 81, 0.05 42 / 55 / 42).  The
+// at ell 0.95 180 / 286 / 156, 0.5 79 / 129 / 76, 0.25 39 / 57 / 38, 0.1
+// 24 / 31 / 22; RGB-D 40,000 at 0.1 66 / 108 / 62, 0.05 33 / 45 / 31).  The
 // allocation-free entry point keeps the fields: finer cells would take more of
 // its fixed scratch.
 ViewShape fixed_shape(const cvo_context *ctx)
@@ -532,14 +532,15 @@ ViewShape fixed_shape(const cvo_context *ctx)
 }
 
 // Density classes and their view shapes, measured per feature layout (a
-// same-box sweep of both cluster rules x 16/32/64 points x cell edge 0.5/1.0
-// x cluster edge 0.5/1.0/1.5 r_c on the stereo and RGB-D pairs).  Chunk
-// clusters win in every band but the sparsest, where the rules tie: their
-// parts fill the power-of-two lane groups.  Dense bands cut the neighbourhood
-// finer (cell edge r_c / 2) and keep clusters small in space; sparse bands
-// let clusters grow past the cutoff radius so a wave's fixed cost is shared
-// by more queries.  Rows of at most 8 floats (cheap pairs) keep 32-point
-// clusters down to 100 pairs per query; wider rows switch to 16 below 500.
+// same-box sweep of 16/32/64-point chunks x cell edge 0.35/0.5/1.0 x cluster
+// edge 0.5/1.0/1.5 r_c on the stereo and RGB-D pairs).  Chunk clusters fill the
+// power-of-two lane groups.  Dense bands cut the neighbourhood finer (cell edge
+// r_c / 2) and keep clusters small in space; sparse bands let clusters grow past
+// the cutoff radius so a wave's fixed cost is shared by more queries.  Pair
+// pass, us: rows over 8 floats, 16 / 1.0 / 1.5 against 16 / 1.0 / 1.0 below 200
+// pairs per query: 27.1 / 27.4 at 138, 21.6 / 24.2 at 62.  Rows of at most 8,
+// 16 / 0.5 / 1.0 against 32 / 0.5 / 1.0 from 100: 66 / 70 at 838, 45 / 46 at 406,
+// 33 / 41 at 195 (RGB-D registrations 1.05x and 1.07x).
 bool light_layout(const FeatLayout &lay) { return lay.d4 <= 8; }
 
 void class_thresholds(const FeatLayout &lay, double t[3])
@@ -562,9 +563,9 @@ ViewShape density_shape(cvo_context *ctx, int cls, const FeatLayout &lay)
     const int r = CVO_CLUSTER_CHUNKS;
     switch (cls) {
     case 3: return ViewShape{32, 0.5, 0.5, r};
-    case 2: return light ? ViewShape{32, 0.5, 1.0, r} : ViewShape{32, 0.5, 0.5, r};
+    case 2: return light ? ViewShape{16, 0.5, 1.0, r} : ViewShape{32, 0.5, 0.5, r};
     case 1: return light ? ViewShape{16, 1.0, 1.5, r} : ViewShape{16, 0.5, 1.0, r};
-    case 0: return light ? ViewShape{16, 1.0, 1.5, r} : ViewShape{16, 1.0, 1.0, r};
+    case 0: return ViewShape{16, 1.0, 1.5, r};
     default: return fixed_shape(ctx);
     }
 }
