@@ -25,6 +25,7 @@
 //     kernel and every SE feature block together, the LIN dot product; W =
 //     sum w and D = sum w d are summed in FP32 over the flush and then added
 //     in FP64, S = sum w d d^T is summed in FP32.
+//     The backward takes its pairs in FP64 throughout.
 //   * Pairs whose FP32 squared distance lies within a proven error band of
 //     the cutoff are decided again with the FP64 expression that defines the
 //     pair set, so |P| is exact.
@@ -54,6 +55,21 @@ __device__ __forceinline__ double uniform_d(double v)
 __device__ __forceinline__ double pow2_below(double v)
 {
     return __longlong_as_double(__double_as_longlong(v) & 0x7ff0000000000000LL);
+}
+
+// 2^-e for e >= 0 (0 from about 1,075 on; NaN stays): e = n + f with n its nearest
+// integer, 2^-f by the polynomial of degree 6 with the least maximum relative
+// error on |f| <= 1/2 (a weighted least-squares fit, reweighted until its error
+// peaks were level): 1.9e-9, where the FP32 exponential has about 1e-7.
+__device__ __forceinline__ double exp2_neg(double e)
+{
+    constexpr double c[7] = {1.0000000005541698,   -0.6931472057372612,   0.24022646890619745, -0.055503287769749755,
+                             0.009618488958667314, -0.0013399931216049354, 0.00015345811584973305};
+    const double n = rint(e), f = e - n;
+    double p = c[6];
+#pragma unroll
+    for (int k = 5; k >= 0; --k) p = fma(p, f, c[k]);
+    return ldexp(p, -(int)n);
 }
 
 // Membership of (x, z) in the pair set, decided exactly as the set is defined:
@@ -99,10 +115,10 @@ void pair_pass_kernel(const PairPassArgs a)
     constexpr int F4 = D4 / 4;
     constexpr int F4s = F4 > 0 ? F4 : 1;
     constexpr int VF = D4 > 0 ? D4 : 1;
-    // candidate queue, one entry of E4 float4s per candidate: (scaled
-    // coordinates relative to the cluster centre, source index bits), then
-    // the feature row
-    constexpr int E4 = 1 + F4;
+    // candidate queue, one entry of E4 float4s per candidate: the scaled
+    // coordinates relative to the cluster centre and the source index's bits
+    // (one float4; backward: FP64, two), then the feature row
+    constexpr int C4 = MODE == 0 ? 1 : 2, E4 = C4 + F4;
     __shared__ float4 s_q[kWavesPerBlock][kQueueCap * E4];
     __shared__ int s_row[kWavesPerBlock][kWave];
 
@@ -203,21 +219,39 @@ void pair_pass_kernel(const PairPassArgs a)
             cull2 = uniform_f((float)(Rq * Rq * ascale));
         }
         if (!active) hi = -1.0f;  // (takes no pair)
+        // (backward) the LIN columns of the query's features in FP64, where the
+        // registers hold them beside the sums of all columns; else they are
+        // converted for each pair
+        constexpr bool kHoldV = MODE == 1 && LIND > 0 && 2 * D4 + 2 * LIND + SED <= 150;
+        double vl[kHoldV ? LIND : 1];
+        vl[0] = 0.0;
+#pragma unroll
+        for (int k = 0; k < (kHoldV ? LIND : 0); ++k) vl[k] = (double)vf[SED + k];
         const double zpx = Pm[0] * zq.x + Pm[1] * zq.y + Pm[2] * zq.z + Pm[3];
         const double zpy = Pm[4] * zq.x + Pm[5] * zq.y + Pm[6] * zq.z + Pm[7];
         const double zpz = Pm[8] * zq.x + Pm[9] * zq.y + Pm[10] * zq.z + Pm[11];
-        const float zrx = (float)((zpx - cx) * sc);
-        const float zry = (float)((zpy - cy) * sc);
-        const float zrz = (float)((zpz - cz) * sc);
+        const double zsx = (zpx - cx) * sc, zsy = (zpy - cy) * sc, zsz = (zpz - cz) * sc;
+        const float zrx = (float)zsx, zry = (float)zsy, zrz = (float)zsz;
 
         double W = 0.0, Dx = 0.0, Dy = 0.0, Dz = 0.0;
         float S00 = 0.f, S01 = 0.f, S02 = 0.f, S11 = 0.f, S12 = 0.f, S22 = 0.f;
         int cnt = 0;
         double Gf[MODE == 1 ? VF : 1];
-        double Ls = 0.0, Wd = 0.0;
+        double Ls = 0.0;
 #pragma unroll
         for (int k = 0; k < (MODE == 1 ? VF : 1); ++k) Gf[k] = 0.0;
 
+        struct Coords {  // of a queue entry
+            float4 a, b;
+            __device__ explicit Coords(const float4 *e) : a(e[0]), b(e[C4 - 1]) {}
+            static __device__ double join(float lo, float hi)
+            {
+                return __hiloint2double(__float_as_int(hi), __float_as_int(lo));
+            }
+            __device__ double dx() const { return join(a.x, a.y); }
+            __device__ double dy() const { return join(a.z, a.w); }
+            __device__ double dz() const { return join(b.x, b.y); }
+        };
         // W and D are summed in FP32 over one queue flush (at most kQueueCap
         // terms per lane) and added to the FP64 accumulators after it.
         float w32 = 0.f, dx32 = 0.f, dy32 = 0.f, dz32 = 0.f;
@@ -230,24 +264,28 @@ void pair_pass_kernel(const PairPassArgs a)
         // with five SE columns, with the loop below.  30,000 stereo points,
         // ell 0.95: 202 -> 188 us; 40,000 RGB-D, 0.1: 68 -> 64 us.)
         // `valid`: the lanes that have an entry (all but in the tail of a flush).
-        auto pair_term = [&](float dx, float dy, float dz, float s, const float4 *ent, unsigned long long valid) {
+        auto members = [&](float s, const float4 *ent, unsigned long long valid) {
             unsigned long long take = __builtin_amdgcn_ballot_w64(s <= hi) & valid;
             const unsigned long long near = __builtin_amdgcn_ballot_w64(s > lo) & take;
             if (near) {
                 bool in = true;
                 if (__builtin_amdgcn_inverse_ballot_w64(near)) {
-                    const float4 *rp = a.rpts + __float_as_int(ent[0].w), *qp = a.qpts + pq;
+                    const float4 *rp = a.rpts + __float_as_int(ent[C4 - 1].w), *qp = a.qpts + pq;
                     in = canonical_member(st->T, inverse ? qp : rp, inverse ? rp : qp, rc2);
                 }
                 take &= __builtin_amdgcn_ballot_w64(in);
             }
+            return take;
+        };
+        auto pair_term = [&](float dx, float dy, float dz, float s, const float4 *ent, unsigned long long valid) {
+            const unsigned long long take = members(s, ent, valid);
             cnt += __popcll(take);
             if (__builtin_amdgcn_inverse_ballot_w64(take)) {
                 float E = s;
                 float lin = 0.0f, lin1 = 0.0f;  // even / odd LIN columns: two shorter FMA chains
 #pragma unroll
                 for (int f = 0; f < F4; ++f) {
-                    const float4 u4 = ent[1 + f];
+                    const float4 u4 = ent[C4 + f];
                     const float uu[4] = {u4.x, u4.y, u4.z, u4.w};
 #pragma unroll
                     for (int q = 0; q < 4; ++q) {
@@ -270,32 +308,75 @@ void pair_pass_kernel(const PairPassArgs a)
                 dx32 += wx;
                 dy32 += wy;
                 dz32 += wz;
-                if (MODE == 0) {
-                    S00 = fmaf(wx, dx, S00);
-                    S01 = fmaf(wx, dy, S01);
-                    S02 = fmaf(wx, dz, S02);
-                    S11 = fmaf(wy, dy, S11);
-                    S12 = fmaf(wy, dz, S12);
-                    S22 = fmaf(wz, dz, S22);
-                } else {
-                    // FP64 products and sums: one conversion and one FMA per
-                    // column.  SE columns sum w u here and take v W off at
-                    // the end (W summed in FP64 for it): sum w (u - v).
-                    // 5 SE + 19 LIN, 30,000 points, both sides: 763 -> 723 us
-                    // at ell 0.95, 149 -> 144 us at 0.25 against an FP32
-                    // product, a conversion and an add per column
-                    const double wd = (double)w, wn = (double)wnl;
-                    Wd += wd;
-                    Ls = fma(wd, (double)s, Ls);
+                S00 = fmaf(wx, dx, S00);
+                S01 = fmaf(wx, dy, S01);
+                S02 = fmaf(wx, dz, S02);
+                S11 = fmaf(wy, dy, S11);
+                S12 = fmaf(wy, dz, S12);
+                S22 = fmaf(wz, dz, S22);
+            }
+        };
+        // The backward's pair is FP64 but for the sum over the SE columns: the
+        // distance, the LIN dot, the weight and all sums.  With signed LIN weights
+        // the terms of sum w s' cancel 10^3 to 10^4 times, and dF/dell keeps
+        // what their rounding leaves: 10,000 points of 32 LIN columns, twelve
+        // draws, relative error against 64 bits 3.0e-7 (geometric mean) and
+        // 4.4e-6 (largest) with FP32 terms, 1.8e-8 and 4.8e-8 (its FP32 result's
+        // own rounding) with these; dX 1.3e-7 -> 2.5e-8.  FP64 FMAs issue at the
+        // rate of FP32's, so what it takes is conversions and the longer
+        // exponential (both sides' pass): those 10,000 points 100 -> 137 us,
+        // 20,011 x 17,389 of 5 SE + 19 LIN 197 -> 277 us, 40,000 RGB-D of 5 SE
+        // 132 -> 204 us.
+        auto grad_term = [&](const Coords &c, const float4 *ent, unsigned long long valid) {
+            const double dx = c.dx() - zsx, dy = c.dy() - zsy, dz = c.dz() - zsz;
+            const double s = fma(dz, dz, fma(dy, dy, dx * dx));
+            const unsigned long long take = members((float)s, ent, valid);
+            if (__builtin_amdgcn_inverse_ballot_w64(take)) {
+                float se = 0.0f, rest = 0.0f;
+                double lin = 0.0;
 #pragma unroll
-                    for (int f = 0; f < F4; ++f) {
-                        const float4 u4 = ent[1 + f];
-                        const float uu[4] = {u4.x, u4.y, u4.z, u4.w};
+                for (int f = 0; f < F4; ++f) {
+                    const float4 u4 = ent[C4 + f];
+                    const float uu[4] = {u4.x, u4.y, u4.z, u4.w};
 #pragma unroll
-                        for (int q = 0; q < 4; ++q) {
-                            const int d = 4 * f + q;
-                            if (MODE == 1 && d < D) Gf[d] = fma(d < SED ? wd : wn, (double)uu[q], Gf[d]);
+                    for (int q = 0; q < 4; ++q) {
+                        const int d = 4 * f + q;
+                        if (d < SED) {
+                            const float df = uu[q] - vf[d];
+                            se = fmaf(df, df, se);
+                        } else if (d < D) {
+                            if (kHoldV) {
+                                lin = fma((double)uu[q], vl[kHoldV ? d - SED : 0], lin);
+                            } else {
+                                const float pr = uu[q] * vf[d];
+                                lin += (double)pr;
+                                rest += fmaf(uu[q], vf[d], -pr);
+                            }
                         }
+                    }
+                }
+                double E = fmin(s, 2048.0);  // (2^-2048 is 0)
+                if (SED > 0) E += (double)(se > 2048.0f ? 2048.0f : se);  // (NaN stays)
+                const double wn = exp2_neg(E);
+                const double w = (LIND > 0) ? wn * (kHoldV ? lin : lin + (double)rest) : wn;
+                W += w;
+                Dx = fma(w, dx, Dx);
+                Dy = fma(w, dy, Dy);
+                Dz = fma(w, dz, Dz);
+                Ls = fma(w, s, Ls);
+                // SE columns sum w u here and take v W off at the end: sum w (u - v).
+                // A wide row is read and converted again, not held over the
+                // exponential (20 columns more in registers spill).
+                const float4 *row = ent + C4;
+                if (LIND > 0 && D4 > 28) asm volatile("" : "+v"(row));
+#pragma unroll
+                for (int f = 0; f < F4; ++f) {
+                    const float4 u4 = row[f];
+                    const float uu[4] = {u4.x, u4.y, u4.z, u4.w};
+#pragma unroll
+                    for (int q = 0; q < 4; ++q) {
+                        const int d = 4 * f + q;
+                        if (MODE == 1 && d < D) Gf[d] = fma(d < SED ? w : wn, (double)uu[q], Gf[d]);
                     }
                 }
             }
@@ -310,30 +391,36 @@ void pair_pass_kernel(const PairPassArgs a)
             const int nfull = wave_uniform(qn >> (6 - lg));  // qn / SUB
             const float4 *ent = &s_q[wv][qs * E4];
             const int step = SUB * E4;
-            auto one = [&](const float4 c, const float4 *at, unsigned long long in) {
-                const float dx = c.x - zrx, dy = c.y - zry, dz = c.z - zrz;
+            auto one = [&](const Coords &c, const float4 *at, unsigned long long in) {
+                if (MODE == 1) return grad_term(c, at, in);
+                const float dx = c.a.x - zrx, dy = c.a.y - zry, dz = c.a.z - zrz;
                 const float s = fmaf(dz, dz, fmaf(dy, dy, dx * dx));
                 pair_term(dx, dy, dz, s, at, in);
             };
-            float4 e0 = ent[0];
-            for (int it = 0; it < nfull - 1; it += 2) {
+            // (the widest rows of the backward: one copy of the pair's code, as
+            // three are not unrolled any more and put their sums in memory)
+            constexpr bool kTwo = MODE == 0 || D4 <= 40;
+            Coords e0(ent);
+            for (int it = 0; kTwo && it < nfull - 1; it += 2) {
                 const float4 *odd = ent + step;
-                const float4 e1 = *odd;
+                const Coords e1(odd);
                 one(e0, ent, ~0ULL);
                 ent = odd + ((it + 3 < nfull) ? step : 0);  // (the last pair re-reads its second row)
-                e0 = *ent;
+                e0 = Coords(ent);
                 one(e1, odd, ~0ULL);
             }
-            for (int k0 = wave_uniform((nfull & ~1) << (6 - lg)); k0 < qn; k0 += SUB) {
+            for (int k0 = kTwo ? wave_uniform((nfull & ~1) << (6 - lg)) : 0; k0 < qn; k0 += SUB) {
                 const int kt = qs + k0;
                 const bool in = kt < qn;
                 const float4 *tl = &s_q[wv][(in ? kt : 0) * E4];
-                one(*tl, tl, __builtin_amdgcn_ballot_w64(in));
+                one(Coords(tl), tl, __builtin_amdgcn_ballot_w64(in));
             }
-            W += (double)w32;
-            Dx += (double)dx32;
-            Dy += (double)dy32;
-            Dz += (double)dz32;
+            if (MODE == 0) {
+                W += (double)w32;
+                Dx += (double)dx32;
+                Dy += (double)dy32;
+                Dz += (double)dz32;
+            }
         };
 
         // this piece takes chunks pidx, pidx + np, pidx + 2 np, ... of the
@@ -401,19 +488,27 @@ void pair_pass_kernel(const PairPassArgs a)
                     };
                     fetch();
                     for (;;) {
-                        const float x0 = (float)(((double)xp.x - cx) * sc);
-                        const float x1 = (float)(((double)xp.y - cy) * sc);
-                        const float x2 = (float)(((double)xp.z - cz) * sc);
+                        const double xd[3] = {((double)xp.x - cx) * sc, ((double)xp.y - cy) * sc, ((double)xp.z - cz) * sc};
+                        const float x0 = (float)xd[0], x1 = (float)xd[1], x2 = (float)xd[2];
                         const float r2 = fmaf(x2, x2, fmaf(x1, x1, x0 * x0));
                         const unsigned long long mask = __builtin_amdgcn_ballot_w64(r2 <= cull2) & in_row;
                         const int cur = src;
                         if (__builtin_amdgcn_inverse_ballot_w64(mask)) {
                             const int slot = __builtin_amdgcn_mbcnt_hi((unsigned)(mask >> 32),
                                                                        __builtin_amdgcn_mbcnt_lo((unsigned)mask, qn));
-                            s_q[wv][__umul24(slot, E4)] = make_float4(x0, x1, x2, __int_as_float(cur));
+                            float4 *q = &s_q[wv][__umul24(slot, E4)];
+                            if (MODE == 0) {
+                                q[0] = make_float4(x0, x1, x2, __int_as_float(cur));
+                            } else {
+                                auto half = [&](int k, bool hi) {
+                                    return __int_as_float(hi ? __double2hiint(xd[k]) : __double2loint(xd[k]));
+                                };
+                                q[0] = make_float4(half(0, false), half(0, true), half(1, false), half(1, true));
+                                q[C4 - 1] = make_float4(half(2, false), half(2, true), 0.f, __int_as_float(cur));
+                            }
                             const float4 *fr = reinterpret_cast<const float4 *>(a.rfeat) + (long long)cur * F4;
 #pragma unroll
-                            for (int f = 0; f < F4; ++f) s_q[wv][__umul24(slot, E4) + 1 + f] = fr[f];
+                            for (int f = 0; f < F4; ++f) q[C4 + f] = fr[f];
                         }
                         k += pstride;
                         const bool more = k * kWave < base + total;
@@ -437,7 +532,7 @@ void pair_pass_kernel(const PairPassArgs a)
 
         if (MODE == 1) {
 #pragma unroll
-            for (int k = 0; k < SED; ++k) Gf[MODE == 1 ? k : 0] -= Wd * (double)vf[k];
+            for (int k = 0; k < SED; ++k) Gf[MODE == 1 ? k : 0] -= W * (double)vf[k];
         }
         float4 ze = make_float4(0.f, 0.f, 0.f, 0.f);
         if (MODE == 0) {  // the query's point again: it need not stay in registers over the walk
