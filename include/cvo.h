@@ -287,7 +287,7 @@ cvo_status cvo_evaluate_noalloc(cvo_handle h, const cvo_cloud *X, const cvo_clou
  * ||f_Z||^2 = F(Z, Z; I) are the self inner products with the same kernels,
  * lengthscale and cutoff.  The three sums are evaluated together, as three
  * pairs of one pair pass on the handle's stream (one after another for clouds
- * of more than 4 million points).
+ * of more than 4 million points, and where the three do not fit together).
  * sums, if non-NULL, receives {F(X,Z;T), F(X,X;I), F(Z,Z;I)} (host memory).
  * cos_theta is 0 when a squared norm is not positive (an empty cloud).
  * Errors as cvo_inner_product. */

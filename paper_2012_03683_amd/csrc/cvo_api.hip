@@ -163,6 +163,13 @@ struct cvo_context {
         fixed.regions[name] = {off, need};
         return fixed.base + off;
     }
+    // gives the arena's buffers back (nothing in flight uses them)
+    void trim()
+    {
+        for (auto &kv : bufs)
+            if (kv.second.p) HIP_OK(hipFree(kv.second.p));
+        bufs.clear();
+    }
     // elements a buffer of the arena has room for without growing
     template <class T> size_t room(const std::string &name) const
     {
@@ -597,8 +604,10 @@ struct PairSpec {
 // which leaves them as they are.  The host waits once, for the piece and slot counts (with the
 // fixed scratch of the allocation-free entry point also for the size of the
 // cell tables).  A later build also finds the clouds' boxes in the arena.
+// slot_bytes: bytes of partial moments per output slot, of a caller that takes the
+// pairs one by one if they do not fit together (CVO_ERR_OUT_OF_MEMORY); else 0.
 void build_pairs(cvo_context *ctx, Views &v, const std::vector<PairSpec> &pairs, const FeatLayout &lay, double kappa,
-                 const void *head, size_t head_bytes)
+                 const void *head, size_t head_bytes, size_t slot_bytes = 0)
 {
     ctx->timing.view_builds += 1;
     const int B = (int)pairs.size();
@@ -667,12 +676,12 @@ void build_pairs(cvo_context *ctx, Views &v, const std::vector<PairSpec> &pairs,
 
     // the head of BuildInfo, which is all the host reads of it
     struct {
-        unsigned long long alloc;
+        unsigned long long pieces, slots;
         long long cells;
         int bad, overflow;
     } info;
-    static_assert(offsetof(BuildInfo, cells) == 8 && offsetof(BuildInfo, bad) == 16 &&
-                      offsetof(BuildInfo, overflow) == 20 && sizeof(info) == 24,
+    static_assert(offsetof(BuildInfo, slots) == 8 && offsetof(BuildInfo, cells) == 16 &&
+                      offsetof(BuildInfo, bad) == 24 && offsetof(BuildInfo, overflow) == 28 && sizeof(info) == 32,
                   "head of BuildInfo");
     // the cell tables' size is not known here: they go into what the arena
     // holds (at least one full table), and are built again if that was too little
@@ -700,7 +709,8 @@ void build_pairs(cvo_context *ctx, Views &v, const std::vector<PairSpec> &pairs,
         // stream synchronisation)
         if (a.mail && ctx->spin_until([&] { return __atomic_load_n(&a.mail->build, __ATOMIC_ACQUIRE) == a.build; })) {
             ctx->timing.host_waits += 1;
-            info.alloc = a.mail->alloc;
+            info.pieces = a.mail->pieces;
+            info.slots = a.mail->slots;
             info.cells = a.mail->cells;
             info.bad = a.mail->bad;
             info.overflow = a.mail->overflow;
@@ -713,9 +723,13 @@ void build_pairs(cvo_context *ctx, Views &v, const std::vector<PairSpec> &pairs,
         if (!info.overflow) break;
         cells = (size_t)info.cells;
     }
-    v.npieces = (int)(info.alloc & 0xffffffffu);
-    v.nslots = (long long)(info.alloc >> 32);
-    require(v.nslots < (1LL << 31), "too many output slots");
+    if (!plan_fits(info.pieces, info.slots))
+        throw CvoError(CVO_ERR_OUT_OF_MEMORY, "the plan needs " + std::to_string(info.slots) +
+                                                  " output slots; there can be 2^31 - 1");
+    if (B > 1 && slot_bytes && !joint_fits(info.slots, slot_bytes))
+        throw CvoError(CVO_ERR_OUT_OF_MEMORY, "a joint plan of " + std::to_string(info.slots) + " output slots");
+    v.npieces = (int)info.pieces;
+    v.nslots = (long long)info.slots;
     if (v.npieces > a.rec_cap) {
         a.recs = ctx->get_t<PieceRec>("v.recs", v.npieces);
         a.rec_cap = v.npieces;
@@ -730,6 +744,11 @@ struct Moments {
     float *S;
     int *cnt;
 };
+
+size_t moment_bytes(int d4, bool backward)  // per output slot
+{
+    return backward ? sizeof(double) * (4 + d4) : 4 * sizeof(double) + 6 * sizeof(float) + sizeof(int);
+}
 
 Moments moments(cvo_context *ctx, const std::string &pre, long long n, int d4, bool backward)
 {
@@ -832,19 +851,21 @@ struct Problem {
 // state: `head` (states and constants) on a call's first build, later the
 // device's own.
 void build_views(cvo_context *ctx, Problem &p, const std::vector<CloudPtrs> &X, const std::vector<CloudPtrs> &Z,
-                 const std::vector<double> &ell, const std::vector<ViewShape> &shape, const void *head = nullptr)
+                 const std::vector<double> &ell, const std::vector<ViewShape> &shape, const void *head = nullptr,
+                 bool may_split = false)
 {
     p.shape = shape;
     std::vector<PairSpec> pairs(X.size());
     for (size_t k = 0; k < X.size(); ++k) pairs[k] = PairSpec{X[k], Z[k], p.kappa * ell[k], shape[k], 0};
-    build_pairs(ctx, p.views, pairs, p.lay, p.kappa, head, X.size() * (sizeof(PairState) + sizeof(AlignConst)));
+    build_pairs(ctx, p.views, pairs, p.lay, p.kappa, head, X.size() * (sizeof(PairState) + sizeof(AlignConst)),
+                may_split ? moment_bytes(p.lay.d4, false) : 0);
     p.mom = moments(ctx, "fm", p.views.nslots, p.lay.d4, false);
     p.nblk = reduce_blocks(p.views.desc);
     p.partials = ctx->get_t<double>("partials", shape.size() * (size_t)p.nblk * kRedVals);
 }
 
 void setup_problem(cvo_context *ctx, Problem &p, const std::vector<CloudPtrs> &X, const std::vector<CloudPtrs> &Z,
-                   const std::vector<PairState> &st, const std::vector<AlignConst> &ac)
+                   const std::vector<PairState> &st, const std::vector<AlignConst> &ac, bool may_split = false)
 {
     const int B = (int)X.size();
     std::vector<double> ell(B);
@@ -853,7 +874,7 @@ void setup_problem(cvo_context *ctx, Problem &p, const std::vector<CloudPtrs> &X
     std::vector<char> head(B * (sizeof(PairState) + sizeof(AlignConst)));
     std::memcpy(head.data(), st.data(), B * sizeof(PairState));
     std::memcpy(head.data() + B * sizeof(PairState), ac.data(), B * sizeof(AlignConst));
-    build_views(ctx, p, X, Z, ell, std::vector<ViewShape>(B, fixed_shape(ctx)), head.data());
+    build_views(ctx, p, X, Z, ell, std::vector<ViewShape>(B, fixed_shape(ctx)), head.data(), may_split);
     p.d_state = reinterpret_cast<PairState *>(p.views.d_head);
     p.d_ac = reinterpret_cast<AlignConst *>(p.views.d_head + B * sizeof(PairState));
 }
@@ -982,9 +1003,9 @@ struct Evaluation {
 
 // Forward evaluations with the same spec and kernels, in one build, one pair
 // pass and one reduction.  A pair with an empty cloud keeps its initial state
-// (all sums zero).
+// (all sums zero).  may_split: the caller takes them one by one if they do not fit.
 void evaluate_all(cvo_context *ctx, std::vector<Evaluation> &ev, const cvo_feature_spec *spec,
-                  const cvo_kernel_params *kp, bool ellobj = false)
+                  const cvo_kernel_params *kp, bool ellobj = false, bool may_split = false)
 {
     check_spec(spec);
     const int D = spec_dim(spec);
@@ -1011,7 +1032,7 @@ void evaluate_all(cvo_context *ctx, std::vector<Evaluation> &ev, const cvo_featu
     p.lay = make_layout(spec, kp->sigma);
     p.sig2 = p.lay.sig2;
     p.ellobj = ellobj ? 1 : 0;
-    setup_problem(ctx, p, xs, zs, st, ac);
+    setup_problem(ctx, p, xs, zs, st, ac, may_split);
     HostMail *mail = st.size() <= kMailStates ? ctx->mail() : nullptr;
     if (mail) std::memset(mail->state, 0, sizeof(PairState) * st.size());
     enqueue_iteration(ctx, p, 0, nullptr, 0, ctx->profiling, mail);
@@ -1036,6 +1057,22 @@ void evaluate_one(cvo_context *ctx, const cvo_cloud *X, const cvo_cloud *Z, cons
     std::vector<Evaluation> ev{{X, Z, T, PairState{}}};
     evaluate_all(ctx, ev, spec, kp, ellobj);
     *out = ev[0].out;
+}
+
+// Runs f, which evaluates several things together; false, with the arena given
+// back, if they do not fit together (too many slots, or memory).
+template <class F> bool together(cvo_context *ctx, F &&f)
+{
+    try {
+        f();
+        return true;
+    } catch (const CvoError &e) {
+        if (e.code != CVO_ERR_OUT_OF_MEMORY) throw;
+    }
+    (void)hipGetLastError();  // (of the failed allocation)
+    ctx->wait();
+    ctx->trim();
+    return false;
 }
 
 cvo_status fail(cvo_context *ctx, const CvoError &e)
@@ -1390,14 +1427,14 @@ cvo_status cvo_cosine(cvo_handle h, const cvo_cloud *X, const cvo_cloud *Z, cons
         static const double I[12] = {1.0, 0.0, 0.0, 0.0, 0.0, 1.0, 0.0, 0.0, 0.0, 0.0, 1.0, 0.0};
         // The three sums are three pairs of one evaluation (40,000 RGB-D points:
         // 629 us one by one, 416 us together); one by one where the views of
-        // three pairs would be gigabytes and launches no longer count.
+        // three pairs would be gigabytes and launches no longer count, and
+        // where the three do not fit together.
         std::vector<Evaluation> ev{{X, Z, T, PairState{}}, {X, X, I, PairState{}}, {Z, Z, I, PairState{}}};
         constexpr int64_t kTogether = int64_t(1) << 22;
-        if (X && Z && X->n <= kTogether && Z->n <= kTogether) {
-            evaluate_all(h, ev, spec, kp);
-        } else {
+        const bool joint = X && Z && X->n <= kTogether && Z->n <= kTogether &&
+                           together(h, [&] { evaluate_all(h, ev, spec, kp, false, true); });
+        if (!joint)
             for (auto &e : ev) evaluate_one(h, e.X, e.Z, spec, kp, e.T, &e.out);
-        }
         const double fxz = ev[0].out.F, fxx = ev[1].out.F, fzz = ev[2].out.F;
         // sqrt of the product: when the three sums coincide (the moved f_Z is
         // f_X) the quotient is exactly 1, as sqrt(fl(F * F)) == F
@@ -1641,10 +1678,11 @@ cvo_status cvo_inner_product_backward(cvo_handle h, const cvo_cloud *X, const cv
         std::vector<PairSpec> sides;
         if (target) sides.push_back(PairSpec{to_ptrs(X), to_ptrs(Z), rc, fixed_shape(h), 0});
         if (source) sides.push_back(PairSpec{to_ptrs(Z), to_ptrs(X), rc, fixed_shape(h), 1});
-        if (!sides.empty()) {
+        auto run = [&](const std::vector<PairSpec> &sides) {
             const std::vector<PairState> st(sides.size(), init_state(T, kp->ell));
             Views v;
-            build_pairs(h, v, sides, lay, kp->kappa, st.data(), sizeof(PairState) * st.size());
+            build_pairs(h, v, sides, lay, kp->kappa, st.data(), sizeof(PairState) * st.size(),
+                        moment_bytes(lay.d4, true));
             const PairState *d_state = v.a.state;
             Moments m = moments(h, "bm", v.nslots, lay.d4, true);
             run_pair_pass(h, pass_args(v, d_state, lay.sig2, kp->kappa, m), lay, 1);
@@ -1678,7 +1716,10 @@ cvo_status cvo_inner_product_backward(cvo_handle h, const cvo_cloud *X, const cv
                 const double ascale = kLog2e / (2.0 * kp->ell * kp->ell);
                 *dEll = gF * sl / (ascale * kp->ell * kp->ell * kp->ell);
             }
-        }
+        };
+        // (one after the other where the two do not fit together)
+        if (sides.size() == 1 || (sides.size() == 2 && !together(h, [&] { run(sides); })))
+            for (const PairSpec &side : sides) run({side});
         HIP_OK(hipStreamSynchronize(h->stream));
         if (h->profiling) h->harvest_events();
     });

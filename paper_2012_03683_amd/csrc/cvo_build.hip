@@ -184,7 +184,8 @@ __global__ __launch_bounds__(1024) void params_kernel(const ViewArgs a)
     __syncthreads();
     if (threadIdx.x == 0) {
         BuildInfo &f = *a.info;
-        f.alloc = 0;
+        f.pieces = 0;
+        f.slots = 0;
         f.cells = base;
         f.bad = s_bad;
         f.overflow = base > a.cell_cap;
@@ -923,7 +924,7 @@ __global__ __launch_bounds__(256) void plan_kernel(const ViewArgs a)
     __shared__ int s_first[256], s_n[256], s_np[256], s_slot[256];
     __shared__ int s_hist[kCostBuckets];
     __shared__ int s_w[4], s_w2[4];
-    __shared__ unsigned long long s_base;
+    __shared__ unsigned long long s_base;  // first slot of the block's clusters
     const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
     const unsigned long long even = (a.info->cand / kPieceTarget + 63) & ~63ULL;
     const int floor_ = (int)min(max(even, (unsigned long long)kPieceFew), (unsigned long long)kPieceMany);
@@ -954,10 +955,11 @@ __global__ __launch_bounds__(256) void plan_kernel(const ViewArgs a)
     if (tid == 0) {
         const unsigned long long tp = s_w[0] + s_w[1] + s_w[2] + s_w[3];
         const unsigned long long ts = s_w2[0] + s_w2[1] + s_w2[2] + s_w2[3];
-        s_base = atomicAdd(&a.info->alloc, tp | ts << 32);
+        atomicAdd(&a.info->pieces, tp);
+        s_base = atomicAdd(&a.info->slots, ts);
     }
     __syncthreads();
-    int slot = (int)(s_base >> 32) + is - ns;
+    int slot = (int)s_base + is - ns;  // (of no use, and not used, in a plan that does not fit)
     for (int w = 0; w < wv; ++w) slot += s_w2[w];
     s_first[tid] = first;
     s_n[tid] = n;
@@ -976,7 +978,7 @@ __global__ __launch_bounds__(256) void plan_kernel(const ViewArgs a)
 
 // The pieces' records, bucket by bucket (heaviest first; a cluster's pieces
 // together): 16 lanes per cluster write them.  Nothing is written when there
-// is no room for all of them.  The build's counts are posted to the host first.
+// is no room for all of them, or the plan does not fit.  The build's counts are posted to the host first.
 __global__ __launch_bounds__(256) void record_kernel(const ViewArgs a)
 {
     static_assert(kCostBuckets == 512, "two buckets per thread");
@@ -985,13 +987,14 @@ __global__ __launch_bounds__(256) void record_kernel(const ViewArgs a)
     const BuildInfo *f = a.info;
     if (a.mail && blockIdx.x == 0 && threadIdx.x == 0) {
         HostMail *m = a.mail;
-        __hip_atomic_store(&m->alloc, f->alloc, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+        __hip_atomic_store(&m->pieces, f->pieces, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+        __hip_atomic_store(&m->slots, f->slots, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
         __hip_atomic_store(&m->cells, f->cells, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
         __hip_atomic_store(&m->bad, f->bad, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
         __hip_atomic_store(&m->overflow, f->overflow, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
         __hip_atomic_store(&m->build, a.build, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
     }
-    if (f->overflow || (long long)(unsigned)f->alloc > a.rec_cap) return;
+    if (f->overflow || !plan_fits(f->pieces, f->slots) || f->pieces > (unsigned long long)a.rec_cap) return;
     const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6, l16 = tid & 15;
     const int h0 = f->hist[2 * tid], h1 = f->hist[2 * tid + 1];
     const int incl = wave_scan_add(h0 + h1);

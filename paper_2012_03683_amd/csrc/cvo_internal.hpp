@@ -23,6 +23,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include "cvo_limits.hpp"
+
 namespace cvo {
 
 constexpr int kWave = 64;
@@ -149,7 +151,8 @@ constexpr int kCostBuckets = 512;  // dispatch order of the pieces: heaviest buc
 
 // State of one view build, on the device.
 struct BuildInfo {
-    unsigned long long alloc;  // pieces planned (low 32 bits), output slots (high 32 bits)
+    unsigned long long pieces; // pieces planned
+    unsigned long long slots;  // output slots planned
     long long cells;           // cell-table entries of all pairs
     int bad;                   // a cloud has a non-finite coordinate
     int overflow;              // the cell tables do not fit: nothing after the boxes was done
@@ -165,11 +168,11 @@ struct BuildInfo {
 constexpr int kMailStates = 4;
 struct alignas(64) HostMail {
     // the head of BuildInfo, then the number of the build it belongs to
-    unsigned long long alloc;
+    unsigned long long pieces, slots;
     long long cells;
     int bad, overflow;
     unsigned long long build;
-    unsigned long long pad[4];
+    unsigned long long pad[3];
     // one registration's progress: steps taken << 2 | paused << 1 | done
     unsigned long long progress;
     unsigned long long pad2[7];

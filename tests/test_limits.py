@@ -1,0 +1,65 @@
+"""The limits of a work plan (cvo_limits.hpp), on the host: totals are compared
+in 64 bits, so a plan whose slots pass 2^32 is refused and not taken for its
+remainder."""
+import os
+import subprocess
+
+import pytest
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+PROGRAM = r"""
+#include <cstdio>
+#include <cstdlib>
+#include "cvo_limits.hpp"
+int main(int argc, char **argv)
+{
+    const unsigned long long pieces = strtoull(argv[1], nullptr, 10), slots = strtoull(argv[2], nullptr, 10);
+    printf("%d %d\n", (int)cvo::plan_fits(pieces, slots), (int)cvo::joint_fits(slots, strtoull(argv[3], nullptr, 10)));
+}
+"""
+
+
+@pytest.fixture(scope="module")
+def fits(tmp_path_factory):
+    d = tmp_path_factory.mktemp("limits")
+    (d / "limits.cpp").write_text(PROGRAM)
+    exe = str(d / "limits")
+    subprocess.run(["g++", "-std=c++17", "-Wall", "-Werror", "-I", os.path.join(ROOT, "paper_2012_03683_amd", "csrc"),
+                    str(d / "limits.cpp"), "-o", exe], check=True)
+
+    def call(pieces, slots, bytes_per_slot=60):
+        out = subprocess.run([exe, str(pieces), str(slots), str(bytes_per_slot)], check=True, capture_output=True,
+                             text=True).stdout.split()
+        return out[0] == "1", out[1] == "1"
+    return call
+
+
+def _plan(n_ref, n_query, cluster=16, least=512, most=4096):
+    """Pieces and slots of a plan without a cutoff: every cluster has every reference point."""
+    clusters = -(-n_query // cluster)
+    pieces = min(-(-n_ref // least), most)
+    return clusters * pieces, n_query * pieces
+
+
+@pytest.mark.parametrize("n,ok", [(1000, True), (1_000_000, True), (1_048_000, True), (1_049_000, False),
+                                  (1_500_000, False), (4_000_000, False)])
+def test_plan_without_cutoff(fits, n, ok):
+    pieces, slots = _plan(n, n)
+    assert (slots < 2 ** 31) == ok
+    assert fits(pieces, slots)[0] == ok
+
+
+def test_totals_are_not_taken_modulo(fits):
+    pieces, slots = _plan(1_500_000, 1_500_000)
+    assert slots == 4_395_000_000 and slots % 2 ** 32 < 2 ** 31  # (32 bits of it would pass)
+    assert not fits(pieces, slots)[0]
+    # three plans that fit one by one, and whose sum passes 2^32
+    one = _plan(860_000, 860_000)
+    assert fits(*one)[0] and not fits(3 * one[0], 3 * one[1])[0]
+
+
+@pytest.mark.parametrize("slots,bytes_per_slot,ok", [(0, 60, True), (2 ** 26, 64, True), (2 ** 26 + 1, 64, False),
+                                                     (2 ** 31 - 1, 2, True), (2 ** 31, 1, False),
+                                                     (2 ** 62 + 1, 4, False)])
+def test_joint_plan(fits, slots, bytes_per_slot, ok):
+    assert fits(0, slots, bytes_per_slot)[1] == ok
