@@ -645,7 +645,7 @@ void build_pairs(cvo_context *ctx, Views &v, const std::vector<PairSpec> &pairs,
         a.n[1] += p.query.n;
         nmax = std::max({nmax, p.ref.n, p.query.n});
     }
-    require(a.n[0] < (1LL << 31) && a.n[1] < (1LL << 31), "more than 2^31 points in one call");
+    require(a.n[0] < kMaxSidePoints && a.n[1] < kMaxSidePoints, "more than 2^31 points in one call");
     std::memcpy(blob.data() + head_bytes + B * sizeof(PairIn), v.desc.data(), B * sizeof(ClusterDesc));
     v.d_head = ctx->get_t<char>("v.in", blob.size());
     const size_t skip = head ? 0 : head_bytes;

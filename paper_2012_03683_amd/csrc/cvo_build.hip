@@ -325,23 +325,24 @@ __global__ __launch_bounds__(1024) void key_kernel(const ViewArgs a)
 
 // ---------------------------------------------------------------- scan
 // Exclusive prefix sum of n ints in three launches: per-block scans of 2048
-// elements, a single-block scan of the block sums, then the add-back.
+// elements, a single-block scan of the block sums, then the add-back.  (Summed
+// as SortPlace: the points of both sides may pass 2^31.)
 constexpr int kScanThreads = 256;
 constexpr int kScanItems = 8;
 constexpr int kScanTile = kScanThreads * kScanItems;
 
-__device__ inline int block_exclusive_scan(int v, int *total)
+__device__ inline SortPlace block_exclusive_scan(SortPlace v, SortPlace *total)
 {
-    __shared__ int sh[kScanThreads];
+    __shared__ SortPlace sh[kScanThreads];
     sh[threadIdx.x] = v;
     __syncthreads();
     for (int off = 1; off < kScanThreads; off <<= 1) {
-        int t = (threadIdx.x >= off) ? sh[threadIdx.x - off] : 0;
+        SortPlace t = (threadIdx.x >= off) ? sh[threadIdx.x - off] : 0;
         __syncthreads();
         sh[threadIdx.x] += t;
         __syncthreads();
     }
-    int incl = sh[threadIdx.x];
+    SortPlace incl = sh[threadIdx.x];
     *total = sh[kScanThreads - 1];
     __syncthreads();
     return incl - v;
@@ -350,50 +351,50 @@ __device__ inline int block_exclusive_scan(int v, int *total)
 __global__ __launch_bounds__(kScanThreads) void scan_tiles(const int *in, int *out, int *bsum, long long n)
 {
     const long long base = (long long)blockIdx.x * kScanTile + (long long)threadIdx.x * kScanItems;
-    int v[kScanItems];
-    int s = 0;
+    SortPlace v[kScanItems];
+    SortPlace s = 0;
     for (int k = 0; k < kScanItems; ++k) {
         v[k] = (base + k < n) ? in[base + k] : 0;
         s += v[k];
     }
-    int tot;
-    int ex = block_exclusive_scan(s, &tot);
+    SortPlace tot;
+    SortPlace ex = block_exclusive_scan(s, &tot);
     for (int k = 0; k < kScanItems; ++k) {
-        if (base + k < n) out[base + k] = ex;
+        if (base + k < n) out[base + k] = (int)ex;
         ex += v[k];
     }
-    if (threadIdx.x == 0) bsum[blockIdx.x] = tot;
+    if (threadIdx.x == 0) bsum[blockIdx.x] = (int)tot;
 }
 
 __global__ __launch_bounds__(kScanThreads) void scan_sums(int *bsum, int nb, int *total)
 {
     // nb <= kScanTile * kScanTile is guaranteed by the launcher (chunks of 2048)
-    int carry = 0;
+    SortPlace carry = 0;
     for (int base = 0; base < nb; base += kScanTile) {
         const int b0 = base + threadIdx.x * kScanItems;
-        int v[kScanItems];
-        int s = 0;
+        SortPlace v[kScanItems];
+        SortPlace s = 0;
         for (int k = 0; k < kScanItems; ++k) {
             v[k] = (b0 + k < nb) ? bsum[b0 + k] : 0;
             s += v[k];
         }
-        int tot;
-        int ex = block_exclusive_scan(s, &tot) + carry;
+        SortPlace tot;
+        SortPlace ex = block_exclusive_scan(s, &tot) + carry;
         for (int k = 0; k < kScanItems; ++k) {
-            if (b0 + k < nb) bsum[b0 + k] = ex;
+            if (b0 + k < nb) bsum[b0 + k] = (int)ex;
             ex += v[k];
         }
         carry += tot;
     }
-    if (threadIdx.x == 0 && total) *total = carry;
+    if (threadIdx.x == 0 && total) *total = (int)carry;
 }
 
 __global__ __launch_bounds__(kScanThreads) void scan_add(int *out, const int *bsum, long long n)
 {
     const long long base = (long long)blockIdx.x * kScanTile + (long long)threadIdx.x * kScanItems;
-    const int add = bsum[blockIdx.x];
+    const SortPlace add = bsum[blockIdx.x];
     for (int k = 0; k < kScanItems; ++k)
-        if (base + k < n) out[base + k] += add;
+        if (base + k < n) out[base + k] = (int)(out[base + k] + add);
 }
 
 void launch_exclusive_scan(const int *in, int *out, int *bsum, long long n, int *total, hipStream_t s)
@@ -537,7 +538,7 @@ __global__ __launch_bounds__(1024) void radix_scatter(const ViewArgs a, int pass
 {
     const int side = blockIdx.y, ntiles = tiles_of(a.n[side]);
     if (blockIdx.x >= ntiles || pass >= passes_of(a, side) || a.info->overflow) return;
-    __shared__ int s_cnt[16][256];
+    __shared__ SortPlace s_cnt[16][256];
     const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
     const long long o = side ? a.n[0] : 0;
     const long long e = (long long)blockIdx.x * kRadixTile + tid;
@@ -554,17 +555,17 @@ __global__ __launch_bounds__(1024) void radix_scatter(const ViewArgs a, int pass
     __syncthreads();
     if (tid < 256) {
         const long long t0 = side ? tiles_of(a.n[0]) : 0;
-        int acc = hist[256 * t0 + (long long)tid * ntiles + blockIdx.x];
+        SortPlace acc = hist[256 * t0 + (long long)tid * ntiles + blockIdx.x];
 #pragma unroll
         for (int w = 0; w < 16; ++w) {
-            const int c = s_cnt[w][tid];
+            const SortPlace c = s_cnt[w][tid];
             s_cnt[w][tid] = acc;
             acc += c;
         }
     }
     __syncthreads();
     if (valid) {
-        const int pos = s_cnt[wv][d] + rank;
+        const SortPlace pos = s_cnt[wv][d] + rank;
         a.key[(pass + 1) & 1][pos] = key;
         a.val[(pass + 1) & 1][pos] = val;
     }

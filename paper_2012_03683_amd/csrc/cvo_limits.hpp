@@ -1,5 +1,6 @@
-// cvo_limits.hpp -- limits of a work plan, in host arithmetic only.
+// cvo_limits.hpp -- limits of a view build and its work plan, in host arithmetic.
 #pragma once
+#include <limits>
 
 namespace cvo {
 
@@ -14,6 +15,13 @@ constexpr bool plan_fits(unsigned long long pieces, unsigned long long slots)
 {
     return slots < kMaxSlots && pieces <= slots;
 }
+
+// A call has fewer than 2^31 points on each side.  The passes of a large sort run
+// their digit counts on from the reference side to the query side, so a place in
+// them is a place among the points of both.
+constexpr long long kMaxSidePoints = 1LL << 31;
+using SortPlace = unsigned;
+static_assert(2 * (kMaxSidePoints - 1) <= std::numeric_limits<SortPlace>::max(), "places of both sides' points");
 
 // Several evaluations share one plan only while its partial moments stay within
 // this: beyond, the pass takes tens of milliseconds, the launches saved do

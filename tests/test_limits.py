@@ -14,7 +14,11 @@ PROGRAM = r"""
 int main(int argc, char **argv)
 {
     const unsigned long long pieces = strtoull(argv[1], nullptr, 10), slots = strtoull(argv[2], nullptr, 10);
-    printf("%d %d\n", (int)cvo::plan_fits(pieces, slots), (int)cvo::joint_fits(slots, strtoull(argv[3], nullptr, 10)));
+    // a place among the points of both sides, counted up as the sort's passes do
+    cvo::SortPlace place = (cvo::SortPlace)(cvo::kMaxSidePoints - 1);
+    place += (cvo::SortPlace)(cvo::kMaxSidePoints - 1);
+    printf("%d %d %llu\n", (int)cvo::plan_fits(pieces, slots), (int)cvo::joint_fits(slots, strtoull(argv[3], nullptr, 10)),
+           (unsigned long long)place);
 }
 """
 
@@ -30,7 +34,7 @@ def fits(tmp_path_factory):
     def call(pieces, slots, bytes_per_slot=60):
         out = subprocess.run([exe, str(pieces), str(slots), str(bytes_per_slot)], check=True, capture_output=True,
                              text=True).stdout.split()
-        return out[0] == "1", out[1] == "1"
+        return out[0] == "1", out[1] == "1", int(out[2])
     return call
 
 
@@ -63,3 +67,8 @@ def test_totals_are_not_taken_modulo(fits):
                                                      (2 ** 62 + 1, 4, False)])
 def test_joint_plan(fits, slots, bytes_per_slot, ok):
     assert fits(0, slots, bytes_per_slot)[1] == ok
+
+
+def test_places_of_both_sides(fits):
+    """The last place of a call with as many points as each side may have."""
+    assert fits(0, 0)[2] == 2 * (2 ** 31 - 1)
