@@ -353,7 +353,7 @@ __global__ __launch_bounds__(kRedThreads) void reduce_kernel(const ReduceArgs a)
         // sets of registers: 30,000 queries of about 16 pieces 19.9 -> 15.2 us,
         // 4 pieces 8.8 -> 8.0 us.  Three or four in flight gain 1 us more in the
         // first case and lose as much in sparse ones (6.0 -> 7.0 us).
-        int nj = 0;
+        long long nj = 0;  // (all pairs of a cluster's queries: up to 64 times the references)
         double Wt = 0.0, D0 = 0.0, D1 = 0.0, D2 = 0.0;
         double S0 = 0.0, S1 = 0.0, S2 = 0.0, S3 = 0.0, S4 = 0.0, S5 = 0.0;
         const int n = qm.y;
