@@ -198,8 +198,10 @@ void pair_pass_kernel(const PairPassArgs a)
         // offsets of the reference points then stay what they are while the
         // pose moves by less than that, instead of being rounded anew each
         // iteration, and with the queries' rounding taken off D at the end
-        // the gradient is smooth in the pose.
-        const double q0 = pow2_below(fmax((cut ? rc : ell) * (1.0 / 256.0), 1e-240));
+        // the gradient is smooth in the pose.  A cutoff of many lengthscales
+        // (or one that overflows) counts as four: the pairs that weigh are
+        // within that, and offsets from a centre off by more lose their digits.
+        const double q0 = pow2_below(fmax(fmin(rc * (1.0 / 256.0), ell * (1.0 / 64.0)), 1e-240));
         const double q1 = 1.0 / q0;
         const double cx = uniform_d(rint(nb.cx * q1) * q0), cy = uniform_d(rint(nb.cy * q1) * q0),
                      cz = uniform_d(rint(nb.cz * q1) * q0);
