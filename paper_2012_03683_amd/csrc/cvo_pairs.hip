@@ -240,6 +240,7 @@ void pair_pass_kernel(const PairPassArgs a)
         int cnt = 0;
         double Gf[MODE == 1 ? VF : 1];
         double Ls = 0.0;
+        unsigned long long paired = 0;  // (backward) lanes that took a pair
 #pragma unroll
         for (int k = 0; k < (MODE == 1 ? VF : 1); ++k) Gf[k] = 0.0;
 
@@ -333,6 +334,7 @@ void pair_pass_kernel(const PairPassArgs a)
             const double dx = c.dx() - zsx, dy = c.dy() - zsy, dz = c.dz() - zsz;
             const double s = fma(dz, dz, fma(dy, dy, dx * dx));
             const unsigned long long take = members((float)s, ent, valid);
+            paired |= take;
             if (__builtin_amdgcn_inverse_ballot_w64(take)) {
                 float se = 0.0f, rest = 0.0f;
                 double lin = 0.0;
@@ -532,7 +534,9 @@ void pair_pass_kernel(const PairPassArgs a)
         process(qn);
         wave_sync();
 
-        if (MODE == 1) {
+        // (a lane without pairs takes nothing off: 0 times a feature that is not
+        // finite is not 0)
+        if (MODE == 1 && __builtin_amdgcn_inverse_ballot_w64(paired)) {
 #pragma unroll
             for (int k = 0; k < SED; ++k) Gf[MODE == 1 ? k : 0] -= W * (double)vf[k];
         }
