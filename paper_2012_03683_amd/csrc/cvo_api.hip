@@ -595,11 +595,12 @@ struct PairSpec {
     double rc;
     ViewShape shape;
     int inverse;
+    const double *pose;  // of the queries, to plan at
 };
 
-// Builds the views of `pairs` and plans their pair pass at the poses in the
-// device states, which stand at the start of the call's input buffer with
-// whatever else is uploaded once (head_bytes in all).  head: their host copy,
+// Builds the views of `pairs` and plans their pair pass.  The device states stand at
+// the start of the call's input buffer with whatever else is uploaded once
+// (head_bytes in all).  head: their host copy,
 // uploaded together with the pairs; null on a later build of the same call,
 // which leaves them as they are.  The host waits once, for the piece and slot counts (with the
 // fixed scratch of the allocation-free entry point also for the size of the
@@ -635,6 +636,7 @@ void build_pairs(cvo_context *ctx, Views &v, const std::vector<PairSpec> &pairs,
         o.xb = a.n[0];
         o.zb = a.n[1];
         o.rc = p.rc;
+        std::memcpy(o.pose, p.pose, sizeof(o.pose));
         o.cell_factor = p.shape.cell_factor;
         o.cluster_factor = p.shape.cluster_factor;
         o.cluster_max = p.shape.cluster_max;
@@ -847,16 +849,15 @@ struct Problem {
     int ellobj = 0;         // reduce the lengthscale objective's sums too
 };
 
-// Grid of X, clusters of Z, and the work plan at the pose held in the device
-// state: `head` (states and constants) on a call's first build, later the
-// device's own.
+// Grid of X, clusters of Z, and the work plan at the poses and lengthscales `at`;
+// `head` (states and constants) on a call's first build, later the device's own.
 void build_views(cvo_context *ctx, Problem &p, const std::vector<CloudPtrs> &X, const std::vector<CloudPtrs> &Z,
-                 const std::vector<double> &ell, const std::vector<ViewShape> &shape, const void *head = nullptr,
+                 const std::vector<PairState> &at, const std::vector<ViewShape> &shape, const void *head = nullptr,
                  bool may_split = false)
 {
     p.shape = shape;
     std::vector<PairSpec> pairs(X.size());
-    for (size_t k = 0; k < X.size(); ++k) pairs[k] = PairSpec{X[k], Z[k], p.kappa * ell[k], shape[k], 0};
+    for (size_t k = 0; k < X.size(); ++k) pairs[k] = PairSpec{X[k], Z[k], p.kappa * at[k].ell, shape[k], 0, at[k].T};
     build_pairs(ctx, p.views, pairs, p.lay, p.kappa, head, X.size() * (sizeof(PairState) + sizeof(AlignConst)),
                 may_split ? moment_bytes(p.lay.d4, false) : 0);
     p.mom = moments(ctx, "fm", p.views.nslots, p.lay.d4, false);
@@ -868,13 +869,11 @@ void setup_problem(cvo_context *ctx, Problem &p, const std::vector<CloudPtrs> &X
                    const std::vector<PairState> &st, const std::vector<AlignConst> &ac, bool may_split = false)
 {
     const int B = (int)X.size();
-    std::vector<double> ell(B);
-    for (int b = 0; b < B; ++b) ell[b] = st[b].ell;
     static_assert(sizeof(PairState) % 16 == 0 && sizeof(AlignConst) % 16 == 0, "states, then constants");
     std::vector<char> head(B * (sizeof(PairState) + sizeof(AlignConst)));
     std::memcpy(head.data(), st.data(), B * sizeof(PairState));
     std::memcpy(head.data() + B * sizeof(PairState), ac.data(), B * sizeof(AlignConst));
-    build_views(ctx, p, X, Z, ell, std::vector<ViewShape>(B, fixed_shape(ctx)), head.data(), may_split);
+    build_views(ctx, p, X, Z, st, std::vector<ViewShape>(B, fixed_shape(ctx)), head.data(), may_split);
     p.d_state = reinterpret_cast<PairState *>(p.views.d_head);
     p.d_ac = reinterpret_cast<AlignConst *>(p.views.d_head + B * sizeof(PairState));
 }
@@ -1141,8 +1140,9 @@ void align_many(cvo_context *ctx, const std::vector<CloudPtrs> &X, const std::ve
     // shrank, or its pair density fell a class) -- a function of the iterates
     // alone.  With adaptive shapes, the first iteration runs by itself and its
     // measured density picks the first shape.
-    std::vector<double> ell_build(B);
-    for (int b = 0; b < B; ++b) ell_build[b] = prm[b].ell_init;
+    // A pair that shares a build with others that need one, but does not need it, is
+    // planned where it was: its sums are the bits that it gives alone.
+    std::vector<PairState> built = st;
     bool probe = adapt;
     std::vector<PairState> now(B);
     // Every launched iteration either ends a running pair or advances its
@@ -1225,7 +1225,7 @@ void align_many(cvo_context *ctx, const std::vector<CloudPtrs> &X, const std::ve
             const ViewShape want = adapt ? density_shape(ctx, cls, p.lay) : fixed_shape(ctx);
             if (now[b].pause || !(want == p.shape[b])) {
                 rebuild = true;
-                ell_build[b] = now[b].ell;
+                built[b] = now[b];
                 shape[b] = want;
                 now[b].rc_build = p.kappa * now[b].ell;
             }
@@ -1235,7 +1235,7 @@ void align_many(cvo_context *ctx, const std::vector<CloudPtrs> &X, const std::ve
         }
         probe = false;
         if (all_done) break;
-        if (rebuild) build_views(ctx, p, X, Z, ell_build, shape);
+        if (rebuild) build_views(ctx, p, X, Z, built, shape);
         if (changed) ctx->upload(p.d_state, now.data(), sizeof(PairState) * B);
         ref = now;
     }
@@ -1676,10 +1676,11 @@ cvo_status cvo_inner_product_backward(cvo_handle h, const cvo_cloud *X, const cv
         // queries X (pose T^-1) against the Z grid; both in the same launches
         const bool target = dZ || dV || dEll, source = dX || dU;
         std::vector<PairSpec> sides;
-        if (target) sides.push_back(PairSpec{to_ptrs(X), to_ptrs(Z), rc, fixed_shape(h), 0});
-        if (source) sides.push_back(PairSpec{to_ptrs(Z), to_ptrs(X), rc, fixed_shape(h), 1});
+        const PairState s0 = init_state(T, kp->ell);
+        if (target) sides.push_back(PairSpec{to_ptrs(X), to_ptrs(Z), rc, fixed_shape(h), 0, s0.T});
+        if (source) sides.push_back(PairSpec{to_ptrs(Z), to_ptrs(X), rc, fixed_shape(h), 1, s0.Tinv});
         auto run = [&](const std::vector<PairSpec> &sides) {
-            const std::vector<PairState> st(sides.size(), init_state(T, kp->ell));
+            const std::vector<PairState> st(sides.size(), s0);
             Views v;
             build_pairs(h, v, sides, lay, kp->kappa, st.data(), sizeof(PairState) * st.size(),
                         moment_bytes(lay.d4, true));

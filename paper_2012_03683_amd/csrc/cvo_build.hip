@@ -165,10 +165,11 @@ __global__ __launch_bounds__(1024) void params_kernel(const ViewArgs a)
                 cp.iq = 1.0 / q;
                 cp.cap = cap;
                 cp.level = L;
-                cp.pad = 0;
-                a.cp[b] = cp;
                 // quanta along the widest axis (+1 for rounding at the far face)
-                atomicMax(&s_mbits, max(L, bits_for((unsigned long long)floor(ext / q) + 1)));
+                cp.bits = min(max(max(L, 1), bits_for((unsigned long long)floor(ext / q) + 1)), maxbits);
+                cp.cand = 0;
+                a.cp[b] = cp;
+                atomicMax(&s_mbits, cp.bits);
             }
         }
         __syncthreads();
@@ -190,9 +191,8 @@ __global__ __launch_bounds__(1024) void params_kernel(const ViewArgs a)
         f.bad = s_bad;
         f.overflow = base > a.cell_cap;
         f.nclus = 0;
-        f.cand = 0;
         f.kbits = bits_for((unsigned long long)s_max);  // the cell count itself must fit
-        f.mbits = min(s_mbits, maxbits);
+        f.mbits = s_mbits;
         f.sbits[0] = f.kbits + cbits;
         f.sbits[1] = 3 * f.mbits + cbits;
     }
@@ -306,10 +306,11 @@ __global__ __launch_bounds__(1024) void key_kernel(const ViewArgs a)
                   (unsigned long long)g.nx * ((unsigned long long)iy + (unsigned long long)g.ny * iz);
             key |= (unsigned long long)b << a.info->kbits;
         } else {
+            // (the curve of the pair's own bits: another number of them turns it)
             const ClusterParam &g = a.cp[b];
-            const int lim = 1 << a.info->mbits;
+            const int lim = 1 << g.bits;
             key = hilbert3(cell_of(xyz[0], g.ox, g.iq, lim), cell_of(xyz[1], g.oy, g.iq, lim),
-                           cell_of(xyz[2], g.oz, g.iq, lim), a.info->mbits);
+                           cell_of(xyz[2], g.oz, g.iq, lim), g.bits);
             key |= (unsigned long long)b << (3 * a.info->mbits);
         }
         const long long o = (side ? a.n[0] : 0) + i;
@@ -863,13 +864,11 @@ __global__ __launch_bounds__(kClusThreads) void cluster_kernel(const ViewArgs a,
         int C = 0;
         if (k < nh) {
             const int kb = s_b[k];
-            const PairState *st = a.state + kb;
-            const double *P = a.in[kb].inverse ? st->Tinv : st->T;
             double Pm[12];
 #pragma unroll
-            for (int i = 0; i < 12; ++i) Pm[i] = P[i];
+            for (int i = 0; i < 12; ++i) Pm[i] = a.in[kb].pose[i];
             const GridDesc gd = a.grid[kb];
-            const Neighbourhood nb = neighbourhood(Pm, s_geo[k], kappa * st->ell, cut, gd);
+            const Neighbourhood nb = neighbourhood(Pm, s_geo[k], a.in[kb].rc, cut, gd);
             if (nb.any) {
                 const int nyr = nb.iy1 - nb.iy0 + 1, nrows = nyr * (nb.iz1 - nb.iz0 + 1);
                 const BallRows br = ball_rows(nb, gd, cut);
@@ -888,12 +887,17 @@ __global__ __launch_bounds__(kClusThreads) void cluster_kernel(const ViewArgs a,
     }
     __syncthreads();
     const int C = tid < nh ? s_C[tid] : 0;
-    const int ic = wave_scan_add(C);
-    if (lane == 63) s_w[wv] = ic;
-    __syncthreads();
-    if (tid == 0 && nh > 0) {
-        s_cbase = atomicAdd(&a.info->nclus, nh);
-        atomicAdd(&a.info->cand, (unsigned long long)s_w[0] + s_w[1] + s_w[2] + s_w[3]);
+    if (tid == 0 && nh > 0) s_cbase = atomicAdd(&a.info->nclus, nh);
+    // the candidates, by pair: one add a wave where it has clusters of one pair
+    if (wv * 64 < nh) {
+        const int mine = s_b[min(tid, nh - 1)], first = wave_uniform(mine);
+        if (__all(mine == first)) {
+            unsigned long long sum = C;
+            for (int off = 32; off > 0; off >>= 1) sum += __shfl_xor(sum, off);
+            if (lane == 0) atomicAdd(&a.cp[first].cand, sum);
+        } else if (tid < nh) {
+            atomicAdd(&a.cp[mine].cand, (unsigned long long)C);
+        }
     }
     __syncthreads();
     if (tid < nh) {
@@ -911,7 +915,7 @@ __global__ __launch_bounds__(kClusThreads) void cluster_kernel(const ViewArgs a,
 }
 
 // The pieces of every cluster, c_max = max(floor, work / n) candidates each (the
-// floor from the candidates of all clusters, see kPieceTarget), their output
+// floor from the candidates of the pair's clusters, see kPieceTarget), their output
 // slots, their places in the dispatch order's cost buckets and the query map.
 // A block reserves slots and bucket places for its 256 clusters with one
 // atomic each (an atomic per cluster serialises on the few buckets that most
@@ -927,8 +931,6 @@ __global__ __launch_bounds__(256) void plan_kernel(const ViewArgs a)
     __shared__ int s_w[4], s_w2[4];
     __shared__ unsigned long long s_base;  // first slot of the block's clusters
     const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
-    const unsigned long long even = (a.info->cand / kPieceTarget + 63) & ~63ULL;
-    const int floor_ = (int)min(max(even, (unsigned long long)kPieceFew), (unsigned long long)kPieceMany);
     for (int k = tid; k < kCostBuckets; k += 256) s_hist[k] = 0;
     ClusterRec *rec = a.clus + c0 + tid;
     const bool in = c0 + tid < nclus;
@@ -937,6 +939,8 @@ __global__ __launch_bounds__(256) void plan_kernel(const ViewArgs a)
         n = rec->n;
         C = rec->cand;
         first = rec->first;
+        const unsigned long long even = (a.cp[rec->b].cand / kPieceTarget + 63) & ~63ULL;
+        const int floor_ = (int)min(max(even, (unsigned long long)kPieceFew), (unsigned long long)kPieceMany);
         const int cm = max(floor_, a.work / n);
         np = C > 0 ? min((C + cm - 1) / cm, 4096) : 1;
     }

@@ -38,8 +38,9 @@ constexpr int kMaxPasses = 8;     // 8-bit passes over a 64-bit key
 constexpr long long kCellCap = 1LL << 23;  // cells of one cloud's grid
 constexpr int kCurveBits = 16;    // bits per axis of the query order's curve
 constexpr int kBoxBlocks = 64;    // partial bounding boxes per cloud
-// Candidates of a piece, at least: as many as leave about kPieceTarget pieces,
-// within [kPieceFew, kPieceMany].  The chip holds 4,096-5,120 waves of the pair
+// Candidates of a piece, at least: as many as leave its pair about kPieceTarget
+// pieces, within [kPieceFew, kPieceMany].  (Of the pair alone, so that its sums
+// are the same bits whatever else is in the call.)  The chip holds 4,096-5,120 waves of the pair
 // pass at once.  With fewer pieces than that the longest piece is the pass, so
 // short pieces win; with many more, a piece's fixed cost and its partials do.
 // Pair pass + reduction, us, at least 512 / 256 / 128 candidates / this rule:
@@ -131,6 +132,7 @@ struct alignas(16) PairIn {
     long long nx, nz;
     long long xb, zb;      // first sorted index of each cloud among its side's clouds
     double rc;             // cutoff radius (infinite: none)
+    double pose[12];       // the pose of the queries to plan at
     double cell_factor, cluster_factor;
     int cluster_max;
     int octree;            // cluster rule: 1 octree blocks, 0 halved chunks
@@ -144,7 +146,8 @@ struct alignas(16) ClusterParam {
     double iq;             // 1 / quantum (edge of a level-0 block)
     double cap;            // largest cluster bounding-box edge (chunk rule)
     int level;             // largest octree level of a cluster (octree rule)
-    int pad;
+    int bits;              // curve bits per axis of this pair
+    unsigned long long cand;  // candidates of its clusters (counted by the planner)
 };
 
 constexpr int kCostBuckets = 512;  // dispatch order of the pieces: heaviest bucket first
@@ -157,8 +160,7 @@ struct BuildInfo {
     int bad;                   // a cloud has a non-finite coordinate
     int overflow;              // the cell tables do not fit: nothing after the boxes was done
     int nclus;                 // clusters of all pairs
-    unsigned long long cand;   // candidates of all clusters
-    int kbits, mbits;          // cell-index bits, curve bits per axis (the pair index sits above)
+    int kbits, mbits;          // cell-index bits, curve bits per axis, the most of any pair (the pair index sits above)
     int sbits[2];              // key bits to sort: reference side, query side
     int hist[kCostBuckets];    // pieces per cost bucket
 };

@@ -34,7 +34,7 @@ struct ViewArgs {
     float4 *pts[2];
     float *feat[2];
     int *perm;                    // query side: sorted -> own cloud's index
-    const PairState *state;       // poses to plan at
+    const PairState *state;       // of the pairs (for the callers; a plan's poses are in `in`)
     ClusterRec *clus;
     int4 *qmap;
     int work;                     // query x candidate products per piece
