@@ -171,7 +171,8 @@ typedef struct {
 #define CVO_CLUSTER_OCTREE 0
 #define CVO_CLUSTER_CHUNKS 1
 
-/* Tuning knobs (picked by cvo_autotune or set by hand). */
+/* Tuning knobs (picked by cvo_autotune or set by hand).  A handle starts with
+ * {16, 0.5, 1.25, 0.6, 16, 512, CVO_CLUSTER_CHUNKS, 1}. */
 typedef struct {
     int32_t cluster_max;   /* max query points per cluster: 8, 16, 32 or 64 */
     double cell_factor;    /* grid cell edge / cutoff radius, in [0.25, 4] */
@@ -186,13 +187,11 @@ typedef struct {
                             * cluster_factor and cluster_rule at every view build from the in-cutoff
                             * pairs per query point of its latest iteration (chunk clusters throughout).
                             * Padded feature rows of more than 8 floats: >= 500: 32, 0.5, 0.5;
-                            * >= 200: 16, 0.5, 1.0; fewer: 16, 1.0, 1.0.  Rows of at most 8 floats:
-                            * >= 100: 32, 0.5, 1.0; fewer: 16, 1.0, 1.5.  Not yet measured: the fields
-                            * above.  One-shot calls, and a registration's first view, use the
-                            * fields above too -- except that while adaptive is 1 and none of
-                            * cluster_max, cell_factor, cluster_factor and cluster_rule has been
-                            * changed by cvo_set_tuning or chosen by cvo_autotune they use chunk
-                            * clusters 16, 0.5, 1.0 (cvo_evaluate_noalloc always the fields). */
+                            * >= 200: 16, 0.5, 1.0; fewer: 16, 1.0, 1.5.  Rows of at most 8 floats:
+                            * >= 100: 16, 0.5, 1.25; fewer: 16, 1.0, 1.5.  Not yet measured, one-shot
+                            * calls and a registration's first view: the fields above
+                            * (cvo_evaluate_noalloc: octree clusters 16, 1.0, 0.5 in place of the
+                            * shape a handle starts with, to spare its scratch). */
 } cvo_tuning;
 
 /* Per-handle timing of the dominant kernel, measured with HIP events on the

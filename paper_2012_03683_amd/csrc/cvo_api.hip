@@ -93,8 +93,7 @@ struct cvo_context {
     std::map<std::string, Buf> bufs;
     void *pinned = nullptr;
     size_t pinned_cap = 0;
-    cvo_tuning tuning{16, 1.0, 0.5, 0.6, 16, 512, CVO_CLUSTER_OCTREE, 1};
-    bool shape_set = false;  // a shape field of `tuning` has been set or tuned
+    cvo_tuning tuning{16, 0.5, 1.25, 0.6, 16, 512, CVO_CLUSTER_CHUNKS, 1};
     bool profiling = false;
     cvo_timing timing{0, 0.0, 0, 0, 0, 0, 0, 0};
     std::vector<hipEvent_t> ev_free;
@@ -522,20 +521,26 @@ struct ViewShape {
     }
 };
 
-// The shape of one-shot calls and of a registration's first view.  Until a
-// shape field has been set or tuned it is 16-point chunks, half-radius cells
-// and clusters up to one radius wide: within 15% of the best of 27 shapes at
-// every density measured, where the fields' own defaults are up to 1.8x off
-// (pair pass, us, this shape / the fields' defaults / the best: stereo 30,000
-// at ell 0.95 180 / 286 / 156, 0.5 79 / 129 / 76, 0.25 39 / 57 / 38, 0.1
-// 24 / 31 / 22; RGB-D 40,000 at 0.1 66 / 108 / 62, 0.05 33 / 45 / 31).  The
-// allocation-free entry point keeps the fields: finer cells would take more of
-// its fixed scratch.
+// The shape of one-shot calls and of a registration's first view: the tuning's
+// fields.  As a handle starts they are 16-point chunks, half-radius cells and
+// clusters up to 1.25 radii wide.  With edges of one radius they are within 16% of
+// the best of 27 shapes at every density measured, where 16-point octree
+// clusters up to half a radius wide on cells of one radius are up to 1.8x off
+// (pair pass, us, chunks / octree / the best: stereo 30,000 at ell 0.95 180 / 286 /
+// 156, 0.5 79 / 129 / 76, 0.25 39 / 57 / 38, 0.1 24 / 31 / 22; RGB-D 40,000 at 0.1
+// 66 / 108 / 62, 0.05 33 / 45 / 31).  Edges of 1.25 / 1.0 / 0.75 radii, at another
+// pose: stereo 248.6 / 249.1 / 246.0, 137.9 / 138.0 / 136.5, 63.0 / 63.6 / 62.8, 27.2 /
+// 27.9 / 29.8; RGB-D 65.1 / 65.2 / 62.1, 31.4 / 33.6 / 33.9.  The allocation-free
+// entry point takes that octree shape in place of the start's: half-radius cells,
+// up to eight times as many, would take more of its fixed scratch and refuse
+// clouds that fit.
+constexpr ViewShape kStartShape{16, 0.5, 1.25, CVO_CLUSTER_CHUNKS};
+
 ViewShape fixed_shape(const cvo_context *ctx)
 {
-    if (ctx->tuning.adaptive && !ctx->shape_set && !ctx->fixed.on) return ViewShape{16, 0.5, 1.0, CVO_CLUSTER_CHUNKS};
-    return ViewShape{ctx->tuning.cluster_max, ctx->tuning.cell_factor, ctx->tuning.cluster_factor,
-                     ctx->tuning.cluster_rule};
+    const ViewShape set{ctx->tuning.cluster_max, ctx->tuning.cell_factor, ctx->tuning.cluster_factor,
+                        ctx->tuning.cluster_rule};
+    return ctx->fixed.on && set == kStartShape ? ViewShape{16, 1.0, 0.5, CVO_CLUSTER_OCTREE} : set;
 }
 
 // Density classes and their view shapes, measured per feature layout (a
@@ -547,7 +552,8 @@ ViewShape fixed_shape(const cvo_context *ctx)
 // pass, us: rows over 8 floats, 16 / 1.0 / 1.5 against 16 / 1.0 / 1.0 below 200
 // pairs per query: 27.1 / 27.4 at 138, 21.6 / 24.2 at 62.  Rows of at most 8,
 // 16 / 0.5 / 1.0 against 32 / 0.5 / 1.0 from 100: 66 / 70 at 838, 45 / 46 at 406,
-// 33 / 41 at 195 (RGB-D registrations 1.05x and 1.07x).
+// 33 / 41 at 195 (RGB-D registrations 1.05x and 1.07x); 16 / 0.5 / 1.25 is as
+// fast (65.1 / 65.2, 44.7 / 43.3, 31.4 / 33.6), and a registration keeps its first view.
 bool light_layout(const FeatLayout &lay) { return lay.d4 <= 8; }
 
 void class_thresholds(const FeatLayout &lay, double t[3])
@@ -570,7 +576,7 @@ ViewShape density_shape(cvo_context *ctx, int cls, const FeatLayout &lay)
     const int r = CVO_CLUSTER_CHUNKS;
     switch (cls) {
     case 3: return ViewShape{32, 0.5, 0.5, r};
-    case 2: return light ? ViewShape{16, 0.5, 1.0, r} : ViewShape{32, 0.5, 0.5, r};
+    case 2: return light ? kStartShape : ViewShape{32, 0.5, 0.5, r};
     case 1: return light ? ViewShape{16, 1.0, 1.5, r} : ViewShape{16, 0.5, 1.0, r};
     case 0: return ViewShape{16, 1.0, 1.5, r};
     default: return fixed_shape(ctx);
@@ -1747,10 +1753,6 @@ cvo_status cvo_set_tuning(cvo_handle h, const cvo_tuning *in)
         require(in->adaptive == 0 || in->adaptive == 1, "adaptive must be 0 or 1");
         require(in->cluster_rule == CVO_CLUSTER_OCTREE || in->cluster_rule == CVO_CLUSTER_CHUNKS,
                 "cluster_rule must be CVO_CLUSTER_OCTREE or CVO_CLUSTER_CHUNKS");
-        const cvo_tuning &t = h->tuning;
-        if (in->cluster_max != t.cluster_max || in->cell_factor != t.cell_factor ||
-            in->cluster_factor != t.cluster_factor || in->cluster_rule != t.cluster_rule)
-            h->shape_set = true;
         h->tuning = *in;
     });
 }
@@ -1792,13 +1794,10 @@ cvo_status cvo_autotune(cvo_handle h, const cvo_cloud *X, const cvo_cloud *Z, co
             h->tuning.cell_factor = t.cell_factor;
             h->tuning.cluster_factor = t.cluster_factor;
             h->tuning.cluster_rule = t.cluster_rule;
-            h->shape_set = true;
             if (chosen) *chosen = h->tuning;
             return;
         }
         const cvo_tuning base = h->tuning;
-        const bool base_set = h->shape_set;
-        h->shape_set = true;  // every build below uses the shape it sets
         const bool prof = h->profiling;
         const cvo_timing saved = h->timing;
         h->profiling = false;
@@ -1856,7 +1855,6 @@ cvo_status cvo_autotune(cvo_handle h, const cvo_cloud *X, const cvo_cloud *Z, co
                         }
         } catch (...) {
             h->tuning = base;
-            h->shape_set = base_set;
             h->profiling = prof;
             h->timing = saved;
             throw;
