@@ -91,7 +91,7 @@ __global__ __launch_bounds__(1024) void params_kernel(const ViewArgs a)
     __shared__ int s_bad, s_mbits, s_max;
     const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
     const int cbits = bits_for((unsigned long long)(a.B - 1));
-    const int maxbits = min(kCurveBits, (62 - cbits) / 3);
+    const int maxbits = min(kCurveBits, (kKeyBits - cbits) / 3);
     if (threadIdx.x == 0) { s_bad = 0; s_mbits = 1; s_max = 1; }
     for (int i = threadIdx.x; i < kCostBuckets; i += 1024) a.info->hist[i] = 0;
     long long base = 0;  // (thread 0)
@@ -1063,7 +1063,7 @@ void launch_views(const ViewArgs &a, const FeatLayout &lay, double kappa, hipStr
     while ((1LL << cbits) < a.B) ++cbits;
     // key bits of each side, at most (the device knows the exact number and
     // skips passes beyond it)
-    const int most[2] = {24 + cbits, 3 * std::min(kCurveBits, (62 - cbits) / 3) + cbits};
+    const int most[2] = {24 + cbits, 3 * std::min(kCurveBits, (kKeyBits - cbits) / 3) + cbits};
     const int passes = (std::max(most[0], most[1]) + 7) / 8;
     const int tiles = std::max(tiles_of(a.n[0]), tiles_of(a.n[1]));
     if (tiles > 0) {

@@ -36,7 +36,15 @@ constexpr int kRadixTile = 1024;  // keys per workgroup and pass of the radix so
 constexpr int kTableTiles = 128;  // sorts of at most this many tiles keep a digit table per pass (one launch a pass)
 constexpr int kMaxPasses = 8;     // 8-bit passes over a 64-bit key
 constexpr long long kCellCap = 1LL << 23;  // cells of one cloud's grid
-constexpr int kCurveBits = 16;    // bits per axis of the query order's curve
+// Bits per axis of the query order's curve.  The smallest octree block is within
+// cluster_factor * r_c while the cloud's extent is within 2^19 of those edges, and
+// the order resolves 16 parts of an edge within 2^15 of them.  With 16 bits (two sort
+// launches a build fewer, 2 us) both ended at an eighth of that extent: 20,000 points
+// and one 10^5 m off, ell 0.15: an evaluation 1,358 us, with 19 bits 520 us.
+constexpr int kCurveBits = 19;
+// Bits of a sort key: the curve's, and the pair above them (all 19 per axis up to 64
+// pairs; the top bit stays clear, so no key is the all-ones mark of no point).
+constexpr int kKeyBits = 63;
 constexpr int kBoxBlocks = 64;    // partial bounding boxes per cloud
 // Candidates of a piece, at least: as many as leave its pair about kPieceTarget
 // pieces, within [kPieceFew, kPieceMany].  (Of the pair alone, so that its sums
