@@ -715,14 +715,6 @@ __global__ __launch_bounds__(256) void view_kernel(const ViewArgs a, const FeatL
 }
 
 // ---------------------------------------------------------------- clusters and plan
-// A piece's cost bucket, non-decreasing in the cost: steps of 96 below 49152
-// (every piece of the default plan: n <= 64 queries x at most 576), none
-// heavier apart above.
-__device__ __forceinline__ int cost_bucket(unsigned long long cost)
-{
-    return (int)min(cost / 96ULL, (unsigned long long)(kCostBuckets - 1));
-}
-
 constexpr int kHalo = 64;         // points beside a block that a cluster may reach
 constexpr int kClusThreads = 256;
 constexpr int kClusBlocks = 256;  // blocks up to which a block takes fewer points

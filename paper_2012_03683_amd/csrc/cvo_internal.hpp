@@ -158,8 +158,6 @@ struct alignas(16) ClusterParam {
     unsigned long long cand;  // candidates of its clusters (counted by the planner)
 };
 
-constexpr int kCostBuckets = 512;  // dispatch order of the pieces: heaviest bucket first
-
 // State of one view build, on the device.
 struct BuildInfo {
     unsigned long long pieces; // pieces planned

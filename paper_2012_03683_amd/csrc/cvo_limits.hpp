@@ -1,4 +1,4 @@
-// cvo_limits.hpp -- limits of a view build and its work plan, in host arithmetic.
+// cvo_limits.hpp -- limits and integer rules of a view build and its work plan.
 #pragma once
 #include <limits>
 
@@ -31,6 +31,21 @@ constexpr unsigned long long kJointBytes = 4ULL << 30;
 constexpr bool joint_fits(unsigned long long slots, unsigned long long bytes_per_slot)
 {
     return slots < kMaxSlots && slots * bytes_per_slot <= kJointBytes;
+}
+
+// A piece's bucket in the dispatch order (heaviest bucket first), non-decreasing in
+// its cost: steps of 96 up to 36,864 (every piece of the default plan: n <= 64
+// queries x at most 576), then four buckets an octave, to the largest cost there is
+// (64 queries x 2^30 candidates).
+constexpr int kCostBuckets = 512;
+constexpr unsigned long long kCostLinear = 384 * 96;
+
+constexpr int cost_bucket(unsigned long long cost)
+{
+    if (cost <= kCostLinear) return (int)(cost / 96);
+    const unsigned long long m = cost / (kCostLinear / 4);  // >= 4
+    const int octave = 61 - __builtin_clzll(m);
+    return 385 + 4 * octave + (int)((m >> octave) & 3);
 }
 
 }  // namespace cvo

@@ -13,6 +13,11 @@ PROGRAM = r"""
 #include "cvo_limits.hpp"
 int main(int argc, char **argv)
 {
+    if (argc == 2) {  // costs on standard input, their buckets on standard output
+        unsigned long long cost;
+        while (scanf("%llu", &cost) == 1) printf("%d\n", cvo::cost_bucket(cost));
+        return 0;
+    }
     const unsigned long long pieces = strtoull(argv[1], nullptr, 10), slots = strtoull(argv[2], nullptr, 10);
     // a place among the points of both sides, counted up as the sort's passes do
     cvo::SortPlace place = (cvo::SortPlace)(cvo::kMaxSidePoints - 1);
@@ -31,7 +36,11 @@ def fits(tmp_path_factory):
     subprocess.run(["g++", "-std=c++17", "-Wall", "-Werror", "-I", os.path.join(ROOT, "paper_2012_03683_amd", "csrc"),
                     str(d / "limits.cpp"), "-o", exe], check=True)
 
-    def call(pieces, slots, bytes_per_slot=60):
+    def call(pieces, slots=0, bytes_per_slot=60):
+        if isinstance(pieces, list):
+            out = subprocess.run([exe, "buckets"], input=" ".join(map(str, pieces)), check=True, capture_output=True,
+                                 text=True).stdout
+            return [int(b) for b in out.split()]
         out = subprocess.run([exe, str(pieces), str(slots), str(bytes_per_slot)], check=True, capture_output=True,
                              text=True).stdout.split()
         return out[0] == "1", out[1] == "1", int(out[2])
@@ -72,3 +81,17 @@ def test_joint_plan(fits, slots, bytes_per_slot, ok):
 def test_places_of_both_sides(fits):
     """The last place of a call with as many points as each side may have."""
     assert fits(0, 0)[2] == 2 * (2 ** 31 - 1)
+
+
+def test_cost_buckets(fits):
+    """Non-decreasing and within the table; steps of 96 for every piece of the default
+    plan; above, costs a quarter apart are told apart up to the largest there is."""
+    top = 64 * (2 ** 30 + 64)
+    costs = sorted(set(list(range(0, 40_000, 7)) + [36_864, 36_865] + [int(36_864 * 1.1 ** k) for k in range(150)] + [top]))
+    costs = [c for c in costs if c <= top]
+    b = fits(costs)
+    assert all(x <= y for x, y in zip(b, b[1:])) and b[0] == 0 and b[-1] < 512
+    assert all(x == c // 96 for c, x in zip(costs, b) if c <= 36_864)
+    above = [36_865 * 5 ** k // 4 ** k for k in range(64) if 36_865 * 5 ** k // 4 ** k <= top]
+    u = fits(above)
+    assert len(above) > 60 and all(x < y for x, y in zip(u, u[1:]))
