@@ -556,11 +556,10 @@ ViewShape fixed_shape(const cvo_context *ctx)
 // fast (65.1 / 65.2, 44.7 / 43.3, 31.4 / 33.6), and a registration keeps its first view.
 bool light_layout(const FeatLayout &lay) { return lay.d4 <= 8; }
 
-void class_thresholds(const FeatLayout &lay, double t[3])
+void class_thresholds(const FeatLayout &lay, double t[2])
 {
-    t[0] = INFINITY;  // (no class 3: the densest shape is also class 2's)
-    t[1] = light_layout(lay) ? 100.0 : 500.0;
-    t[2] = light_layout(lay) ? 0.0 : 200.0;
+    t[0] = light_layout(lay) ? 100.0 : 500.0;
+    t[1] = light_layout(lay) ? 0.0 : 200.0;
 }
 
 ViewShape density_shape(cvo_context *ctx, int cls, const FeatLayout &lay)
@@ -575,7 +574,6 @@ ViewShape density_shape(cvo_context *ctx, int cls, const FeatLayout &lay)
     }
     const int r = CVO_CLUSTER_CHUNKS;
     switch (cls) {
-    case 3: return ViewShape{32, 0.5, 0.5, r};
     case 2: return light ? kStartShape : ViewShape{32, 0.5, 0.5, r};
     case 1: return light ? ViewShape{16, 1.0, 1.5, r} : ViewShape{16, 0.5, 1.0, r};
     case 0: return ViewShape{16, 1.0, 1.5, r};
@@ -976,7 +974,7 @@ AlignConst const_for(const cvo_align_params *ap, long long N, long long M)
     }
     a.rebuild_ratio = 1.0;
     a.adaptive = 0;
-    a.cls_t[0] = a.cls_t[1] = a.cls_t[2] = INFINITY;
+    a.cls_t[0] = a.cls_t[1] = INFINITY;
     a.sqrt_nm = std::sqrt((double)N * (double)M);
     a.inv_m = M > 0 ? 1.0 / (double)M : 0.0;
     return a;
@@ -1869,9 +1867,9 @@ cvo_status cvo_autotune(cvo_handle h, const cvo_cloud *X, const cvo_cloud *Z, co
         out.cluster_factor = best.cluster_factor;
         h->tuning = out;
         h->tune_cache[key] = out;
-        double t3[3];
-        class_thresholds(lay, t3);
-        const int cls = density_class(npairs / (double)Z->n, t3);
+        double t[2];
+        class_thresholds(lay, t);
+        const int cls = density_class(npairs / (double)Z->n, t);
         h->class_shape[{light_layout(lay) ? 1 : 0, cls}] =
             cvo_context::Shape{out.cluster_max, out.cell_factor, out.cluster_factor, out.cluster_rule};
         if (chosen) *chosen = out;
@@ -1926,6 +1924,7 @@ cvo_status cvo_load_tuning(cvo_handle h, const char *path)
                 header = std::sscanf(line, "cvo-tuning %d", &ver) == 1 && ver == 1;
                 if (!header) { bad = true; break; }
             } else if (std::sscanf(line, "class %d %d %d %lf %lf %d", &a, &b, &cm, &cell, &cf, &rule) == 6) {
+                // (class 3 of older files is taken and never used)
                 if (!valid(cm, cell, cf, rule) || (a != 0 && a != 1) || b < 0 || b > 3) { bad = true; break; }
                 cls_tab[{a, b}] = cvo_context::Shape{cm, cell, cf, rule};
             } else if (std::sscanf(line, "oneshot %255s %d %lf %lf %d", key, &cm, &cell, &cf, &rule) == 5) {

@@ -92,10 +92,10 @@ struct alignas(16) PairState {
 };
 
 // Density class of an evaluation from its in-cutoff pairs per query point
-// (-1: unknown): 3 from t[0], 2 from t[1], 1 from t[2], else 0.
-__host__ __device__ inline int density_class(double ppq, const double t[3])
+// (-1: unknown): 2 from t[0], 1 from t[1], else 0.
+__host__ __device__ inline int density_class(double ppq, const double t[2])
 {
-    return !(ppq >= 0.0) ? -1 : (ppq >= t[0] ? 3 : (ppq >= t[1] ? 2 : (ppq >= t[2] ? 1 : 0)));
+    return !(ppq >= 0.0) ? -1 : (ppq >= t[0] ? 2 : (ppq >= t[1] ? 1 : 0));
 }
 
 // Per-pair constants of the ascent.
@@ -111,7 +111,7 @@ struct alignas(16) AlignConst {
     int ell_mode;        // 0: annealing (Sec. IV), 1: adaptive (maximiser of the lengthscale objective)
     double ell_init;     // adaptive mode: upper clamp of ell
     int adaptive;        // nonzero: also pause when the density class drops below cls_built
-    double cls_t[3];     // pairs per query where density classes 3, 2 and 1 begin
+    double cls_t[2];     // pairs per query where density classes 2 and 1 begin
     const double *ell_sched;  // replay: lengthscale of every iteration (device; null: annealing)
     long long n_sched;        // replay: iterations to run
 };

@@ -113,7 +113,6 @@ void pair_pass_kernel(const PairPassArgs a)
     constexpr int D = SED + LIND;
     constexpr int D4 = (D + 3) & ~3;
     constexpr int F4 = D4 / 4;
-    constexpr int F4s = F4 > 0 ? F4 : 1;
     constexpr int VF = D4 > 0 ? D4 : 1;
     // candidate queue, one entry of E4 float4s per candidate: the scaled
     // coordinates relative to the cluster centre and the source index's bits
