@@ -8,7 +8,6 @@
 
 #include <algorithm>
 #include <cmath>
-#include <cstddef>
 #include <cstdio>
 #include <cstring>
 #include <map>
@@ -664,6 +663,7 @@ void build_pairs(cvo_context *ctx, Views &v, const std::vector<PairSpec> &pairs,
     a.box = ctx->get_t<float>("v.box", 2 * (size_t)B * kBoxBlocks * 8);
     a.grid = ctx->get_t<GridDesc>("v.grid", B);
     a.cp = ctx->get_t<ClusterParam>("v.cp", B);
+    a.cand = ctx->get_t<unsigned long long>("v.cand", B);
     a.info = ctx->get_t<BuildInfo>("v.info", 1);
     for (int k = 0; k < 2; ++k) {
         a.key[k] = ctx->get_t<unsigned long long>(k ? "v.key1" : "v.key0", n0 + n1);
@@ -680,15 +680,7 @@ void build_pairs(cvo_context *ctx, Views &v, const std::vector<PairSpec> &pairs,
     a.work = ctx->tuning.piece_work;
     if (head) launch_boxes(a, ctx->stream);
 
-    // the head of BuildInfo, which is all the host reads of it
-    struct {
-        unsigned long long pieces, slots;
-        long long cells;
-        int bad, overflow;
-    } info;
-    static_assert(offsetof(BuildInfo, slots) == 8 && offsetof(BuildInfo, cells) == 16 &&
-                      offsetof(BuildInfo, bad) == 24 && offsetof(BuildInfo, overflow) == 28 && sizeof(info) == 32,
-                  "head of BuildInfo");
+    BuildInfo info;
     // the cell tables' size is not known here: they go into what the arena
     // holds (at least one full table), and are built again if that was too little
     size_t cells = std::max(ctx->room<int>("v.cells"), (size_t)kCellCap + 2);

@@ -167,7 +167,7 @@ __global__ __launch_bounds__(1024) void params_kernel(const ViewArgs a)
                 cp.level = L;
                 // quanta along the widest axis (+1 for rounding at the far face)
                 cp.bits = min(max(max(L, 1), bits_for((unsigned long long)floor(ext / q) + 1)), maxbits);
-                cp.cand = 0;
+                a.cand[b] = 0;
                 a.cp[b] = cp;
                 atomicMax(&s_mbits, cp.bits);
             }
@@ -195,6 +195,7 @@ __global__ __launch_bounds__(1024) void params_kernel(const ViewArgs a)
         f.mbits = s_mbits;
         f.sbits[0] = f.kbits + cbits;
         f.sbits[1] = 3 * f.mbits + cbits;
+        f.passes = max(a.n[0] > 1 ? (f.sbits[0] + 7) / 8 : 0, a.n[1] > 1 ? (f.sbits[1] + 7) / 8 : 0);
     }
 }
 
@@ -349,8 +350,12 @@ __device__ inline SortPlace block_exclusive_scan(SortPlace v, SortPlace *total)
     return incl - v;
 }
 
-__global__ __launch_bounds__(kScanThreads) void scan_tiles(const int *in, int *out, int *bsum, long long n)
+__device__ __forceinline__ bool scan_skips(const int *passes, int pass) { return passes && pass >= *passes; }
+
+__global__ __launch_bounds__(kScanThreads) void scan_tiles(const int *in, int *out, int *bsum, long long n,
+                                                           const int *passes, int pass)
 {
+    if (scan_skips(passes, pass)) return;
     const long long base = (long long)blockIdx.x * kScanTile + (long long)threadIdx.x * kScanItems;
     SortPlace v[kScanItems];
     SortPlace s = 0;
@@ -367,8 +372,9 @@ __global__ __launch_bounds__(kScanThreads) void scan_tiles(const int *in, int *o
     if (threadIdx.x == 0) bsum[blockIdx.x] = (int)tot;
 }
 
-__global__ __launch_bounds__(kScanThreads) void scan_sums(int *bsum, int nb, int *total)
+__global__ __launch_bounds__(kScanThreads) void scan_sums(int *bsum, int nb, int *total, const int *passes, int pass)
 {
+    if (scan_skips(passes, pass)) return;
     // nb <= kScanTile * kScanTile is guaranteed by the launcher (chunks of 2048)
     SortPlace carry = 0;
     for (int base = 0; base < nb; base += kScanTile) {
@@ -390,24 +396,27 @@ __global__ __launch_bounds__(kScanThreads) void scan_sums(int *bsum, int nb, int
     if (threadIdx.x == 0 && total) *total = (int)carry;
 }
 
-__global__ __launch_bounds__(kScanThreads) void scan_add(int *out, const int *bsum, long long n)
+__global__ __launch_bounds__(kScanThreads) void scan_add(int *out, const int *bsum, long long n, const int *passes,
+                                                         int pass)
 {
+    if (scan_skips(passes, pass)) return;
     const long long base = (long long)blockIdx.x * kScanTile + (long long)threadIdx.x * kScanItems;
     const SortPlace add = bsum[blockIdx.x];
     for (int k = 0; k < kScanItems; ++k)
         if (base + k < n) out[base + k] = (int)(out[base + k] + add);
 }
 
-void launch_exclusive_scan(const int *in, int *out, int *bsum, long long n, int *total, hipStream_t s)
+void launch_exclusive_scan(const int *in, int *out, int *bsum, long long n, int *total, hipStream_t s,
+                           const int *passes, int pass)
 {
     const int nb = (int)((n + kScanTile - 1) / kScanTile);
     if (nb == 0) {
         if (total) hipMemsetAsync(total, 0, sizeof(int), s);
         return;
     }
-    hipLaunchKernelGGL(scan_tiles, dim3(nb), dim3(kScanThreads), 0, s, in, out, bsum, n);
-    hipLaunchKernelGGL(scan_sums, dim3(1), dim3(kScanThreads), 0, s, bsum, nb, total);
-    hipLaunchKernelGGL(scan_add, dim3(nb), dim3(kScanThreads), 0, s, out, bsum, n);
+    hipLaunchKernelGGL(scan_tiles, dim3(nb), dim3(kScanThreads), 0, s, in, out, bsum, n, passes, pass);
+    hipLaunchKernelGGL(scan_sums, dim3(1), dim3(kScanThreads), 0, s, bsum, nb, total, passes, pass);
+    hipLaunchKernelGGL(scan_add, dim3(nb), dim3(kScanThreads), 0, s, out, bsum, n, passes, pass);
 }
 
 // ---------------------------------------------------------------- radix sort
@@ -519,11 +528,12 @@ __global__ __launch_bounds__(1024) void sort_pass(const ViewArgs a, int pass)
 // per tile (digit-major, the query side's after the reference side's), the
 // scan of all of them, and the scatter.  The scan runs on from one side to
 // the next as their keys do, so its values are places in the joint buffers.
-// (A side that needs no more passes still counts, so that holds for the other.)
+// (A side that needs no more passes still counts, so that holds for the other;
+// beyond the last pass of both nothing is counted or moved.)
 __global__ __launch_bounds__(1024) void radix_hist(const ViewArgs a, int pass, int *hist)
 {
     const int side = blockIdx.y, ntiles = tiles_of(a.n[side]);
-    if (blockIdx.x >= ntiles || a.info->overflow) return;
+    if (blockIdx.x >= ntiles || a.info->overflow || pass >= a.info->passes) return;
     __shared__ int h[256];
     if (threadIdx.x < 256) h[threadIdx.x] = 0;
     __syncthreads();
@@ -886,9 +896,9 @@ __global__ __launch_bounds__(kClusThreads) void cluster_kernel(const ViewArgs a,
         if (__all(mine == first)) {
             unsigned long long sum = C;
             for (int off = 32; off > 0; off >>= 1) sum += __shfl_xor(sum, off);
-            if (lane == 0) atomicAdd(&a.cp[first].cand, sum);
+            if (lane == 0) atomicAdd(&a.cand[first], sum);
         } else if (tid < nh) {
-            atomicAdd(&a.cp[mine].cand, (unsigned long long)C);
+            atomicAdd(&a.cand[mine], (unsigned long long)C);
         }
     }
     __syncthreads();
@@ -931,7 +941,7 @@ __global__ __launch_bounds__(256) void plan_kernel(const ViewArgs a)
         n = rec->n;
         C = rec->cand;
         first = rec->first;
-        const unsigned long long even = (a.cp[rec->b].cand / kPieceTarget + 63) & ~63ULL;
+        const unsigned long long even = (a.cand[rec->b] / kPieceTarget + 63) & ~63ULL;
         const int floor_ = (int)min(max(even, (unsigned long long)kPieceFew), (unsigned long long)kPieceMany);
         const int cm = max(floor_, a.work / n);
         np = C > 0 ? min((C + cm - 1) / cm, 4096) : 1;
@@ -949,12 +959,8 @@ __global__ __launch_bounds__(256) void plan_kernel(const ViewArgs a)
     __syncthreads();
     for (int k = tid; k < kCostBuckets; k += 256)
         if (s_hist[k] > 0) s_hist[k] = atomicAdd(&a.info->hist[k], s_hist[k]);
-    if (tid == 0) {
-        const unsigned long long tp = s_w[0] + s_w[1] + s_w[2] + s_w[3];
-        const unsigned long long ts = s_w2[0] + s_w2[1] + s_w2[2] + s_w2[3];
-        atomicAdd(&a.info->pieces, tp);
-        s_base = atomicAdd(&a.info->slots, ts);
-    }
+    if (tid == 0) s_base = atomicAdd(&a.info->slots, (unsigned long long)(s_w2[0] + s_w2[1] + s_w2[2] + s_w2[3]));
+    if (tid == 64) atomicAdd(&a.info->pieces, (unsigned long long)(s_w[0] + s_w[1] + s_w[2] + s_w[3]));
     __syncthreads();
     int slot = (int)s_base + is - ns;  // (of no use, and not used, in a plan that does not fit)
     for (int w = 0; w < wv; ++w) slot += s_w2[w];
@@ -1067,7 +1073,7 @@ void launch_views(const ViewArgs &a, const FeatLayout &lay, double kappa, hipStr
             const long long ints = 256LL * (tiles_of(a.n[0]) + tiles_of(a.n[1]));
             for (int p = 0; p < passes; ++p) {
                 hipLaunchKernelGGL(radix_hist, dim3(tiles, 2), dim3(kRadixTile), 0, s, a, p, a.table);
-                launch_exclusive_scan(a.table, a.table, a.bsum, ints, nullptr, s);
+                launch_exclusive_scan(a.table, a.table, a.bsum, ints, nullptr, s, &a.info->passes, p);
                 hipLaunchKernelGGL(radix_scatter, dim3(tiles, 2), dim3(kRadixTile), 0, s, a, p, a.table);
             }
         }

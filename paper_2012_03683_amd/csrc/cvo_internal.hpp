@@ -155,12 +155,10 @@ struct alignas(16) ClusterParam {
     double cap;            // largest cluster bounding-box edge (chunk rule)
     int level;             // largest octree level of a cluster (octree rule)
     int bits;              // curve bits per axis of this pair
-    unsigned long long cand;  // candidates of its clusters (counted by the planner)
 };
 
 // State of one view build, on the device.
 struct BuildInfo {
-    unsigned long long pieces; // pieces planned
     unsigned long long slots;  // output slots planned
     long long cells;           // cell-table entries of all pairs
     int bad;                   // a cloud has a non-finite coordinate
@@ -168,14 +166,18 @@ struct BuildInfo {
     int nclus;                 // clusters of all pairs
     int kbits, mbits;          // cell-index bits, curve bits per axis, the most of any pair (the pair index sits above)
     int sbits[2];              // key bits to sort: reference side, query side
+    int passes;                // passes of the sort, the most of either side
     int hist[kCostBuckets];    // pieces per cost bucket
+    // pieces planned (each block of the planner adds to this and to the slots: apart,
+    // the two do not wait for each other)
+    alignas(128) unsigned long long pieces;
 };
 
 // What kernels tell a waiting host without a copy: pinned host memory, written
 // with system-scope stores.
 constexpr int kMailStates = 4;
 struct alignas(64) HostMail {
-    // the head of BuildInfo, then the number of the build it belongs to
+    // the counts of BuildInfo, then the number of the build they belong to
     unsigned long long pieces, slots;
     long long cells;
     int bad, overflow;

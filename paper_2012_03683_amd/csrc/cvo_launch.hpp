@@ -22,6 +22,10 @@ struct ViewArgs {
     int boxblocks;                // partial boxes per cloud
     GridDesc *grid;               // B
     ClusterParam *cp;             // B
+    // B: candidates of each pair's clusters.  Added to by every block of the cluster
+    // kernel, so apart from what all of them read (beside the parameters, 8 million
+    // points took 2.0 instead of 0.8 ms).
+    unsigned long long *cand;
     BuildInfo *info;
     long long cell_cap;           // entries the cell table has room for
     // keys and values of both sides, [0, n[0]) and [n[0], n[0] + n[1]), and
@@ -51,7 +55,9 @@ void launch_records(const ViewArgs &a, hipStream_t s);
 long long view_table_ints(long long n0, long long n1);  // entries of ViewArgs.table
 long long view_bsum_ints(long long n0, long long n1);   // entries of ViewArgs.bsum
 
-void launch_exclusive_scan(const int *in, int *out, int *bsum, long long n, int *total, hipStream_t s);
+// (passes, on the device, may be null: nothing is done if pass is not below it)
+void launch_exclusive_scan(const int *in, int *out, int *bsum, long long n, int *total, hipStream_t s,
+                           const int *passes = nullptr, int pass = 0);
 
 // pair pass: mode 0 = forward moments, 1 = backward (feature gradients)
 // returns false when no kernel exists for the feature layout
