@@ -900,15 +900,15 @@ void iteration_args(const Problem &p, int mode, double *trace, long long trace_r
 }
 
 void enqueue_iteration(cvo_context *ctx, Problem &p, int mode, double *trace, long long trace_rows, bool timed,
-                       HostMail *mail = nullptr)
+                       HostMail *mail = nullptr, int pass = 0)
 {
     PairPassArgs a;
     ReduceArgs r;
     iteration_args(p, mode, trace, trace_rows, a, r);
     r.mail = mail;
-    if (timed) run_pair_pass(ctx, a, p.lay, 0);
+    if (timed) run_pair_pass(ctx, a, p.lay, pass);
     else {
-        if (!launch_pair_pass(a, p.lay, 0, ctx->stream))
+        if (!launch_pair_pass(a, p.lay, pass, ctx->stream))
             throw CvoError(CVO_ERR_UNSUPPORTED, "no compiled pair kernel for the feature layout");
         ctx->timing.evaluations += 1;
     }
@@ -999,8 +999,9 @@ struct Evaluation {
 // Forward evaluations with the same spec and kernels, in one build, one pair
 // pass and one reduction.  A pair with an empty cloud keeps its initial state
 // (all sums zero).  may_split: the caller takes them one by one if they do not fit.
+// pass 2: only F and |P| are wanted (see launch_pair_pass).
 void evaluate_all(cvo_context *ctx, std::vector<Evaluation> &ev, const cvo_feature_spec *spec,
-                  const cvo_kernel_params *kp, bool ellobj = false, bool may_split = false)
+                  const cvo_kernel_params *kp, bool ellobj = false, bool may_split = false, int pass = 0)
 {
     check_spec(spec);
     const int D = spec_dim(spec);
@@ -1030,7 +1031,7 @@ void evaluate_all(cvo_context *ctx, std::vector<Evaluation> &ev, const cvo_featu
     setup_problem(ctx, p, xs, zs, st, ac, may_split);
     HostMail *mail = st.size() <= kMailStates ? ctx->mail() : nullptr;
     if (mail) std::memset(mail->state, 0, sizeof(PairState) * st.size());
-    enqueue_iteration(ctx, p, 0, nullptr, 0, ctx->profiling, mail);
+    enqueue_iteration(ctx, p, 0, nullptr, 0, ctx->profiling, mail, pass);
     if (mail) {
         ctx->wait();
         std::memcpy(st.data(), mail->state, sizeof(PairState) * st.size());
@@ -1047,10 +1048,10 @@ void evaluate_all(cvo_context *ctx, std::vector<Evaluation> &ev, const cvo_featu
 }
 
 void evaluate_one(cvo_context *ctx, const cvo_cloud *X, const cvo_cloud *Z, const cvo_feature_spec *spec,
-                  const cvo_kernel_params *kp, const double *T, PairState *out, bool ellobj = false)
+                  const cvo_kernel_params *kp, const double *T, PairState *out, bool ellobj = false, int pass = 0)
 {
     std::vector<Evaluation> ev{{X, Z, T, PairState{}}};
-    evaluate_all(ctx, ev, spec, kp, ellobj);
+    evaluate_all(ctx, ev, spec, kp, ellobj, false, pass);
     *out = ev[0].out;
 }
 
@@ -1313,7 +1314,7 @@ cvo_status cvo_inner_product(cvo_handle h, const cvo_cloud *X, const cvo_cloud *
     return guarded(h, [&] {
         require(F != nullptr, "F output is NULL");
         PairState s;
-        evaluate_one(h, X, Z, spec, kp, T, &s);
+        evaluate_one(h, X, Z, spec, kp, T, &s, false, 2);
         *F = s.F;
         if (n_pairs) *n_pairs = (int64_t)s.n_pairs;
     });

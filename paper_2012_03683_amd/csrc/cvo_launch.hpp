@@ -59,7 +59,9 @@ long long view_bsum_ints(long long n0, long long n1);   // entries of ViewArgs.b
 void launch_exclusive_scan(const int *in, int *out, int *bsum, long long n, int *total, hipStream_t s,
                            const int *passes = nullptr, int pass = 0);
 
-// pair pass: mode 0 = forward moments, 1 = backward (feature gradients)
+// pair pass: mode 0 = forward moments, 1 = backward (feature gradients), 2 = W and the
+// pair count alone, its terms in FP64 (LIN columns without SE columns; other layouts take
+// mode 0)
 // returns false when no kernel exists for the feature layout
 bool launch_pair_pass(const PairPassArgs &a, const FeatLayout &lay, int mode, hipStream_t s);
 

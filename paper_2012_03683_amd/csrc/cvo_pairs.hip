@@ -25,7 +25,8 @@
 //     kernel and every SE feature block together, the LIN dot product; W =
 //     sum w and D = sum w d are summed in FP32 over the flush and then added
 //     in FP64, S = sum w d d^T is summed in FP32.
-//     The backward takes its pairs in FP64 throughout.
+//     The backward, and an inner product of LIN columns alone, take their pairs in
+//     FP64 throughout.
 //   * Pairs whose FP32 squared distance lies within a proven error band of
 //     the cutoff are decided again with the FP64 expression that defines the
 //     pair set, so |P| is exact.
@@ -118,6 +119,8 @@ void pair_pass_kernel(const PairPassArgs a)
     // coordinates relative to the cluster centre and the source index's bits
     // (one float4; backward: FP64, two), then the feature row
     constexpr int C4 = MODE == 0 ? 1 : 2, E4 = C4 + F4;
+    // (see launch_pair_pass for the modes)
+    constexpr bool kGrad = MODE == 1;
     __shared__ float4 s_q[kWavesPerBlock][kQueueCap * E4];
     __shared__ int s_row[kWavesPerBlock][kWave];
 
@@ -220,10 +223,10 @@ void pair_pass_kernel(const PairPassArgs a)
             cull2 = uniform_f((float)(Rq * Rq * ascale));
         }
         if (!active) hi = -1.0f;  // (takes no pair)
-        // (backward) the LIN columns of the query's features in FP64, where the
+        // (FP64 terms) the LIN columns of the query's features in FP64, where the
         // registers hold them beside the sums of all columns; else they are
         // converted for each pair
-        constexpr bool kHoldV = MODE == 1 && LIND > 0 && 2 * D4 + 2 * LIND + SED <= 150;
+        constexpr bool kHoldV = MODE != 0 && LIND > 0 && (kGrad ? 2 * D4 : 0) + 2 * LIND + SED <= 150;
         double vl[kHoldV ? LIND : 1];
         vl[0] = 0.0;
 #pragma unroll
@@ -318,7 +321,7 @@ void pair_pass_kernel(const PairPassArgs a)
                 S22 = fmaf(wz, dz, S22);
             }
         };
-        // The backward's pair is FP64 but for the sum over the SE columns: the
+        // The pair of modes 1 and 2 is FP64 but for the sum over the SE columns: the
         // distance, the LIN dot, the weight and all sums.  With signed LIN weights
         // the terms of sum w s' cancel 10^3 to 10^4 times, and dF/dell keeps
         // what their rounding leaves: 10,000 points of 32 LIN columns, twelve
@@ -329,11 +332,12 @@ void pair_pass_kernel(const PairPassArgs a)
         // exponential (both sides' pass): those 10,000 points 100 -> 137 us,
         // 20,011 x 17,389 of 5 SE + 19 LIN 197 -> 277 us, 40,000 RGB-D of 5 SE
         // 132 -> 204 us.
-        auto grad_term = [&](const Coords &c, const float4 *ent, unsigned long long valid) {
+        auto exact_term = [&](const Coords &c, const float4 *ent, unsigned long long valid) {
             const double dx = c.dx() - zsx, dy = c.dy() - zsy, dz = c.dz() - zsz;
             const double s = fma(dz, dz, fma(dy, dy, dx * dx));
             const unsigned long long take = members((float)s, ent, valid);
-            paired |= take;
+            if (kGrad) paired |= take;
+            else cnt += __popcll(take);
             if (__builtin_amdgcn_inverse_ballot_w64(take)) {
                 float se = 0.0f, rest = 0.0f;
                 double lin = 0.0;
@@ -363,6 +367,7 @@ void pair_pass_kernel(const PairPassArgs a)
                 const double wn = exp2_neg(E);
                 const double w = (LIND > 0) ? wn * (kHoldV ? lin : lin + (double)rest) : wn;
                 W += w;
+                if (!kGrad) return;
                 Dx = fma(w, dx, Dx);
                 Dy = fma(w, dy, Dy);
                 Dz = fma(w, dz, Dz);
@@ -395,7 +400,7 @@ void pair_pass_kernel(const PairPassArgs a)
             const float4 *ent = &s_q[wv][qs * E4];
             const int step = SUB * E4;
             auto one = [&](const Coords &c, const float4 *at, unsigned long long in) {
-                if (MODE == 1) return grad_term(c, at, in);
+                if (MODE != 0) return exact_term(c, at, in);
                 const float dx = c.a.x - zrx, dy = c.a.y - zry, dz = c.a.z - zrz;
                 const float s = fmaf(dz, dz, fmaf(dy, dy, dx * dx));
                 pair_term(dx, dy, dz, s, at, in);
@@ -558,7 +563,7 @@ void pair_pass_kernel(const PairPassArgs a)
                 S11 += __shfl_xor(S11, off);
                 S12 += __shfl_xor(S12, off);
                 S22 += __shfl_xor(S22, off);
-            } else {
+            } else if (kGrad) {
                 Ls += __shfl_xor(Ls, off);
 #pragma unroll
                 for (int k = 0; k < (MODE == 1 ? VF : 1); ++k) Gf[k] += __shfl_xor(Gf[k], off);
@@ -581,7 +586,7 @@ void pair_pass_kernel(const PairPassArgs a)
             // value over the cluster's queries
             const double sg = (double)sig2;
             const long long f = pc.w;
-            if (MODE == 0) {
+            if (!kGrad) {  // (mode 2: D and S are zero)
                 double *B = a.oWD + 4 * f + t;
                 B[0] = sg * W;
                 B[n] = sg * Dx;
@@ -623,6 +628,13 @@ bool pair_layout_supported(int sed, int lind)
     return false;
 }
 
+// Layouts whose inner product takes FP64 terms: LIN columns, whose signed weights may
+// cancel (10,000 points of 32, twelve draws, F's largest relative error against 64 bits
+// 1.1e-6 -> 4.9e-8, the FP32 result's own rounding; pass 36 -> 50 us), without SE
+// columns beside them, whose rounding to FP32 when they are scaled leaves as much
+// (5 SE + 19 LIN, 20,011 points, would take 103 instead of 61 us).
+constexpr bool pair_exact(int sed, int lind) { return sed == 0 && lind > 0; }
+
 template <int S, int L, int MODE>
 static void launch_one(const PairPassArgs &a, hipStream_t s)
 {
@@ -635,8 +647,9 @@ bool launch_pair_pass(const PairPassArgs &a, const FeatLayout &lay, int mode, hi
     if (a.npieces <= 0) return true;
 #define CVO_LAUNCH(S, L)                                          \
     if (lay.sed == S && lay.lind == L) {                          \
-        if (mode == 0) launch_one<S, L, 0>(a, s);                 \
-        else launch_one<S, L, 1>(a, s);                           \
+        if (mode == 1) launch_one<S, L, 1>(a, s);                 \
+        else if (mode == 2 && pair_exact(S, L)) launch_one<S, L, pair_exact(S, L) ? 2 : 0>(a, s); \
+        else launch_one<S, L, 0>(a, s);                           \
         return true;                                              \
     }
     CVO_LAYOUTS(CVO_LAUNCH)
